@@ -972,7 +972,7 @@ __global__ __launch_bounds__(256) void k_refresh_neighbours(const int32_t *__res
     }
 }
 
-__global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, DevMesh m, int nc) {
+static __global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, DevMesh m, int nc) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n * nc) return;
     const int P = list[e / nc];
@@ -1181,7 +1181,7 @@ __device__ inline int item_count(const SimDesc &d, int L, int kind) {
     return kind == 0 ? d.nids[L] : (kind == 1 ? d.niface[L] : (d.force_on ? d.nsolid[L] : 0));
 }
 
-__global__ void k_batch_items(const SimDesc *__restrict__ sims, int nsims, uint32_t *__restrict__ items,
+static __global__ void k_batch_items(const SimDesc *__restrict__ sims, int nsims, uint32_t *__restrict__ items,
                               int64_t stride, int32_t *__restrict__ counts) {
     const int s = blockIdx.y, L = blockIdx.z / 3, kind = blockIdx.z % 3;
     __shared__ int s_off, s_n;
@@ -1288,7 +1288,7 @@ __global__ __launch_bounds__(256) void k_exchange_batch(const SimDesc *__restric
 // ---------------------------------------------------------------------------
 // Per-level totals of the momentum exchange over the active blocks (one
 // workgroup per level, fixed summation order): out[L][0..2].
-__global__ __launch_bounds__(256) void k_force_sum(DevMesh m, double *out) {
+static __global__ __launch_bounds__(256) void k_force_sum(DevMesh m, double *out) {
     __shared__ double s[3][256];
     const int L = blockIdx.x, t = threadIdx.x;
     double a[3] = {0.0, 0.0, 0.0};
@@ -1307,16 +1307,9 @@ __global__ __launch_bounds__(256) void k_force_sum(DevMesh m, double *out) {
         for (int c = 0; c < 3; c++) out[L * 3 + c] = s[c][0];
 }
 
-__global__ void k_force_reset(DevMesh m) {
+static __global__ void k_force_reset(DevMesh m) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < (int64_t)m.cap * 3) m.force[e] = 0.0;
-}
-
-void launch_force_sum(const Ctx &c, double *out) { k_force_sum<<<c.m.lmax, 256, 0, c.stream>>>(c.m, out); }
-
-void launch_force_reset(const Ctx &c) {
-    const int64_t n = (int64_t)c.m.cap * 3;
-    k_force_reset<<<(int)((n + 255) / 256), 256, 0, c.stream>>>(c.m);
 }
 
 // ---------------------------------------------------------------------------
@@ -1690,7 +1683,7 @@ __device__ inline void tree_sum4(double (*s)[256], double *v) {
     }
 }
 
-__global__ __launch_bounds__(256) void k_mass_chunks(double *part4, int cap) {
+static __global__ __launch_bounds__(256) void k_mass_chunks(double *part4, int cap) {
     __shared__ double s[4][256];
     const int64_t b0 = (int64_t)blockIdx.x * kMassChunk;
     const int64_t b1 = b0 + kMassChunk < cap ? b0 + kMassChunk : cap;
@@ -1701,7 +1694,7 @@ __global__ __launch_bounds__(256) void k_mass_chunks(double *part4, int cap) {
     if (threadIdx.x < 4) part4[b0 * 4 + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(256) void k_mass_final(const double *part4, int cap, double *out) {
+static __global__ __launch_bounds__(256) void k_mass_final(const double *part4, int cap, double *out) {
     __shared__ double s[4][256];
     const int nchunk = (cap + kMassChunk - 1) / kMassChunk;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1746,7 +1739,7 @@ __global__ __launch_bounds__(256) void k_mass_chunks_direct(DevMesh m, typename 
     if (t < 4) chunks[(int64_t)blockIdx.x * 4 + t] = s[t][0];
 }
 
-__global__ __launch_bounds__(256) void k_mass_final_direct(const double *chunks, int cap, double *out) {
+static __global__ __launch_bounds__(256) void k_mass_final_direct(const double *chunks, int cap, double *out) {
     __shared__ double s[4][256];
     const int nchunk = (cap + kMassChunk - 1) / kMassChunk;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1756,55 +1749,61 @@ __global__ __launch_bounds__(256) void k_mass_final_direct(const double *chunks,
     if (threadIdx.x < 4) out[threadIdx.x] = s[threadIdx.x][0];
 }
 
-// The chunk sums' storage: a fixed array in device memory, one copy per GPU
-// for the life of the process.  Host code uses the address resolved once per
-// device with hipGetSymbolAddress (mass_scratch), never the array's name.
-static __device__ __align__(256) double scratch[kMassStaticChunks * 4];
-
 // ---------------------------------------------------------------------------
-// dispatch over (lattice, storage)
-#define AMR_DISPATCH(qv, sv, BODY)                                                \
-    do {                                                                          \
-        switch ((qv) * 8 + (sv)) {                                                \
-        case 9 * 8 + AMR_F64: { constexpr int Qc = 9, Sc = AMR_F64; BODY; } break;   \
-        case 9 * 8 + AMR_F32: { constexpr int Qc = 9, Sc = AMR_F32; BODY; } break;   \
-        case 9 * 8 + AMR_F32S: { constexpr int Qc = 9, Sc = AMR_F32S; BODY; } break; \
-        case 9 * 8 + AMR_F16S: { constexpr int Qc = 9, Sc = AMR_F16S; BODY; } break; \
-        case 9 * 8 + AMR_BF16S: { constexpr int Qc = 9, Sc = AMR_BF16S; BODY; } break; \
-        case 19 * 8 + AMR_F64: { constexpr int Qc = 19, Sc = AMR_F64; BODY; } break;   \
-        case 19 * 8 + AMR_F32: { constexpr int Qc = 19, Sc = AMR_F32; BODY; } break;   \
-        case 19 * 8 + AMR_F32S: { constexpr int Qc = 19, Sc = AMR_F32S; BODY; } break; \
-        case 19 * 8 + AMR_F16S: { constexpr int Qc = 19, Sc = AMR_F16S; BODY; } break; \
-        case 19 * 8 + AMR_BF16S: { constexpr int Qc = 19, Sc = AMR_BF16S; BODY; } break; \
-        case 27 * 8 + AMR_F64: { constexpr int Qc = 27, Sc = AMR_F64; BODY; } break;   \
-        case 27 * 8 + AMR_F32: { constexpr int Qc = 27, Sc = AMR_F32; BODY; } break;   \
-        case 27 * 8 + AMR_F32S: { constexpr int Qc = 27, Sc = AMR_F32S; BODY; } break; \
-        case 27 * 8 + AMR_F16S: { constexpr int Qc = 27, Sc = AMR_F16S; BODY; } break; \
-        case 27 * 8 + AMR_BF16S: { constexpr int Qc = 27, Sc = AMR_BF16S; BODY; } break; \
-        default: break;                                                           \
-        }                                                                         \
-    } while (0)
-
-#define TPTR(Sc, p) ((typename Store<Sc>::T *)(p))
+// Launchers of one (lattice, storage).  Each pair is compiled in a unit of its
+// own (AMR_TU_Q, AMR_TU_S; the build lists them), side by side; the unit
+// without them holds the dispatch and what depends on neither.
+template <int Q, int S>
+struct Launch {
+    static bool collide_stream(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp,
+                               const BCParams &bc, bool exchange);
+    static bool interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
+                               const LevelParams &lp, const BCParams &bc, bool exchange);
+    static void interp(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells);
+    static void exchange(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp);
+    static void exchange_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                               int par, int grid);
+    static void collide_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                              int L, int par, int nt, int grid);
+    static void interp_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                             int L, int par0, int par1, int grid);
+    static void average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                              int L, int par0, int par1, int grid);
+    static void refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
+    static void average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U);
+    static void fill_rest(const Ctx &c);
+    static void set_rho_u_root(const Ctx &c, const double *ru, int b0, int b1);
+    static void velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children);
+    static void block_f(const Ctx &c, int set, int b0, int b1, double *stage, const LevelParams &lp);
+    static void out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage, const LevelParams &lp);
+    static void mass_blocks(const Ctx &c, const LevelParams &lp);
+    static void mass_chunks_direct(const Ctx &c, const LevelParams &lp, double *chunks);
+};
 
 static inline int grid_blocks(int64_t nblocks, int mb) {
     const int bpw = 256 / mb;
     return (int)((nblocks + bpw - 1) / bpw);
 }
 
+#ifdef AMR_TU_Q
+
+template <int S>
+static typename Store<S>::T *buf(const Ctx &c, int k) {
+    return (typename Store<S>::T *)c.f[k];
+}
+
 // A level sweep whose output exceeds c.stream_bytes (by default half the 256 MB
 // Infinity Cache) stores with non-temporal writes.  Smaller levels are still
 // cached when the next sweep (or the interpolation and averaging) reads them.
 template <int Q, int S>
-static bool collide_stream_nts(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp,
-                               const BCParams &bc, bool exchange) {
-    using T = typename Store<S>::T;
+bool Launch<Q, S>::collide_stream(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp,
+                                  const BCParams &bc, bool exchange) {
     const int sp = lp.par[L];
     constexpr int bpw = collide_blocks_per_wg<Q, S>();
     const int grid = (n + bpw - 1) / bpw;
-    const T *src = (const T *)c.f[sp];
-    T *dst = (T *)c.f[1 - sp];
-    const bool nts = (int64_t)n * Q * c.mb * (int64_t)sizeof(T) > c.stream_bytes;
+    const typename Store<S>::T *src = buf<S>(c, sp);
+    typename Store<S>::T *dst = buf<S>(c, 1 - sp);
+    const bool nts = (int64_t)n * Q * c.mb * (int64_t)sizeof(typename Store<S>::T) > c.stream_bytes;
     const int tpb = collide_threads<S>();
     const double om = lp.omega[L];
     if constexpr (Q == 27) {
@@ -1830,22 +1829,13 @@ static bool collide_stream_nts(const Ctx &c, const int32_t *list, int n, int L, 
     return false;
 }
 
-bool launch_collide_stream(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, const BCParams &bc,
-                           bool exchange) {
-    if (n <= 0) return false;
-    bool done = false;
-    AMR_DISPATCH(c.q, c.storage, (done = collide_stream_nts<Qc, Sc>(c, list, n, L, lp, bc, exchange)));
-    return done;
-}
-
 template <int Q, int S>
-static bool interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
-                           const LevelParams &lp, const BCParams &bc, bool exchange) {
-    using T = typename Store<S>::T;
+bool Launch<Q, S>::interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
+                                  const LevelParams &lp, const BCParams &bc, bool exchange) {
     constexpr int bpw = collide_blocks_per_wg<Q, S>();
     const int grid = ni + (nblk + bpw - 1) / bpw;
-    const bool nts = (int64_t)nblk * Q * c.mb * (int64_t)sizeof(T) > c.stream_bytes;
-    T *f0 = (T *)c.f[0], *f1 = (T *)c.f[1];
+    const bool nts = (int64_t)nblk * Q * c.mb * (int64_t)sizeof(typename Store<S>::T) > c.stream_bytes;
+    typename Store<S>::T *f0 = buf<S>(c, 0), *f1 = buf<S>(c, 1);
     if (exchange && !nts) {
         if (c.m.interp == AMR_INTERP_CUBIC)
             k_interp_collide<Q, S, false, 1, true><<<grid, 256, 0, c.stream>>>(ilist, ni, clist, nblk, c.m, f0, f1, lp, L, bc);
@@ -1863,42 +1853,29 @@ static bool interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int
     return false;
 }
 
-bool launch_interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
-                           const LevelParams &lp, const BCParams &bc, bool exchange) {
-    bool done = false;
-    AMR_DISPATCH(c.q, c.storage, (done = interp_collide<Qc, Sc>(c, ilist, ni, clist, nblk, L, lp, bc, exchange)));
-    return done;
-}
-
-void launch_interp(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells) {
-    if (n <= 0) return;
+template <int Q, int S>
+void Launch<Q, S>::interp(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells) {
     const int threads = c.dim == 2 ? 64 : 256;
     if (c.m.interp == AMR_INTERP_CUBIC)
-        AMR_DISPATCH(c.q, c.storage,
-                     (k_interp<Qc, Sc, 1><<<n, threads, 0, c.stream>>>(list, n, c.m, TPTR(Sc, c.f[0]),
-                                                                        TPTR(Sc, c.f[1]), lp, all_cells)));
+        k_interp<Q, S, 1><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
     else
-        AMR_DISPATCH(c.q, c.storage,
-                     (k_interp<Qc, Sc, 0><<<n, threads, 0, c.stream>>>(list, n, c.m, TPTR(Sc, c.f[0]),
-                                                                        TPTR(Sc, c.f[1]), lp, all_cells)));
-}
-
-void launch_exchange(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp) {
-    if (n <= 0) return;
-    const int bpw = 256 / c.mb;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_exchange<Qc, Sc><<<(n + bpw - 1) / bpw, 256, 0, c.stream>>>(list, n, c.m,
-                                                                               TPTR(Sc, c.f[lp.par[L]]))));
-}
-
-void launch_exchange_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                           const int32_t *count, int par, int grid) {
-    AMR_DISPATCH(q, storage, (k_exchange_batch<Qc, Sc><<<grid, 256, 0, stream>>>(sims, items, count, par)));
+        k_interp<Q, S, 0><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
 }
 
 template <int Q, int S>
-static void collide_batch_shape(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                                int L, int par, int nt, int grid) {
+void Launch<Q, S>::exchange(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp) {
+    k_exchange<Q, S><<<grid_blocks(n, c.mb), 256, 0, c.stream>>>(list, n, c.m, buf<S>(c, lp.par[L]));
+}
+
+template <int Q, int S>
+void Launch<Q, S>::exchange_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                                  int par, int grid) {
+    k_exchange_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, par);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::collide_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                                 int L, int par, int nt, int grid) {
     if (nt == 64)
         k_collide_stream_batch<Q, S, 64><<<grid, 64, 0, stream>>>(sims, items, count, L, par);
     else if (nt == 128)
@@ -1907,23 +1884,139 @@ static void collide_batch_shape(hipStream_t stream, const SimDesc *sims, const u
         k_collide_stream_batch<Q, S, 256><<<grid, 256, 0, stream>>>(sims, items, count, L, par);
 }
 
+template <int Q, int S>
+void Launch<Q, S>::interp_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                                int L, int par0, int par1, int grid) {
+    k_interp_batch<Q, S><<<grid, Q == 9 ? 64 : 256, 0, stream>>>(sims, items, count, L, par0, par1);
+}
+
+// one lane per fine cell of the workgroup's children
+template <int Q, int S>
+void Launch<Q, S>::average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                                 int L, int par0, int par1, int grid) {
+    k_average_batch<Q, S><<<grid, Q == 9 ? 64 : 256, 0, stream>>>(sims, items, count, L, par0, par1);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp) {
+    const int threads = c.dim == 2 ? 64 : 256;
+    k_refresh_neighbours<Q, S><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U) {
+    // one lane per fine cell of the workgroup's children; 3-D: two workgroups per parent
+    const int split = c.dim == 3 ? 2 : 1;
+    const int threads = c.nc / split * c.mb;
+    if (U) k_average<Q, S, true><<<n * split, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, 1, U);
+    else k_average<Q, S><<<n * split, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells, nullptr);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::fill_rest(const Ctx &c) {
+    const int64_t total = c.m.halo_base + (int64_t)c.m.cap * c.m.nh;
+    k_fill_rest<Q, S><<<(int)((total + 255) / 256), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), total);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::set_rho_u_root(const Ctx &c, const double *ru, int b0, int b1) {
+    k_set_rho_u<Q, S><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), ru, b0, b1);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children) {
+    const int64_t items = children ? (int64_t)n * c.nc : n;
+    k_velocity<Q, S><<<grid_blocks(items, c.mb), 256, 0, c.stream>>>(list, n, c.m, buf<S>(c, lp.par[L]), c.U,
+                                                                     children ? 1 : 0);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::block_f(const Ctx &c, int set, int b0, int b1, double *stage, const LevelParams &lp) {
+    k_block_f<Q, S><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), lp, set, b0, b1,
+                                                                      stage);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage,
+                              const LevelParams &lp) {
+    k_out_gather<Q, S><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), lp, kind, b0,
+                                                                         b1, c.off, off0, stage);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::mass_blocks(const Ctx &c, const LevelParams &lp) {
+    k_mass_blocks<Q, S><<<grid_blocks(c.m.cap, c.mb), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), lp, c.part4);
+}
+
+template <int Q, int S>
+void Launch<Q, S>::mass_chunks_direct(const Ctx &c, const LevelParams &lp, double *chunks) {
+    const int nchunk = (c.m.cap + kMassChunk - 1) / kMassChunk;
+    k_mass_chunks_direct<Q, S><<<nchunk, 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), lp, chunks);
+}
+
+template struct Launch<AMR_TU_Q, AMR_TU_S>;
+#else
+
+// X(Q, S) for every lattice and storage
+#define AMR_STORAGES(X, Q) X(Q, AMR_F64) X(Q, AMR_F32) X(Q, AMR_F32S) X(Q, AMR_F16S) X(Q, AMR_BF16S)
+#define AMR_PAIRS(X) AMR_STORAGES(X, 9) AMR_STORAGES(X, 19) AMR_STORAGES(X, 27)
+
+#define AMR_EXTERN(Qc, Sc) extern template struct Launch<Qc, Sc>;
+AMR_PAIRS(AMR_EXTERN)
+
+// calls fn(Launch<Q, S>()) of the run-time lattice and storage
+template <typename F>
+static void dispatch(int q, int storage, F &&fn) {
+    switch (q * 8 + storage) {
+#define AMR_CASE(Qc, Sc) case Qc * 8 + Sc: fn(Launch<Qc, Sc>()); break;
+        AMR_PAIRS(AMR_CASE)
+    default: break;
+    }
+}
+
+bool launch_collide_stream(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, const BCParams &bc,
+                           bool exchange) {
+    if (n <= 0) return false;
+    bool done = false;
+    dispatch(c.q, c.storage, [&](auto l) { done = l.collide_stream(c, list, n, L, lp, bc, exchange); });
+    return done;
+}
+
+bool launch_interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
+                           const LevelParams &lp, const BCParams &bc, bool exchange) {
+    bool done = false;
+    dispatch(c.q, c.storage, [&](auto l) { done = l.interp_collide(c, ilist, ni, clist, nblk, L, lp, bc, exchange); });
+    return done;
+}
+
+void launch_interp(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells) {
+    if (n <= 0) return;
+    dispatch(c.q, c.storage, [&](auto l) { l.interp(c, list, n, lp, all_cells); });
+}
+
+void launch_exchange(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp) {
+    if (n <= 0) return;
+    dispatch(c.q, c.storage, [&](auto l) { l.exchange(c, list, n, L, lp); });
+}
+
+void launch_exchange_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
+                           const int32_t *count, int par, int grid) {
+    dispatch(q, storage, [&](auto l) { l.exchange_batch(stream, sims, items, count, par, grid); });
+}
+
 void launch_collide_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
                           const int32_t *count, int L, int par, int nt, int grid) {
-    AMR_DISPATCH(q, storage, (collide_batch_shape<Qc, Sc>(stream, sims, items, count, L, par, nt, grid)));
+    dispatch(q, storage, [&](auto l) { l.collide_batch(stream, sims, items, count, L, par, nt, grid); });
 }
 
 void launch_interp_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
                          const int32_t *count, int L, int par0, int par1, int grid) {
-    const int threads = q == 9 ? 64 : 256;
-    AMR_DISPATCH(q, storage,
-                 (k_interp_batch<Qc, Sc><<<grid, threads, 0, stream>>>(sims, items, count, L, par0, par1)));
+    dispatch(q, storage, [&](auto l) { l.interp_batch(stream, sims, items, count, L, par0, par1, grid); });
 }
 
 void launch_average_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
                           const int32_t *count, int L, int par0, int par1, int grid) {
-    const int threads = q == 9 ? 64 : 256;  // one lane per fine cell of the workgroup's children
-    AMR_DISPATCH(q, storage,
-                 (k_average_batch<Qc, Sc><<<grid, threads, 0, stream>>>(sims, items, count, L, par0, par1)));
+    dispatch(q, storage, [&](auto l) { l.average_batch(stream, sims, items, count, L, par0, par1, grid); });
 }
 
 void launch_batch_items(hipStream_t stream, const SimDesc *sims, int nsims, int lmax, int cap_max, uint32_t *items,
@@ -1935,49 +2028,27 @@ void launch_batch_items(hipStream_t stream, const SimDesc *sims, int nsims, int 
 
 void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp) {
     if (n <= 0) return;
-    const int threads = c.dim == 2 ? 64 : 256;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_refresh_neighbours<Qc, Sc><<<n, threads, 0, c.stream>>>(list, n, c.m, TPTR(Sc, c.f[0]),
-                                                                             TPTR(Sc, c.f[1]), lp)));
+    dispatch(c.q, c.storage, [&](auto l) { l.refresh_neighbours(c, list, n, lp); });
     k_clear_fresh<<<(n * c.nc + 255) / 256, 256, 0, c.stream>>>(list, n, c.m, c.nc);
-}
-
-template <int Q, int S>
-static void average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U) {
-    using T = typename Store<S>::T;
-    // one lane per fine cell of the workgroup's children; 3-D: two workgroups per parent
-    const int split = c.dim == 3 ? 2 : 1;
-    const int threads = c.nc / split * c.mb;
-    T *f0 = (T *)c.f[0], *f1 = (T *)c.f[1];
-    if (U) k_average<Q, S, true><<<n * split, threads, 0, c.stream>>>(list, n, c.m, f0, f1, lp, 1, U);
-    else k_average<Q, S><<<n * split, threads, 0, c.stream>>>(list, n, c.m, f0, f1, lp, all_cells, nullptr);
 }
 
 void launch_average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U) {
     if (n <= 0) return;
-    AMR_DISPATCH(c.q, c.storage, (average<Qc, Sc>(c, list, n, lp, all_cells, U)));
+    dispatch(c.q, c.storage, [&](auto l) { l.average(c, list, n, lp, all_cells, U); });
 }
 
 void launch_fill_rest(const Ctx &c) {
-    const int64_t total = c.m.halo_base + (int64_t)c.m.cap * c.m.nh;
-    const int grid = (int)((total + 255) / 256);
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_fill_rest<Qc, Sc><<<grid, 256, 0, c.stream>>>(c.m, TPTR(Sc, c.f[0]), TPTR(Sc, c.f[1]), total)));
+    dispatch(c.q, c.storage, [&](auto l) { l.fill_rest(c); });
 }
 
 void launch_set_rho_u_root(const Ctx &c, const double *ru, int b0, int b1) {
     if (b1 <= b0) return;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_set_rho_u<Qc, Sc><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(c.m, TPTR(Sc, c.f[0]), ru,
-                                                                                         b0, b1)));
+    dispatch(c.q, c.storage, [&](auto l) { l.set_rho_u_root(c, ru, b0, b1); });
 }
 
 void launch_velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children) {
     if (n <= 0) return;
-    const int64_t items = children ? (int64_t)n * c.nc : n;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_velocity<Qc, Sc><<<grid_blocks(items, c.mb), 256, 0, c.stream>>>(
-                     list, n, c.m, TPTR(Sc, c.f[lp.par[L]]), c.U, children ? 1 : 0)));
+    dispatch(c.q, c.storage, [&](auto l) { l.velocity(c, list, n, L, lp, children); });
 }
 
 void launch_vorticity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &) {
@@ -1991,17 +2062,25 @@ void launch_vorticity(const Ctx &c, const int32_t *list, int n, int L, const Lev
 
 void launch_block_f(const Ctx &c, int set, int b0, int b1, double *stage, const LevelParams &lp) {
     if (b1 <= b0) return;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_block_f<Qc, Sc><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(
-                     c.m, TPTR(Sc, c.f[0]), TPTR(Sc, c.f[1]), lp, set, b0, b1, stage)));
+    dispatch(c.q, c.storage, [&](auto l) { l.block_f(c, set, b0, b1, stage, lp); });
 }
 
 void launch_out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage, const LevelParams &lp) {
     if (b1 <= b0) return;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_out_gather<Qc, Sc><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(
-                     c.m, TPTR(Sc, c.f[0]), TPTR(Sc, c.f[1]), lp, kind, b0, b1, c.off, off0, stage)));
+    dispatch(c.q, c.storage, [&](auto l) { l.out_gather(c, kind, b0, b1, off0, stage, lp); });
 }
+
+void launch_force_sum(const Ctx &c, double *out) { k_force_sum<<<c.m.lmax, 256, 0, c.stream>>>(c.m, out); }
+
+void launch_force_reset(const Ctx &c) {
+    const int64_t n = (int64_t)c.m.cap * 3;
+    k_force_reset<<<(int)((n + 255) / 256), 256, 0, c.stream>>>(c.m);
+}
+
+// The chunk sums' storage: a fixed array in device memory, one copy per GPU
+// for the life of the process.  Host code uses the address resolved once per
+// device with hipGetSymbolAddress (mass_scratch), never the array's name.
+static __device__ __align__(256) double scratch[kMassStaticChunks * 4];
 
 int64_t mass_static_max_blocks() { return (int64_t)kMassStaticChunks * kMassChunk; }
 
@@ -2025,19 +2104,16 @@ hipError_t mass_scratch(int device, double **ptr) {
 }
 
 void launch_mass_static(const Ctx &c, const LevelParams &lp, double *chunks, double *out_dev) {
-    const int nchunk = (c.m.cap + kMassChunk - 1) / kMassChunk;
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_mass_chunks_direct<Qc, Sc><<<nchunk, 256, 0, c.stream>>>(c.m, TPTR(Sc, c.f[0]),
-                                                                            TPTR(Sc, c.f[1]), lp, chunks)));
+    dispatch(c.q, c.storage, [&](auto l) { l.mass_chunks_direct(c, lp, chunks); });
     k_mass_final_direct<<<1, 256, 0, c.stream>>>(chunks, c.m.cap, out_dev);
 }
 
 void launch_mass(const Ctx &c, const LevelParams &lp) {
-    AMR_DISPATCH(c.q, c.storage,
-                 (k_mass_blocks<Qc, Sc><<<grid_blocks(c.m.cap, c.mb), 256, 0, c.stream>>>(
-                     c.m, TPTR(Sc, c.f[0]), TPTR(Sc, c.f[1]), lp, c.part4)));
+    dispatch(c.q, c.storage, [&](auto l) { l.mass_blocks(c, lp); });
     k_mass_chunks<<<(c.m.cap + kMassChunk - 1) / kMassChunk, 256, 0, c.stream>>>(c.part4, c.m.cap);
     k_mass_final<<<1, 256, 0, c.stream>>>(c.part4, c.m.cap, c.ctr->mass);
 }
+
+#endif  // AMR_TU_Q
 
 }  // namespace amr
