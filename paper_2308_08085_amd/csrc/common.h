@@ -161,6 +161,26 @@ struct HaloIndex {
     }
 };
 template <typename Lt> constexpr HaloIndex<Lt> kHalo{};
+// The same numbering without a table: entry = base[p] + the number of cells
+// below l whose source lies outside (a constant mask and a bit count instead of
+// a dependent load per population).
+template <typename Lt>
+struct HaloMask {
+    uint64_t out[Lt::Q];
+    int base[Lt::Q];
+    constexpr HaloMask() : out(), base() {
+        int n = 0;
+        for (int p = 0; p < Lt::Q; p++) {
+            base[p] = n;
+            for (int l = 0; l < Lt::MB; l++)
+                if (kHalo<Lt>.idx[p][l] >= 0) {
+                    out[p] |= uint64_t(1) << l;
+                    n++;
+                }
+        }
+    }
+};
+template <typename Lt> constexpr HaloMask<Lt> kHaloMask{};
 inline int halo_entries(int q) {
     return q == 9 ? kHalo<Lat<9>>.n : (q == 19 ? kHalo<Lat<19>>.n : kHalo<Lat<27>>.n);
 }
@@ -180,11 +200,28 @@ struct DevMesh {
     int32_t *hid;       // halo record of each block, -1 if it has no N_SKIP link
     int32_t *parent;    // parent block, -1 on the root level
     int8_t *fresh;      // 1 for blocks created by the adaptation in progress
+    int32_t *desc;      // [cap][Desc<D>::kWords] packed block descriptors
     int32_t *nbr, *nbrc, *X;
     int8_t *level, *status, *tag, *ldes, *viol;
     uint8_t *bflag;
     uint64_t *gmask, *imask;  // ghost / interface cell bitmasks (bit l)
 };
+
+// Packed descriptor of an active block, one aligned 128-byte line (2-D: half a
+// line): the links in region-slot order, then what a solver kernel needs
+// before it can address the block's populations.  One coalesced load per wave
+// takes the place of a load from each of the 27 (9) link arrays and two more.
+// Rebuilt with the masks and lists after every adaptation.
+template <int D>
+struct Desc {
+    static constexpr int kWords = D == 2 ? 16 : 32;
+    static constexpr int kLinks = D == 2 ? 9 : 27;
+    static constexpr int kHid = kLinks;        // halo record, -1 none
+    static constexpr int kFlags = kLinks + 1;  // BF_* | DF_LEAF | level << 16
+    static constexpr int kFirst = kLinks + 2;  // first child, kNone for a leaf
+    static constexpr int kGhost = kLinks + 3;  // ghost cells: 64 bits (3-D); 2-D: ghost | interface << 16
+};
+constexpr uint32_t DF_LEAF = 1u << 8;
 
 struct BCParams {
     int32_t kind[6];

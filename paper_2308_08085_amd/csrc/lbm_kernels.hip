@@ -8,6 +8,7 @@
 // every kernel finds population p of a cell with entry_slot().
 #include <algorithm>
 #include <mutex>
+#include <utility>
 
 #include "kernels.h"
 
@@ -154,11 +155,12 @@ struct InteriorLane {
     uint32_t own;         // byte offset of the lane's own cell in a row
 };
 
-template <typename T>
+template <typename T, typename Lt = D3>
 __device__ __forceinline__ InteriorLane interior_lane(const uint64_t *tab, int i, int j, int k) {
     InteriorLane u;
-    // LDS byte offset of the table (the pointer cast to the local address space)
-    const uint32_t t = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint64_t *)tab + 13u * 8u;
+    // LDS byte offset of the table's centre entry (the pointer cast to the local address space)
+    const uint32_t t = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint64_t *)tab +
+                       (uint32_t)kCenterSlot<Lt> * 8u;
     u.x0 = t;
     u.xm = t + (i == 3 ? 8u : 0u);
     u.xp = t - (i == 0 ? 8u : 0u);
@@ -170,30 +172,157 @@ __device__ __forceinline__ InteriorLane interior_lane(const uint64_t *tab, int i
     return u;
 }
 
+// f(std::integral_constant<int, 0>()) .. f(<N - 1>): an unrolled loop whose
+// index is a constant expression
+template <typename F, int... P>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, P...>) {
+    (f(std::integral_constant<int, P>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// row-table entry of the region that population P of the lane's cell streams
+// from (for opp(P): the region that its population P leaves to)
+template <typename Lt, int P>
+__device__ __forceinline__ uint64_t row_entry(const InteriorLane &u) {
+    constexpr int cx = Lt::cx(P), cy = Lt::cy(P), cz = Lt::cz(P);
+    const uint32_t ex = cx < 0 ? u.xm : (cx > 0 ? u.xp : u.x0);
+    const uint32_t ey = cy < 0 ? u.ym : (cy > 0 ? u.yp : 0u);
+    const uint32_t ez = cz < 0 ? u.zm : (cz > 0 ? u.zp : 0u);
+    return *(const __attribute__((address_space(3))) uint64_t *)(uintptr_t)(ex + ey + ez);
+}
+
+// byte offset of population P from a row-table entry plus the lane's own offset
+template <typename Lt, typename T, int P>
+constexpr int64_t row_offset() {
+    return ((int64_t)P * Lt::MB - (Lt::cx(P) + 4 * Lt::cy(P) + 16 * Lt::cz(P))) * (int64_t)sizeof(T);
+}
+
+// a global-memory pointer, so that a load is a global (not flat) load and does
+// not hold up the waits on the LDS table reads
+template <typename T>
+__device__ __forceinline__ T *global_ptr(uint64_t a) {
+    return (T *)(__attribute__((address_space(1))) T *)a;
+}
+
 // out[p] = conv(stored value of population p, p) for every population
-template <typename Lt, typename ST, int P, typename Out, typename Conv>
+template <typename Lt, typename ST, typename Out, typename Conv>
 __device__ __forceinline__ void gather_interior_by(const InteriorLane &u, Out *out, Conv conv) {
-    if constexpr (P < Lt::Q) {
-        using T = typename ST::T;
-        constexpr int cx = Lt::cx(P), cy = Lt::cy(P), cz = Lt::cz(P);
-        const uint32_t ex = cx < 0 ? u.xm : (cx > 0 ? u.xp : u.x0);
-        const uint32_t ey = cy < 0 ? u.ym : (cy > 0 ? u.yp : 0u);
-        const uint32_t ez = cz < 0 ? u.zm : (cz > 0 ? u.zp : 0u);
-        const uint64_t row = *(const __attribute__((address_space(3))) uint64_t *)(uintptr_t)(ex + ey + ez);
-        constexpr int64_t c = (int64_t)P * Lt::MB - (cx + 4 * cy + 16 * cz);
-        // a global-memory pointer, so the load is a global (not flat) load and
-        // does not hold up the waits on the LDS table reads
-        const T *a = (const T *)(const __attribute__((address_space(1))) T *)(row + u.own) + c;
-        out[P] = conv(ST::ld(a), P);
-        gather_interior_by<Lt, ST, P + 1>(u, out, conv);
-    }
+    using T = typename ST::T;
+    static_for<Lt::Q>([&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        const uint64_t row = row_entry<Lt, P>(u);
+        out[P] = conv(ST::ld(global_ptr<const T>(row + u.own + row_offset<Lt, T, P>())), P);
+    });
 }
 
 // the shifted populations g (as load_g; RAW: the stored values)
 template <typename Lt, typename ST, bool RAW = false>
 __device__ __forceinline__ void gather_interior(const InteriorLane &u, typename ST::R *g) {
     using R = typename ST::R;
-    gather_interior_by<Lt, ST, 0>(u, g, [](R v, int p) { return (ST::shift || RAW) ? v : v - R(Lt::w(p)); });
+    gather_interior_by<Lt, ST>(u, g, [](R v, int p) { return (ST::shift || RAW) ? v : v - R(Lt::w(p)); });
+}
+
+// ---------------------------------------------------------------------------
+// A block's descriptor and row table, handled by the lanes of the block alone:
+// a wave in 3-D, 16 lanes in 2-D.  Nothing is shared between waves, so no wave
+// waits for another: list entry, descriptor, populations are the only
+// dependent loads.  With the links staged from the 27 link arrays by the whole
+// workgroup (three barriers, one cache line per link and block) and a branch
+// per population for blocks with walls or coarser neighbours, a D3Q27 sweep of
+// the cylinder (4.2e5 blocks) took 1,360 us with FP32 and 871 us with FP16
+// storage, now 1,297 and 744 us (4.55 and 4.00 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0, now
+// 30.2 us; a D2Q9 FP64 sweep of 64 blocks 7.2, now 5.3 us; a coarse step of 32
+// mixed cavities in a batch 870, now 700 us.  An entry whose link is not a block holds the link code,
+// sign extended, so it is negative as an int64.
+template <typename Lt> constexpr int kTab = Desc<Lt::D>::kWords;  // table entries per block
+
+// orders the LDS writes of a wave before its later LDS reads
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// word `lane` of the descriptor of block B (0 past its end; B < 0: zeros)
+template <typename Lt>
+__device__ __forceinline__ int32_t desc_word(const int32_t *__restrict__ desc, int B, int lane) {
+    constexpr int NW = Desc<Lt::D>::kWords;
+    return lane < NW && B >= 0 ? desc[(int64_t)B * NW + lane] : 0;
+}
+
+// word k of the descriptor whose words the block's lanes hold
+template <typename Lt>
+__device__ __forceinline__ int32_t desc_get(int32_t w, int k) {
+    if constexpr (Lt::D == 3) return __builtin_amdgcn_readlane(w, k);
+    else return __shfl(w, k, 16);
+}
+
+// the row table of a block from its descriptor words (`base`: a distribution buffer)
+template <typename Lt, typename T>
+__device__ __forceinline__ void put_rows(uint64_t *tab, int32_t w, int lane, const T *base) {
+    if (lane < Desc<Lt::D>::kLinks) {
+        const int rx = lane % 3 - 1, ry = (lane / 3) % 3 - 1, rz = Lt::D == 3 ? lane / 9 - 1 : 0;
+        const int64_t el = (int64_t)w * (Lt::Q * Lt::MB) - 4 * (rx + 4 * ry + 16 * rz);
+        tab[lane] = w >= 0 ? (uint64_t)(uintptr_t)base + (uint64_t)(el * (int64_t)sizeof(T)) : (uint64_t)(int64_t)w;
+    }
+}
+
+// Addresses of the populations of one cell of a block with any links.
+template <typename T>
+struct CellRows {
+    InteriorLane u;
+    uint64_t own;    // the cell's own slot of population 0
+    uint64_t halo;   // the block's halo record
+    uint64_t below;  // bits of the cells below the lane's cell
+};
+
+template <typename Lt, typename T>
+__device__ __forceinline__ CellRows<T> cell_rows(const uint64_t *tab, int B, int h, int l, const T *base,
+                                                 const DevMesh &m) {
+    CellRows<T> r;
+    r.u = interior_lane<T, Lt>(tab, l & 3, (l >> 2) & 3, l >> 4);
+    r.own = (uint64_t)(uintptr_t)(base + (int64_t)B * (Lt::Q * Lt::MB)) + r.u.own;
+    r.halo = (uint64_t)(uintptr_t)(base + (m.halo_base + (int64_t)h * m.nh));
+    r.below = (uint64_t(1) << l) - 1;
+    return r;
+}
+
+// entry of population P of a cell in the block's halo record
+template <typename Lt, int P>
+__device__ __forceinline__ uint32_t halo_entry(uint64_t below) {
+    constexpr uint64_t out = kHaloMask<Lt>.out[P];
+    uint32_t n = kHaloMask<Lt>.base[P] + __popc((uint32_t)out & (uint32_t)below);
+    if constexpr (Lt::MB == 64) n += __popc((uint32_t)(out >> 32) & (uint32_t)(below >> 32));
+    return n;
+}
+
+// address of population P: its source's slot on the same level, the halo
+// record (HALO: the block has a coarser neighbour), or the cell's own opposite slot
+template <typename Lt, typename T, int P, bool HALO>
+__device__ __forceinline__ uint64_t slot_address(const CellRows<T> &r) {
+    if constexpr (P == 0) return r.own;
+    const uint64_t e = row_entry<Lt, P>(r.u);
+    const uint64_t in = e + r.u.own + row_offset<Lt, T, P>();
+    uint64_t a = (int64_t)e >= 0 ? in : r.own + (uint64_t)Lt::opp(P) * (Lt::MB * sizeof(T));
+    if constexpr (HALO) {
+        const uint64_t ha = r.halo + halo_entry<Lt, P>(r.below) * (uint32_t)sizeof(T);
+        a = e == (uint64_t)(int64_t)kNSkip ? ha : a;
+    }
+    return a;
+}
+
+// gather of a cell of a block with any links: every population's address by
+// selects, so all loads are in flight together
+template <typename Lt, typename ST, bool HALO, typename Out, typename Conv>
+__device__ __forceinline__ void gather_rows_by(const CellRows<typename ST::T> &r, Out *out, Conv conv) {
+    using T = typename ST::T;
+    static_for<Lt::Q>([&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        out[P] = conv(ST::ld(global_ptr<const T>(slot_address<Lt, T, P, HALO>(r))), P);
+    });
 }
 
 // BGK relaxation of one cell in the shifted variables: moments, then
@@ -464,6 +593,7 @@ __device__ inline DevMesh load_mesh(CSimDesc *cs) {
     m.hid = cs->m.hid;
     m.parent = cs->m.parent;
     m.fresh = cs->m.fresh;
+    m.desc = cs->m.desc;
     m.nbr = cs->m.nbr;
     m.nbrc = cs->m.nbrc;
     m.X = cs->m.X;
@@ -505,54 +635,98 @@ __device__ inline void decode_item(uint32_t it, int &sim, int &B) {
 // EX: a leaf block next to a solid also adds its momentum exchange of this
 // sweep to its total, exactly as the separate pass (exchange_block) would from
 // the values just stored.
-// Body: the cells of staged block s (this thread: cell l).
-template <int Q, int S, int NBLK, bool NTS, int COLL = 0, bool EX = false>
-__device__ __forceinline__ void collide_block(const DevMesh &m, const BlockStage<Lat<Q>, NBLK> &st, int s, int l,
-                                              const typename Store<S>::T *__restrict__ src,
+//
+// Kind and wall velocity of the domain's faces, as the lanes of a block read them.
+template <typename Lt, typename R>
+struct FaceTable {
+    static constexpr int NF = 2 * Lt::D;
+    R u[NF][3];
+    int32_t kind[NF];
+    // by the block's lanes: NF * D <= 18 of 64, 8 of 16
+    __device__ void put(const BCParams &bc, int lane) {
+        if (lane < NF * Lt::D) u[lane / Lt::D][lane % Lt::D] = R(bc.u[lane / Lt::D][lane % Lt::D]);
+        if (lane < NF) {
+            kind[lane] = bc.kind[lane];
+            if (Lt::D == 2) u[lane][2] = R(0);
+        }
+    }
+};
+
+// LDS of one wave: row table and faces of each of its blocks (the blocks of a
+// wave of a 2-D batch may belong to different simulations)
+template <typename Lt, typename R>
+struct CollideSmem {
+    uint64_t tab[64 / Lt::MB][kTab<Lt>];
+    FaceTable<Lt, R> face[64 / Lt::MB];
+};
+
+// Keeps a 2-D block's result in FP32 until it is stored.  The conversion to
+// FP16 would otherwise fuse with the last multiply-add on the path for interior
+// blocks and not on the other, and which path a 2-D block takes depends on the
+// three that share its wave.
+template <typename Lt, int S, typename R>
+__device__ __forceinline__ void pin_result(R &g) {
+    if constexpr (Lt::D == 2 && S == AMR_F16S) asm volatile("" : "+v"(g));
+}
+
+// Body: cell l of block B (B < 0: none), whole wave; `glane` = the lane's
+// index among the block's lanes (= l).
+template <int Q, int S, bool NTS, int COLL = 0, bool EX = false>
+__device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, const typename Store<S>::T *__restrict__ src,
                                               typename Store<S>::T *__restrict__ dst, typename Store<S>::R om,
-                                              const BCParams &bc, const uint64_t *tab,
+                                              const BCParams &bc, CollideSmem<Lat<Q>, typename Store<S>::R> &sm,
                                               typename Store<S>::R sh = typename Store<S>::R(0)) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
     using R = typename ST::R;
-    const int B = st.id[s];
+    using T = typename ST::T;
+    using De = Desc<Lt::D>;
+    const int lane = threadIdx.x & 63;
+    uint64_t *tab = sm.tab[Lt::D == 3 ? 0 : lane >> 4];
+    const int32_t w = desc_word<Lt>(m.desc, B, l);
+    put_rows<Lt>(tab, w, l, src);
+    wave_lds_sync();
+    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
+    const int h = desc_get<Lt>(w, De::kHid);
     if (B < 0) return;
-    const uint8_t flag = st.flag[s];
-    const int h = st.hid[s];
-    const int32_t *link = st.link[s];
-    const int i = l & 3, j = (l >> 2) & 3, k = l >> 4;
+    FaceTable<Lt, R> &face = sm.face[Lt::D == 3 ? 0 : lane >> 4];
+    const bool wall = __any(flag & BF_BOUNDARY);
+    if (wall) face.put(bc, l);
 
     R g[Q];
-    R drho, ux, uy, uz;
-    if constexpr (Lt::D == 3) {
-        // Interior block (every region link a same-level block): one block per
-        // wave; sources through the wave's row table (tab, in LDS).
-        if (!(flag & (BF_BOUNDARY | BF_NSKIP))) {
-            gather_interior<Lt, ST>(interior_lane<typename ST::T>(tab, i, j, k), g);
-            R uu;
-            relax<Lt, R, COLL>(g, om, sh, drho, ux, uy, uz, uu);
-            const int Bu = __builtin_amdgcn_readfirstlane(B);
+    R drho, ux, uy, uz, uu;
+    // Interior blocks (every region link a same-level block; 2-D: all four of the wave)
+    if (!__any(flag & (BF_BOUNDARY | BF_NSKIP))) {
+        gather_interior<Lt, ST>(interior_lane<T, Lt>(tab, l & 3, (l >> 2) & 3, l >> 4), g);
+        relax<Lt, R, COLL>(g, om, sh, drho, ux, uy, uz, uu);
 #pragma unroll
-            for (int p = 0; p < Q; p++) store_g<Lt, ST, NTS>(dst, mslot<Lt>(Bu, p, l), p, g[p]);
-            return;
+        for (int p = 0; p < Q; p++) {
+            pin_result<Lt, S>(g[p]);
+            store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, p, l), p, g[p]);
         }
+        return;
     }
-    gather_cell<Lt, ST>(m, link, B, h, l, src, g);
-    R uu;
+    const CellRows<T> r = cell_rows<Lt, T>(tab, B, h, l, src, m);
+    const bool halo = __any(flag & BF_NSKIP);
+    const auto conv = [](R v, int p) { return ST::shift ? v : v - R(Lt::w(p)); };
+    if (halo)
+        gather_rows_by<Lt, ST, true>(r, g, conv);
+    else
+        gather_rows_by<Lt, ST, false>(r, g, conv);
     relax<Lt, R, COLL>(g, om, sh, drho, ux, uy, uz, uu);
+    wave_lds_sync();
 
     [[maybe_unused]] double fx = 0.0, fy = 0.0, fz = 0.0;
-#pragma unroll
-    for (int q = 0; q < Q; q++) {
-        if (flag & BF_BOUNDARY) {
-            const int32_t code = link[region_of<Lt>(i + Lt::cx(q), j + Lt::cy(q), k + Lt::cz(q))];
-            if (code < 0 && code != kNSkip) {
-                R val;
-                if (code == kSolid) {
-                    val = g[q];
+    static_for<Q>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        R val = g[q];
+        if (wall) {
+            const int64_t e = (int64_t)row_entry<Lt, Lt::opp(q)>(r.u);  // where population q leaves to
+            if (e < 0 && e != kNSkip) {
+                if (e == kSolid) {
                     if constexpr (EX) {
                         // 2 f*_q c_q from the value as stored (rounded to the storage type)
-                        typename ST::T t;
+                        T t;
                         ST::st(&t, ST::shift ? val : val + R(Lt::w(q)));
                         const double two_f = 2.0 * double(ST::ld(&t) + (ST::shift ? Lt::w(q) : 0.0));
                         fx += two_f * Lt::cx(q);
@@ -560,26 +734,24 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, const BlockStage
                         fz += two_f * Lt::cz(q);
                     }
                 } else {
-                    const int face = -3 - code;
+                    const int f = -3 - (int)e;
                     const R cx = R(Lt::cx(q)), cy = R(Lt::cy(q)), cz = R(Lt::cz(q));
-                    if (bc.kind[face] == AMR_FACE_VELOCITY) {
-                        const R cuw = cx * R(bc.u[face][0]) + cy * R(bc.u[face][1]) + cz * R(bc.u[face][2]);
+                    if (face.kind[f] == AMR_FACE_VELOCITY) {
+                        const R cuw = cx * face.u[f][0] + cy * face.u[f][1] + cz * face.u[f][2];
                         val = g[q] - R(6) * R(Lt::w(q)) * cuw;
                     } else {
                         const R cu = cx * ux + cy * uy + cz * uz;
                         val = -g[q] + R(2) * R(Lt::w(q)) * (R(4.5) * cu * cu - R(1.5) * uu);
                     }
                 }
-                // the slot now holds population opposite(q) of this cell
-                store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, q, l), Lt::opp(q), val);
-                continue;
             }
         }
-        store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, q, l), q, g[q]);
-    }
+        // outside the fluid the slot now holds population opposite(q) of this cell
+        store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, q, l), q, val);
+    });
     if constexpr (EX) {
         // uniform over the block's lanes: sum over the block, one lane adds
-        if ((flag & BF_SOLID) && m.status[B] == ST_UNREF) {
+        if ((flag & BF_SOLID) && (flag & DF_LEAF)) {
 #pragma unroll
             for (int mask = 1; mask < Lt::MB; mask <<= 1) {
                 fx += __shfl_xor(fx, mask, 64);
@@ -593,12 +765,15 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, const BlockStage
             }
         }
     }
-    if ((flag & BF_NSKIP) && h >= 0) {
-#pragma unroll
-        for (int p = 1; p < Q; p++) {
-            if (link[region_of<Lt>(i - Lt::cx(p), j - Lt::cy(p), k - Lt::cz(p))] == kNSkip)
-                store_g<Lt, ST, NTS>(dst, m.halo_base + (int64_t)h * m.nh + kHalo<Lt>.idx[p][l], p, g[p]);
-        }
+    if (halo) {
+        const int64_t rec = m.halo_base + (int64_t)h * m.nh;
+        static_for<Q>([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            if constexpr (p > 0) {
+                if (row_entry<Lt, p>(r.u) == (uint64_t)(int64_t)kNSkip)
+                    store_g<Lt, ST, NTS>(dst, rec + halo_entry<Lt, p>(r.below), p, g[p]);
+            }
+        });
     }
 }
 
@@ -626,19 +801,15 @@ __device__ __forceinline__ void collide_wg(const int32_t *__restrict__ list, int
     using Lt = Lat<Q>;
     using R = typename Store<S>::R;
     constexpr int MB = Lt::MB, BPW = collide_blocks_per_wg<Q, S>();
-    __shared__ BlockStage<Lt, BPW> st;
-    __shared__ uint64_t tab[Lt::D == 3 ? BPW : 1][27];
-    const int base = wg * BPW;
-    if ((int)threadIdx.x < BPW) st.id[threadIdx.x] = base + (int)threadIdx.x < n ? list[base + threadIdx.x] : -1;
-    __syncthreads();
-    stage_blocks<Lt, BPW>(m, st);
+    __shared__ CollideSmem<Lt, R> sm[collide_threads<S>() / 64];
+    int pos = wg * BPW + (int)threadIdx.x / MB;
     if constexpr (Lt::D == 3) {
-        fill_row_tables<Lt, BPW>(st, [&](int) -> const DevMesh & { return m; }, [&](int) { return src; }, tab);
-        __syncthreads();
+        pos = __builtin_amdgcn_readfirstlane(pos);  // one block per wave
+        if (pos >= n) return;
     }
-    const int s = threadIdx.x / MB;
-    collide_block<Q, S, BPW, NTS, COLL, EX>(m, st, s, threadIdx.x % MB, src, dst, R(omega_d), bc,
-                                            tab[Lt::D == 3 ? s : 0], R(s_high));
+    const int B = pos < n ? list[pos] : -1;
+    collide_block<Q, S, NTS, COLL, EX>(m, B, threadIdx.x % MB, src, dst, R(omega_d), bc, sm[threadIdx.x >> 6],
+                                       R(s_high));
 }
 
 template <int Q, int S, bool NTS, int COLL = 0, bool EX = false>
@@ -660,35 +831,25 @@ __global__ __launch_bounds__(NT) void k_collide_stream_batch(const SimDesc *__re
     using R = typename ST::R;
     using T = typename ST::T;
     constexpr int MB = Lt::MB, BPW = NT / MB;
-    __shared__ BlockStage<Lt, BPW> st;
-    __shared__ uint64_t tab[Lt::D == 3 ? BPW : 1][27];
+    __shared__ CollideSmem<Lt, R> sm[NT / 64];
     const int n = *count;
     int u0, u1;
     persistent_range((n + BPW - 1) / BPW, u0, u1);
     for (int u = u0; u < u1; u++) {
-        if ((int)threadIdx.x < BPW) {
-            const int idx = u * BPW + (int)threadIdx.x;
-            int sim = 0, B = -1;
-            if (idx < n) decode_item(items[idx], sim, B);
-            st.id[threadIdx.x] = B;
-            st.sim[threadIdx.x] = sim;
-        }
-        __syncthreads();
-        stage_blocks_by<Lt, BPW>([&](int e) -> const DevMesh & { return sims[st.sim[e]].m; }, st);
-        if constexpr (Lt::D == 3) {
-            fill_row_tables<Lt, BPW>(st, [&](int e) -> const DevMesh & { return sims[st.sim[e]].m; },
-                                     [&](int e) { return (const T *)sims[st.sim[e]].f[par]; }, tab);
-            __syncthreads();
-        }
         const int tid = opaque_tid();
-        const int s = tid / MB;
-        int sim = st.sim[s];
-        if (MB == 64) sim = __builtin_amdgcn_readfirstlane(sim);  // one block per wave
+        int idx = u * BPW + tid / MB;
+        if (MB == 64) {
+            idx = __builtin_amdgcn_readfirstlane(idx);  // one block per wave
+            if (idx >= n) break;
+        }
+        int sim = 0, B = -1;
+        if (idx < n) decode_item(items[idx], sim, B);
+        if (MB == 64) sim = __builtin_amdgcn_readfirstlane(sim);
         CSimDesc *cs = const_view(sims) + sim;
         const DevMesh m = load_mesh(cs);
-        collide_block<Q, S, BPW, false>(m, st, s, tid % MB, (const T *)cs->f[par], (T *)cs->f[1 - par],
-                                 R(cs->lp.omega[L]), sims[sim].bc, tab[Lt::D == 3 ? s : 0]);
-        __syncthreads();
+        collide_block<Q, S, false>(m, B, tid % MB, (const T *)cs->f[par], (T *)cs->f[1 - par], R(cs->lp.omega[L]),
+                                   sims[sim].bc, sm[tid >> 6]);
+        wave_lds_sync();
     }
 }
 
@@ -1423,7 +1584,7 @@ __global__ __launch_bounds__(256) void k_velocity(const int32_t *__restrict__ li
     if constexpr (Lt::D == 3) {
         if (!(st.flag[s] & (BF_BOUNDARY | BF_NSKIP))) {
             // the same values as cell_f64, through the row table
-            gather_interior_by<Lt, ST, 0>(interior_lane<typename ST::T>(tab[s], l & 3, (l >> 2) & 3, l >> 4), fv,
+            gather_interior_by<Lt, ST>(interior_lane<typename ST::T>(tab[s], l & 3, (l >> 2) & 3, l >> 4), fv,
                                           [](typename ST::R v, int p) {
                                               return double(v) + (ST::shift ? Lt::w(p) : 0.0);
                                           });

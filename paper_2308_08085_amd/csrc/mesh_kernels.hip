@@ -301,6 +301,36 @@ __global__ void k_parent_mask(DevMesh m) {
     if (any) m.bflag[B] = m.bflag[B] | BF_PARENT_MASK;
 }
 
+// Packed block descriptors (Desc): one workgroup turns the links of 64
+// consecutive blocks, read along each link array, into 64 rows through LDS.
+template <typename Dd>
+__global__ __launch_bounds__(256) void k_block_desc(DevMesh m) {
+    using De = Desc<Dd::D>;
+    constexpr int NW = De::kWords;
+    __shared__ int32_t row[64][NW + 1];
+    const int B0 = blockIdx.x * 64;
+    const int b = threadIdx.x & 63, B = B0 + b;
+    const bool act = B < m.cap && m.status[B] != ST_INACTIVE;
+    for (int p = threadIdx.x >> 6; p < NW; p += 4) {
+        int32_t v = 0;
+        if (act) {
+            if (p < Dd::NB) v = m.nbr[(int64_t)p * m.cap + B];
+            else if (p == De::kHid) v = m.hid[B];
+            else if (p == De::kFlags)
+                v = (int32_t)(m.bflag[B] | (m.status[B] == ST_UNREF ? DF_LEAF : 0u) | ((uint32_t)m.level[B] << 16));
+            else if (p == De::kFirst) v = m.nbrc[B];
+            else if (p == De::kGhost)
+                v = Dd::D == 3 ? (int32_t)m.gmask[B] : (int32_t)(m.gmask[B] | m.imask[B] << 16);
+            else if (Dd::D == 3) v = (int32_t)(m.gmask[B] >> 32);
+        }
+        const int at = p < Dd::NB ? offset_slot(Dd::cx(p), Dd::cy(p), Dd::cz(p)) - (Dd::D == 2 ? 9 : 0) : p;
+        row[b][at] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 64 * NW; e += 256)
+        if (B0 + e / NW < m.cap) m.desc[(int64_t)B0 * NW + e] = row[e / NW][e % NW];
+}
+
 // ---------------------------------------------------------------------------
 // Tagging.
 __global__ void k_crit_reset(double *crit, int cap, DevCounters *ctr) {
@@ -814,6 +844,7 @@ void masks_and_lists(const Ctx &c) {
     run_scan(c, c.bins, cap, 1);
     k_set_hid<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins, c.rank);
     k_parent_mask<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
+    k_block_desc<Dd><<<grid_for(cap, 64), 256, 0, c.stream>>>(c.m);
     const int64_t tot = (int64_t)c.m.lmax * cap;
     k_bins_keep<<<grid_for(tot), 256, 0, c.stream>>>(c.m, c.ids, c.ctr, c.bins, 1);
     run_scan(c, c.bins, tot, c.m.lmax);

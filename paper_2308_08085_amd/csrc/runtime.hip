@@ -88,6 +88,7 @@ void make_layout(const amr_config *c, Layout *L) {
     L->hid = take(cap * 4);
     L->parent = take(cap * 4);
     L->fresh = take(cap);
+    L->desc = take(cap * (c->dim == 2 ? Desc<2>::kWords : Desc<3>::kWords) * 4);
     L->U = take(3 * capc * 8);
     L->nbr = take(nb * cap * 4);
     L->nbrc = take(nb * cap * 4);
@@ -356,6 +357,7 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
     c.m.hid = (int32_t *)(a + lay.hid);
     c.m.parent = (int32_t *)(a + lay.parent);
     c.m.fresh = (int8_t *)(a + lay.fresh);
+    c.m.desc = (int32_t *)(a + lay.desc);
     c.U = (double *)(a + lay.U);
     c.m.nbr = (int32_t *)(a + lay.nbr);
     c.m.nbrc = (int32_t *)(a + lay.nbrc);

@@ -205,3 +205,27 @@ def test_benchmark_batch_sampled_cells_match_the_oracle():
                     assert abs(got[s_, l, p] - want) <= tol, (c.name, int(B), l, p, got[s_, l, p], want)
         print("%s: %d sampled blocks match" % (c.name, len(sample)), flush=True)
     b.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32s", "f16s", "bf16s"])
+def test_batch_waves_of_different_simulations(storage):
+    """Cavities of one and four root blocks with different lids: the four 2-D
+    blocks of a wave belong to different members, with their own walls,
+    viscosities and buffers, and to the tail of the item list.  Members step
+    identically alone (the same per-cell operations in the same order)."""
+    cases = [W.cavity(2, 9, side, 2, 100.0, u_lid=u, storage=storage, seed=50 + i)
+             for i, (side, u) in enumerate(((4, 0.05), (8, 0.02), (4, 0.04), (8, 0.08), (12, 0.01)))]
+    batched, alone = make(cases, stream=torch.cuda.Stream()), make(cases)
+    for g in batched + alone:  # one member in two stays on one level
+        if g.nroot == 4:
+            tags = np.zeros(g.cap, np.int8)
+            tags[3] = 1
+            g.tag(tags_in=tags)
+            g.adapt()
+    b = abi.AmrBatch(batched)
+    for n in (1, 5):
+        b.step(n, graph=n > 1)
+        for i, (x, y) in enumerate(zip(batched, alone)):
+            y.step(n)
+            assert_same(x, y, "%s member %d" % (storage, i))
+    b.close()
