@@ -98,43 +98,6 @@ __device__ __forceinline__ void gather_cell(const DevMesh &m, const int32_t *lin
     for (int p = 0; p < Lt::Q; p++) g[p] = load_g<Lt, ST, RAW>(f, entry_slot<Lt>(m, link, B, h, p, l), p);
 }
 
-// The same for a block whose only links outside the fluid are domain faces or
-// solid blocks (no coarser neighbour): each population comes from a same-level
-// block or from the cell's own opposite slot, a select between two addresses
-// rather than a branch per population.
-template <typename Lt, typename ST, bool RAW = false>
-__device__ __forceinline__ void gather_cell_nohalo(const DevMesh &m, const int32_t *link, int B, int l,
-                                                   const typename ST::T *f, typename ST::R *g) {
-#pragma unroll
-    for (int p = 0; p < Lt::Q; p++) {
-        const int sx = (l & 3) - Lt::cx(p), sy = ((l >> 2) & 3) - Lt::cy(p), sz = (l >> 4) - Lt::cz(p);
-        const int32_t code = link[region_of<Lt>(sx, sy, sz)];
-        const bool in = code >= 0 && code < m.cap;
-        const int blk = in ? code : B;
-        const int q = in ? p : Lt::opp(p);
-        const int cell = in ? (sx & 3) + 4 * (sy & 3) + 16 * (sz & 3) : l;
-        g[p] = load_g<Lt, ST, RAW>(f, mslot<Lt>(blk, q, cell), p);
-    }
-}
-
-// gather of a cell of a block with flags `flag`: the select form unless the
-// block has a coarser neighbour
-template <typename Lt, typename ST, bool RAW = false>
-__device__ __forceinline__ void gather_cell_flag(const DevMesh &m, const int32_t *link, int B, int h, uint8_t flag,
-                                                 int l, const typename ST::T *f, typename ST::R *g) {
-    if (flag & BF_NSKIP)
-        gather_cell<Lt, ST, RAW>(m, link, B, h, l, f, g);
-    else
-        gather_cell_nohalo<Lt, ST, RAW>(m, link, B, l, f, g);
-}
-
-template <typename Lt, typename ST>
-__device__ __forceinline__ void scatter_cell(const DevMesh &m, const int32_t *link, int B, int h, int l,
-                                             typename ST::T *f, const typename ST::R *g) {
-#pragma unroll
-    for (int p = 0; p < Lt::Q; p++) store_g<Lt, ST>(f, entry_slot<Lt>(m, link, B, h, p, l), p, g[p]);
-}
-
 // Gather of an interior 3-D block (every region link a same-level block; one
 // block per wave) through a per-wave LDS table of its 27 region rows.
 //
@@ -314,6 +277,30 @@ __device__ __forceinline__ uint64_t slot_address(const CellRows<T> &r) {
     return a;
 }
 
+// The same for a population known only at run time (uniform over the wave).
+template <typename Lt>
+struct DirTable {
+    int32_t c[Lt::Q][3], opp[Lt::Q];
+    constexpr DirTable() : c(), opp() {
+        for (int p = 0; p < Lt::Q; p++) {
+            c[p][0] = Lt::cx(p);
+            c[p][1] = Lt::cy(p);
+            c[p][2] = Lt::cz(p);
+            opp[p] = Lt::opp(p);
+        }
+    }
+};
+template <typename Lt> constexpr DirTable<Lt> kDir{};
+
+template <typename Lt, typename T>
+__device__ __forceinline__ uint64_t slot_address_any(const CellRows<T> &r, const uint64_t *tab, int l, int p) {
+    const int cx = kDir<Lt>.c[p][0], cy = kDir<Lt>.c[p][1], cz = kDir<Lt>.c[p][2];
+    const uint64_t e = tab[region_of<Lt>((l & 3) - cx, ((l >> 2) & 3) - cy, (l >> 4) - cz)];
+    if ((int64_t)e >= 0) return e + r.u.own + (int64_t)(p * Lt::MB - (cx + 4 * cy + 16 * cz)) * (int64_t)sizeof(T);
+    if (e != (uint64_t)(int64_t)kNSkip) return r.own + (uint32_t)(kDir<Lt>.opp[p] * Lt::MB) * (uint32_t)sizeof(T);
+    return r.halo + (uint32_t)(kHaloMask<Lt>.base[p] + __popcll(kHaloMask<Lt>.out[p] & r.below)) * (uint32_t)sizeof(T);
+}
+
 // gather of a cell of a block with any links: every population's address by
 // selects, so all loads are in flight together
 template <typename Lt, typename ST, bool HALO, typename Out, typename Conv>
@@ -323,6 +310,20 @@ __device__ __forceinline__ void gather_rows_by(const CellRows<typename ST::T> &r
         constexpr int P = decltype(pc)::value;
         out[P] = conv(ST::ld(global_ptr<const T>(slot_address<Lt, T, P, HALO>(r))), P);
     });
+}
+
+// The shifted populations of a cell of a block with flags `flag` (RAW: the
+// stored values); `r` from cell_rows.
+template <typename Lt, typename ST, bool RAW = false>
+__device__ __forceinline__ void gather_rows_flag(const CellRows<typename ST::T> &r, uint32_t flag, typename ST::R *g) {
+    using R = typename ST::R;
+    const auto conv = [](R v, int p) { return (ST::shift || RAW) ? v : v - R(Lt::w(p)); };
+    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
+        gather_interior<Lt, ST, RAW>(r.u, g);
+    else if (flag & BF_NSKIP)
+        gather_rows_by<Lt, ST, true>(r, g, conv);
+    else
+        gather_rows_by<Lt, ST, false>(r, g, conv);
 }
 
 // BGK relaxation of one cell in the shifted variables: moments, then
@@ -546,24 +547,6 @@ __device__ void stage_blocks_by(MeshOf mesh_of, BlockStage<Lt, NBLK> &st) {
 template <typename Lt, int NBLK>
 __device__ void stage_blocks(const DevMesh &m, BlockStage<Lt, NBLK> &st) {
     stage_blocks_by<Lt, NBLK>([&](int) -> const DevMesh & { return m; }, st);
-}
-
-// Fill the row tables of the NBLK staged blocks (row(r) - 4 r . (1, 4, 16)
-// in elements, as addresses; 0 where the link is not a block)
-template <typename Lt, int NBLK, typename MeshOf, typename SrcOf>
-__device__ __forceinline__ void fill_row_tables(const BlockStage<Lt, NBLK> &st, MeshOf mesh_of, SrcOf src_of,
-                                                uint64_t (*tab)[27]) {
-    for (int e = threadIdx.x; e < NBLK * 27; e += blockDim.x) {
-        const int s = e / 27, r = e - s * 27;
-        const int32_t id = st.id[s] >= 0 ? st.link[s][r] : -1;
-        uint64_t v = 0;
-        if (id >= 0 && id < mesh_of(s).cap) {
-            const int rx = r % 3 - 1, ry = (r / 3) % 3 - 1, rz = r / 9 - 1;
-            const int64_t el = (int64_t)id * (Lt::Q * Lt::MB) - 4 * (rx + 4 * ry + 16 * rz);
-            v = (uint64_t)(uintptr_t)src_of(s) + (uint64_t)(el * (int64_t)sizeof(*src_of(s)));
-        }
-        tab[s][r] = v;
-    }
 }
 
 // Contiguous range of work units [u0, u1) of a persistent workgroup: the
@@ -855,26 +838,44 @@ __global__ __launch_bounds__(NT) void k_collide_stream_batch(const SimDesc *__re
 
 // ---------------------------------------------------------------------------
 // Coarse-to-fine linear interpolation with Dupuis-Chopard rescaling (Sec.
-// "Linear Interpolation").  One parent block per workgroup: its cells are
-// rescaled into LDS, then every targeted fine cell evaluates the (bi/tri)linear
-// polynomial through the 2^d parent cells of its quadrant at
-// (-1/4 + I/2, -1/4 + J/2, -1/4 + K/2).
-template <typename R>
-__device__ inline R lin2(R F0, R F1, R F2, R F3, R x, R y) {
-    const R a0 = F0, a1 = F1 - F0, a2 = F2 - F0, a3 = F3 - F2 - F1 + F0;
-    return a0 + a1 * x + a2 * y + a3 * x * y;
+// "Linear Interpolation").  One parent block per team (3-D: a 256-thread
+// workgroup, 2-D: a wave): its cells are rescaled into LDS, the coefficients of
+// the (bi/tri)linear polynomial through the 2^d parent cells of each quadrant
+// are formed once per quadrant and population, and every targeted fine cell
+// evaluates them at (-1/4 + I/2, -1/4 + J/2, -1/4 + K/2).
+template <int D>
+constexpr int kLinCoef = D == 2 ? 4 : 8;
+
+template <typename Lt, typename R>
+__device__ __forceinline__ void lin_coef(const R *P, int c, R *a) {
+    const R *F = P + 2 * (c & 1) + 8 * ((c >> 1) & 1) + (Lt::D == 3 ? 32 * (c >> 2) : 0);
+    if constexpr (Lt::D == 2) {
+        const R F0 = F[0], F1 = F[1], F2 = F[4], F3 = F[5];
+        a[0] = F0;
+        a[1] = F1 - F0;
+        a[2] = F2 - F0;
+        a[3] = F3 - F2 - F1 + F0;
+    } else {
+        R G[8];
+#pragma unroll
+        for (int n = 0; n < 8; n++) G[n] = F[(n & 1) + 4 * ((n >> 1) & 1) + 16 * (n >> 2)];
+        a[0] = G[0];
+        a[1] = G[1] - G[0];
+        a[2] = G[2] - G[0];
+        a[3] = G[4] - G[0];
+        a[4] = G[3] - G[1] - G[2] + G[0];
+        a[5] = G[6] - G[2] - G[4] + G[0];
+        a[6] = G[5] - G[1] - G[4] + G[0];
+        a[7] = G[7] - G[3] - G[5] - G[6] + G[1] + G[2] + G[4] - G[0];
+    }
 }
-template <typename R>
-__device__ inline R lin3(const R *F, R x, R y, R z) {
-    const R a0 = F[0];
-    const R a1 = F[1] - F[0];
-    const R a2 = F[2] - F[0];
-    const R a3 = F[4] - F[0];
-    const R a4 = F[3] - F[1] - F[2] + F[0];
-    const R a5 = F[6] - F[2] - F[4] + F[0];
-    const R a6 = F[5] - F[1] - F[4] + F[0];
-    const R a7 = F[7] - F[3] - F[5] - F[6] + F[1] + F[2] + F[4] - F[0];
-    return a0 + a1 * x + a2 * y + a3 * z + a4 * x * y + a5 * y * z + a6 * x * z + a7 * x * y * z;
+
+template <typename Lt, typename R>
+__device__ __forceinline__ R lin_value(const R *a, int lf) {
+    const int I = lf & 3, J = (lf >> 2) & 3, K = lf >> 4;
+    const R x = R(-0.25) + R(0.5) * R(I), y = R(-0.25) + R(0.5) * R(J), z = R(-0.25) + R(0.5) * R(K);
+    if constexpr (Lt::D == 2) return a[0] + a[1] * x + a[2] * y + a[3] * x * y;
+    else return a[0] + a[1] * x + a[2] * y + a[3] * z + a[4] * x * y + a[5] * y * z + a[6] * x * z + a[7] * x * y * z;
 }
 
 // Weights of the cubic Lagrange polynomials through the nodes u = 0, 1, 2, 3 at u.
@@ -898,13 +899,9 @@ __device__ __forceinline__ R interp_value(const R *F, int c, int lf, int cubic) 
     const int cx = c & 1, cy = (c >> 1) & 1, cz = (c >> 2) & 1;
     const int I = lf & 3, J = (lf >> 2) & 3, K = lf >> 4;
     if (!cubic) {
-        const R x = R(-0.25) + R(0.5) * R(I), y = R(-0.25) + R(0.5) * R(J), z = R(-0.25) + R(0.5) * R(K);
-        const int m0 = 2 * cx + 4 * (2 * cy) + 16 * (2 * cz);
-        if (Lt::D == 2) return lin2<R>(F[m0], F[m0 + 1], F[m0 + 4], F[m0 + 5], x, y);
-        R G[8];
-#pragma unroll
-        for (int nn = 0; nn < 8; nn++) G[nn] = F[m0 + (nn & 1) + 4 * ((nn >> 1) & 1) + 16 * (nn >> 2)];
-        return lin3<R>(G, x, y, z);
+        R a[kLinCoef<Lt::D>];
+        lin_coef<Lt, R>(F, c, a);
+        return lin_value<Lt, R>(a, lf);
     }
     R wx[4], wy[4], wz[4];
     lagrange4<R>(R(-0.25) + R(0.5) * R(I) + R(2 * cx), wx);
@@ -926,79 +923,135 @@ __device__ __forceinline__ R interp_value(const R *F, int c, int lf, int cubic) 
     return v;
 }
 
+// Children that one lane group of a team handles, and the teams of a
+// 256-thread workgroup.
+template <typename Lt> constexpr int kTeamThreads = Lt::D == 3 ? 256 : 64;
+template <typename Lt> constexpr int kTeamTurns = Lt::NC * Lt::MB / kTeamThreads<Lt>;  // children per lane group
+
 template <typename Lt, typename R>
 struct InterpSmem {
-    R g[Lt::Q][Lt::MB];
-    uint64_t gm[Lt::NC];
-    BlockStage<Lt, Lt::NC + 1> st;  // entry NC = the parent
+    R g[Lt::Q][Lt::MB];                         // the parent's rescaled cells
+    R coef[Lt::NC][Lt::Q][kLinCoef<Lt::D>];     // linear: per quadrant and population
+    uint64_t ptab[kTab<Lt>];                    // rows of the parent and of the children
+    uint64_t tab[Lt::NC][kTab<Lt>];
 };
 
-// Body (whole workgroup): targeted cells of the children of refined parent P.
-// CUB: 0 linear, 1 cubic, 2 the mesh's choice at run time.
-template <int Q, int S, int CUB>
-__device__ __forceinline__ void interp_parent(const DevMesh &m, int P, const typename Store<S>::T *src,
-                                              typename Store<S>::T *dst, typename Store<S>::R r, int all_cells,
-                                              InterpSmem<Lat<Q>, typename Store<S>::R> &sm, int t) {
+template <typename Lt>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (Lt::D == 3) __syncthreads();
+    else wave_lds_sync();
+}
+
+// Body (whole team, thread t of it): targeted cells of the children of parent P
+// (a block that is not a refined parent is skipped).  CUB: 0 linear, 1 cubic,
+// 2 the mesh's choice at run time.  src_of(L) / dst_of(L): current buffers of
+// the parent's and the children's level, r_of(L): the rescaling.
+// Two team barriers: parent's cells, coefficients.  Bound by its chain of
+// dependent loads (list, parent's descriptor, its cells and the children's
+// descriptors) and by the address work of the ghost cells' scattered stores.
+// D3Q27 cylinder, per launch: 174 us with FP32 and 120 us with FP16 storage when
+// links were staged for the workgroup, each cell formed its polynomial from
+// eight LDS reads per population and stores branched on their link; now 167
+// and 95 us.
+template <int Q, int S, int CUB, typename SrcOf, typename DstOf, typename ROf>
+__device__ __forceinline__ void interp_parent(const DevMesh &m, int P, SrcOf src_of, DstOf dst_of, ROf r_of,
+                                              int all_cells, InterpSmem<Lat<Q>, typename Store<S>::R> &sm, int t) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
     using R = typename ST::R;
-    constexpr int MB = Lt::MB, NC = Lt::NC;
-    const int first = m.nbrc[P];
-    if (t <= NC) sm.st.id[t] = t < NC ? first + t : P;
-    if (t < NC) sm.gm[t] = all_cells ? ~0ull : m.gmask[first + t];
-    __syncthreads();
-    stage_blocks<Lt, NC + 1>(m, sm.st);
-    if (t < MB) {
+    using T = typename ST::T;
+    using De = Desc<Lt::D>;
+    constexpr int MB = Lt::MB, NC = Lt::NC, TT = kTeamThreads<Lt>, NT = kTeamTurns<Lt>;
+    const int l = t % MB, grp = t / MB;  // lane among the MB of a block; child grp + k TT / MB in turn k
+    const int32_t pw = desc_word<Lt>(m.desc, P, l);
+    const int first = desc_get<Lt>(pw, De::kFirst);
+    const uint32_t pflag = (uint32_t)desc_get<Lt>(pw, De::kFlags);
+    const int L = (int)(pflag >> 16);
+    if (first < 0 || first > m.cap - NC || L + 1 >= m.lmax) return;  // uniform over the team
+    const T *src = src_of(L);
+    T *dst = dst_of(L);
+    int32_t w[NT];
+#pragma unroll
+    for (int k = 0; k < NT; k++) w[k] = desc_word<Lt>(m.desc, first + grp + k * (TT / MB), l);
+    if (grp == 0) {
+        put_rows<Lt>(sm.ptab, pw, l, src);
+        wave_lds_sync();
+        const CellRows<T> r = cell_rows<Lt, T>(sm.ptab, P, desc_get<Lt>(pw, De::kHid), l, src, m);
         R g[Q];
-        gather_cell_flag<Lt, ST>(m, sm.st.link[NC], P, sm.st.hid[NC], sm.st.flag[NC], t, src, g);
+        gather_rows_flag<Lt, ST>(r, pflag, g);
         R drho, ux, uy, uz;
         moments_g<Lt, R>(g, drho, ux, uy, uz);
-        const R uu = ux * ux + uy * uy + uz * uz;
+        const R uu = ux * ux + uy * uy + uz * uz, sc = r_of(L);
 #pragma unroll
-        for (int p = 0; p < Q; p++) sm.g[p][t] = rescale_neq<Lt, R>(p, g[p], r, drho, ux, uy, uz, uu);
+        for (int p = 0; p < Q; p++) sm.g[p][l] = rescale_neq<Lt, R>(p, g[p], sc, drho, ux, uy, uz, uu);
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NT; k++) put_rows<Lt>(sm.tab[grp + k * (TT / MB)], w[k], l, dst);
+    team_sync<Lt>();
     const int cubic = CUB == 2 ? m.interp : CUB;
-    for (int e = t; e < NC * MB; e += blockDim.x) {
-        const int c = e / MB, lf = e - c * MB;
-        if (!((sm.gm[c] >> lf) & 1ull)) continue;
-        const int32_t *link = sm.st.link[c];
-        const int hc = sm.st.hid[c];
+    if (!cubic) {
+        for (int e = t; e < NC * Q; e += TT) lin_coef<Lt, R>(sm.g[e % Q], e / Q, sm.coef[e / Q][e % Q]);
+        team_sync<Lt>();
+    }
+#pragma unroll 1
+    for (int k = 0; k < NT; k++) {
+        const int c = grp + k * (TT / MB);
+        const int32_t wk = NT == 1 || k == 0 ? w[0] : w[NT - 1];
+        uint64_t gm = (uint32_t)desc_get<Lt>(wk, De::kGhost);
+        if constexpr (Lt::D == 3) gm |= (uint64_t)(uint32_t)desc_get<Lt>(wk, De::kGhost + 1) << 32;
+        else gm &= 0xffff;
+        if (all_cells) gm = ~0ull;
+        const uint32_t flag = (uint32_t)desc_get<Lt>(wk, De::kFlags);
+        const int h = desc_get<Lt>(wk, De::kHid);
+        if (!((gm >> l) & 1ull)) continue;
+        // the cell's index hidden from loop-invariant code motion: per
+        // population offsets kept across the two turns would take 50 VGPRs
+        int lf = l;
+        asm volatile("" : "+v"(lf));
+        const CellRows<T> r = cell_rows<Lt, T>(sm.tab[c], first + c, h, lf, dst, m);
+        const auto put = [&](auto pc, auto halo, R v) {
+            constexpr int p = decltype(pc)::value;
+            T *a = global_ptr<T>(slot_address<Lt, T, p, decltype(halo)::value>(r));
+            ST::st(a, ST::shift ? v : v + R(Lt::w(p)));
+            // one population at a time: reading all coefficients ahead would take 160 VGPRs
+            __builtin_amdgcn_sched_barrier(0);
+        };
         if (cubic) {
             // 4^d terms per population: not unrolled over the populations
 #pragma unroll 1
             for (int p = 0; p < Q; p++) {
                 const R v = interp_value<Lt, R>(sm.g[p], c, lf, 1);
-                store_g<Lt, ST>(dst, entry_slot<Lt>(m, link, first + c, hc, p, lf), p, v);
+                T *a = global_ptr<T>(slot_address_any<Lt, T>(r, sm.tab[c], lf, p));
+                ST::st(a, ST::shift ? v : v + R(Lt::w(p)));
             }
+        } else if (flag & BF_NSKIP) {
+            static_for<Q>([&](auto pc) {
+                put(pc, std::true_type(), lin_value<Lt, R>(sm.coef[c][decltype(pc)::value], lf));
+            });
         } else {
-#pragma unroll
-            for (int p = 0; p < Q; p++) {
-                const R v = interp_value<Lt, R>(sm.g[p], c, lf, 0);
-                store_g<Lt, ST>(dst, entry_slot<Lt>(m, link, first + c, hc, p, lf), p, v);
-            }
+            static_for<Q>([&](auto pc) {
+                put(pc, std::false_type(), lin_value<Lt, R>(sm.coef[c][decltype(pc)::value], lf));
+            });
         }
     }
 }
 
-// refined parents only (a listed block that is not one is skipped)
-__device__ inline bool interp_target(const DevMesh &m, int P, int nc) {
-    const int first = m.nbrc[P];
-    return !(first < 0 || first > m.cap - nc || m.level[P] + 1 >= m.lmax);
-}
+// parents per 256-thread workgroup
+template <typename Lt> constexpr int kInterpPerWg = 256 / kTeamThreads<Lt>;
 
 template <int Q, int S, int CUB>
 __device__ __forceinline__ void interp_wg(const int32_t *__restrict__ list, int n, const DevMesh &m,
                                           typename Store<S>::T *f0, typename Store<S>::T *f1, const LevelParams &lp,
-                                          int all_cells, int item) {
+                                          int all_cells, int wg) {
+    using Lt = Lat<Q>;
     using R = typename Store<S>::R;
-    __shared__ InterpSmem<Lat<Q>, R> sm;
+    __shared__ InterpSmem<Lt, R> sm[kInterpPerWg<Lt>];
+    const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kTeamThreads<Lt>);
+    const int item = wg * kInterpPerWg<Lt> + team;
     if (item >= n) return;
-    const int P = list[item];
-    if (!interp_target(m, P, Lat<Q>::NC)) return;
-    const int L = m.level[P];
-    interp_parent<Q, S, CUB>(m, P, lp.par[L] ? f1 : f0, lp.par[L + 1] ? f1 : f0, R(lp.r_cf[L]), all_cells, sm,
-                             threadIdx.x);
+    interp_parent<Q, S, CUB>(
+        m, list[item], [&](int L) { return lp.par[L] ? f1 : f0; }, [&](int L) { return lp.par[L + 1] ? f1 : f0; },
+        [&](int L) { return R(lp.r_cf[L]); }, all_cells, sm[team], threadIdx.x % kTeamThreads<Lt>);
 }
 
 template <int Q, int S, int CUB>
@@ -1009,9 +1062,8 @@ __global__ __launch_bounds__(256) void k_interp(const int32_t *__restrict__ list
 }
 
 // The ghost interpolation into level L+1 and the collide-stream sweep of level
-// L in one 256-thread launch: workgroups 0 .. ni-1 interpolate one parent each
-// (in 2-D with the first 64 threads; interp_parent strides by the workgroup
-// size), the rest sweep the level.  Both read level L's current buffer; one
+// L in one 256-thread launch: the first workgroups interpolate one parent each
+// (2-D: four), the rest sweep the level.  Both read level L's current buffer; one
 // writes ghost cells of level L+1, the other level L's other buffer, so they
 // need no order, and small levels save a launch gap.  EX: the sweep adds the
 // momentum exchange too (collide_block).
@@ -1021,39 +1073,44 @@ __global__ __launch_bounds__(256) void k_interp_collide(const int32_t *__restric
                                                         typename Store<S>::T *f0, typename Store<S>::T *f1,
                                                         LevelParams lp, int L, BCParams bc) {
     const int b = blockIdx.x;
-    if (b < ni) {
+    const int iwg = (ni + kInterpPerWg<Lat<Q>> - 1) / kInterpPerWg<Lat<Q>>;
+    if (b < iwg) {
         interp_wg<Q, S, CUB>(ilist, ni, m, f0, f1, lp, 0, b);
     } else {
         const typename Store<S>::T *src = lp.par[L] ? f1 : f0;
         typename Store<S>::T *dst = lp.par[L] ? f0 : f1;
         collide_wg<Q, S, NTS, 0, EX>(clist, nblk, m, src, dst, lp.omega[L], bc, lp.omega[L],
-                                     xcd_remap(b - ni, (int)gridDim.x - ni));
+                                     xcd_remap(b - iwg, (int)gridDim.x - iwg));
     }
 }
 
 // Batched ghost fill of level L+1 from level L (interface parents of every
-// simulation), persistent workgroups; par0/par1 = buffers of levels L, L+1.
+// simulation), persistent teams; par0/par1 = buffers of levels L, L+1.
 template <int Q, int S>
 __global__ __launch_bounds__(256) void k_interp_batch(const SimDesc *__restrict__ sims,
                                                       const uint32_t *__restrict__ items,
                                                       const int32_t *__restrict__ count, int L, int par0, int par1) {
-    using ST = Store<S>;
-    using R = typename ST::R;
-    using T = typename ST::T;
-    __shared__ InterpSmem<Lat<Q>, R> sm;
+    using Lt = Lat<Q>;
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    __shared__ InterpSmem<Lt, R> sm[kInterpPerWg<Lt>];
+    const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kTeamThreads<Lt>);
+    const int n = *count;
     int u0, u1;
-    persistent_range(*count, u0, u1);
+    persistent_range((n + kInterpPerWg<Lt> - 1) / kInterpPerWg<Lt>, u0, u1);
     for (int u = u0; u < u1; u++) {
+        const int item = u * kInterpPerWg<Lt> + team;
+        if (item >= n) break;  // 3-D: never
         int sim, P;
-        decode_item(items[u], sim, P);
-        sim = __builtin_amdgcn_readfirstlane(sim);  // one item per workgroup
+        decode_item(items[item], sim, P);
+        sim = __builtin_amdgcn_readfirstlane(sim);  // one item per team
         P = __builtin_amdgcn_readfirstlane(P);
         CSimDesc *cs = const_view(sims) + sim;
         const DevMesh m = load_mesh(cs);
-        if (interp_target(m, P, Lat<Q>::NC))
-            interp_parent<Q, S, 2>(m, P, (const T *)cs->f[par0], (T *)cs->f[par1], R(cs->lp.r_cf[L]), 0, sm,
-                                   opaque_tid());
-        __syncthreads();
+        interp_parent<Q, S, 2>(
+            m, P, [&](int) { return (const T *)cs->f[par0]; }, [&](int) { return (T *)cs->f[par1]; },
+            [&](int) { return R(cs->lp.r_cf[L]); }, 0, sm[team], opaque_tid() % kTeamThreads<Lt>);
+        team_sync<Lt>();
     }
 }
 
@@ -1145,10 +1202,9 @@ static __global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, De
 // Fine-to-coarse averaging with rescaling (Sec. "Averaging"): parent cell
 // (i,j,k) takes the mean of the 2^d rescaled cells of child octant
 // (i/2, j/2, k/2) starting at fine cell (2(i mod 2), 2(j mod 2), 2(k mod 2)).
-// One lane per fine cell of the children (3-D: a wave per child; two
-// workgroups of four children per parent, so that children that end early do
-// not hold back a workgroup of eight): every lane gathers and rescales its
-// cell, the 2^d cells of a parent cell (lanes differing in bits 0, 2, 4 of the
+// One lane per fine cell of the children (3-D: a wave per child, on its own, so
+// that children that end early hold back no other): every lane gathers and
+// rescales its cell, the 2^d cells of a parent cell (lanes differing in bits 0, 2, 4 of the
 // cell index, all in one wave) are summed with xor shuffles, and the lane of
 // the first one writes the parent cell.  Children without a targeted cell are
 // skipped whole.
@@ -1156,16 +1212,17 @@ static __global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, De
 // The vorticity criterion reads velocities of leaf blocks and, across the six
 // faces of a leaf, of its same-level neighbours: a refined block none of whose
 // face neighbours is a leaf is never read.
+// w, flag: the block's descriptor words and its flags.
 template <typename Lt>
-__device__ __forceinline__ bool velocity_read(const DevMesh &m, const int32_t *link, int B) {
-    if (!is_refined(m.status[B])) return true;
+__device__ __forceinline__ bool velocity_read(const DevMesh &m, int32_t w, uint32_t flag) {
+    if (flag & DF_LEAF) return true;
     bool read = false;
 #pragma unroll
     for (int a = 0; a < Lt::D; a++)
+#pragma unroll
         for (int sg = -1; sg <= 1; sg += 2) {
-            const int32_t code =
-                link[region_of<Lt>(a == 0 ? 1 + 3 * sg : 1, a == 1 ? 1 + 3 * sg : 1, a == 2 ? 1 + 3 * sg : 1)];
-            if (code >= 0 && code < m.cap && m.status[code] == ST_UNREF) read = true;
+            const int32_t code = desc_get<Lt>(w, kCenterSlot<Lt> + sg * (a == 0 ? 1 : (a == 1 ? 3 : 9)));
+            if (code >= 0 && m.status[code] == ST_UNREF) read = true;
         }
     return read;
 }
@@ -1184,72 +1241,76 @@ __device__ __forceinline__ void cell_velocity(const double *fv, double *U, int64
     for (int a = 0; a < 3; a++) U[a * capc + cell] = j[a] / rho;
 }
 
-// refined parents with children in the next level
-__device__ inline bool average_target(const DevMesh &m, int P, int nc) {
-    const int c0 = m.nbrc[P];
-    return is_refined(m.status[P]) && c0 >= 0 && c0 <= m.cap - nc && m.level[P] + 1 < m.lmax;
+// The value of the lane whose index differs in bit MASK (1, 4 or 16).
+template <int MASK>
+__device__ __forceinline__ int xor_lane32(int v) {
+    if constexpr (MASK == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);  // quad_perm 1, 0, 3, 2
+    else return __builtin_amdgcn_ds_swizzle(v, 0x1f | (MASK << 10));
+}
+template <int MASK>
+__device__ __forceinline__ float xor_sum(float v) {
+    return v + __builtin_bit_cast(float, xor_lane32<MASK>(__builtin_bit_cast(int, v)));
+}
+template <int MASK>
+__device__ __forceinline__ double xor_sum(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)xor_lane32<MASK>((int)(uint32_t)b), hi = (uint32_t)xor_lane32<MASK>((int)(b >> 32));
+    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-template <typename R>
-__device__ __forceinline__ R xor_sum(R v, int mask) {
-    return v + __shfl_xor(v, mask, 64);
-}
-
-// children per averaging workgroup
-template <int Q>
-constexpr int avg_children() { return Lat<Q>::D == 3 ? 4 : Lat<Q>::NC; }
-
-// children c0 .. c0 + NCW - 1 of parent P.  VEL (every cell averaged): also
-// the criterion's FP64 velocity of each child cell that it reads
-// (velocity_read) and that the ghost interpolation after the averaging does
-// not rewrite (no N_SKIP link), from the values as stored, into U: the same
-// values and arithmetic as k_velocity, so that pass can skip those blocks.
+// child c of refined parent P, by the lanes of the child (3-D: a wave, 2-D: 16
+// lanes), with nothing shared beyond them: ctab, ptab are their own row tables.
+// The chain of dependent loads (parent's descriptor, child's descriptor and
+// mask, cells) and the gather's address work bound it.  D3Q27 cylinder, per
+// launch of interface averaging: 143 us with FP32 and 134 us with FP16 storage
+// in workgroups of four children that shared staged links, now 117 and 95 us;
+// every cell of every parent before an adaptation: 2.9 and 2.4, now 2.6 and 1.9 ms.  VEL (every cell
+// averaged): also the criterion's FP64 velocity of each child cell that it
+// reads (velocity_read) and that the ghost interpolation after the averaging
+// does not rewrite (no N_SKIP link), from the values as stored, into U: the
+// same values and arithmetic as k_velocity, so that pass can skip those blocks.
 template <int Q, int S, bool VEL = false>
-__device__ __forceinline__ void average_parent(const DevMesh &m, int P, int c0, const typename Store<S>::T *src,
-                                               typename Store<S>::T *dst, typename Store<S>::R r, int all_cells,
-                                               BlockStage<Lat<Q>, avg_children<Q>() + 1> &st,
-                                               uint64_t (*tab)[27], int t, double *U = nullptr) {
+__device__ __forceinline__ void average_child(const DevMesh &m, int P, int c, const typename Store<S>::T *src,
+                                              typename Store<S>::T *dst, typename Store<S>::R r, int all_cells,
+                                              uint64_t *ctab, uint64_t *ptab, int lf, double *U = nullptr) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
     using R = typename ST::R;
+    using T = typename ST::T;
+    using De = Desc<Lt::D>;
     // with unshifted storage the velocities need the stored values: gather
     // those, then form g exactly as load_g does
     constexpr bool RAW = VEL && !ST::shift;
-    constexpr int MB = Lt::MB, NCW = avg_children<Q>(), NC = Lt::NC;
-    const int first = m.nbrc[P];
-    if (t <= NCW) st.id[t] = t < NCW ? first + c0 + t : P;
-    __syncthreads();
-    stage_blocks<Lt, NCW + 1>(m, st);
-    if constexpr (Lt::D == 3) {
-        fill_row_tables<Lt, NCW + 1>(st, [&](int) -> const DevMesh & { return m; }, [&](int) { return src; }, tab);
-        __syncthreads();
-    }
-    const int cw = t / MB, lf = t - cw * MB;
-    if (cw >= NCW) return;
-    const int c = c0 + cw;  // octant of the child in its parent
+    constexpr int MB = Lt::MB, NC = Lt::NC;
+    const int32_t pw = desc_word<Lt>(m.desc, P, lf);
+    const int first = desc_get<Lt>(pw, De::kFirst);
+    if (first < 0 || first > m.cap - NC) return;
     const int child = first + c;
+    const int32_t w = desc_word<Lt>(m.desc, child, lf);
     const uint64_t im = all_cells ? ~0ull : m.imask[child];
-    if (im == 0) return;  // the whole child (a wave in 3-D, a 16-lane group in 2-D)
+    if (im == 0) return;  // the whole child
+    put_rows<Lt>(ptab, pw, lf, dst);
+    put_rows<Lt>(ctab, w, lf, src);
+    wave_lds_sync();
+    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
+    const int h = desc_get<Lt>(w, De::kHid);
+    const uint32_t pflag = (uint32_t)desc_get<Lt>(pw, De::kFlags);
+    const int ph = desc_get<Lt>(pw, De::kHid);
     // the 2^d lanes of one parent cell (cell-index bits 0, 2 and, in 3-D, 4)
     // are exactly the partners of the sums below: a group whose parent cell
     // is not written loads nothing
     const int lead = lf & ~(Lt::D == 3 ? 0x15 : 0x5);
+    [[maybe_unused]] bool read = false;
+    if constexpr (VEL) read = !(flag & BF_NSKIP) && velocity_read<Lt>(m, w, flag);
     R g[Q];
     if ((im >> lead) & 1ull) {
-        bool done = false;
-        if constexpr (Lt::D == 3) {
-            if (!(st.flag[cw] & (BF_BOUNDARY | BF_NSKIP))) {
-                gather_interior<Lt, ST, RAW>(interior_lane<typename ST::T>(tab[cw], lf & 3, (lf >> 2) & 3, lf >> 4), g);
-                done = true;
-            }
-        }
-        if (!done) gather_cell_flag<Lt, ST, RAW>(m, st.link[cw], child, st.hid[cw], st.flag[cw], lf, src, g);
+        gather_rows_flag<Lt, ST, RAW>(cell_rows<Lt, T>(ctab, child, h, lf, src, m), flag, g);
     } else {
 #pragma unroll
         for (int p = 0; p < Q; p++) g[p] = R(0);
     }
     if constexpr (VEL) {
-        if (!(st.flag[cw] & BF_NSKIP) && velocity_read<Lt>(m, st.link[cw], child)) {
+        if (read) {
             double fv[Q];
 #pragma unroll
             for (int p = 0; p < Q; p++) fv[p] = double(g[p]) + (ST::shift ? Lt::w(p) : 0.0);
@@ -1268,40 +1329,48 @@ __device__ __forceinline__ void average_parent(const DevMesh &m, int P, int c0, 
 #pragma unroll
     for (int p = 0; p < Q; p++) {
         R v = rescale_neq<Lt, R>(p, g[p], r, drho, ux, uy, uz, uu);
-        v = xor_sum(v, 1);
-        v = xor_sum(v, 4);
-        if (Lt::D == 3) v = xor_sum(v, 16);
+        v = xor_sum<1>(v);
+        v = xor_sum<4>(v);
+        if constexpr (Lt::D == 3) v = xor_sum<16>(v);
         g[p] = v;
     }
     const int i = lf & 3, j = (lf >> 2) & 3, k = lf >> 4;
     if (lf != lead || !((im >> lf) & 1ull)) return;
     const int l = ((c & 1) * 2 + (i >> 1)) + 4 * (((c >> 1) & 1) * 2 + (j >> 1)) + 16 * ((c >> 2) * 2 + (k >> 1));
-    const int32_t *plink = st.link[NCW];
-    const int ph = st.hid[NCW];
-#pragma unroll
-    for (int p = 0; p < Q; p++) store_g<Lt, ST>(dst, entry_slot<Lt>(m, plink, P, ph, p, l), p, g[p] / R(NC));
+    const CellRows<T> pr = cell_rows<Lt, T>(ptab, P, ph, l, dst, m);
+    const auto put = [&](auto pc, auto halo) {
+        constexpr int p = decltype(pc)::value;
+        const R v = g[p] / R(NC);
+        ST::st(global_ptr<T>(slot_address<Lt, T, p, decltype(halo)::value>(pr)), ST::shift ? v : v + R(Lt::w(p)));
+    };
+    if (pflag & BF_NSKIP) static_for<Q>([&](auto pc) { put(pc, std::true_type()); });
+    else static_for<Q>([&](auto pc) { put(pc, std::false_type()); });
 }
 
-// grid: NC / avg_children workgroups per listed parent.  At least 6 waves per
-// SIMD: left alone the compiler takes 88 VGPRs (5 waves) for D3Q27 FP32; at 80
-// the launch is 9 % shorter on the cylinder set-up (no spills; at 64 it spills
-// and is slower).
+// children per 256-thread workgroup: one per wave in 3-D, four per wave in 2-D
+template <typename Lt> constexpr int kAvgPerWg = 256 / Lt::MB;
+
+template <typename Lt>
+struct AvgSmem {
+    uint64_t ctab[kAvgPerWg<Lt>][kTab<Lt>], ptab[kAvgPerWg<Lt>][kTab<Lt>];
+};
+
+// list: refined blocks of level L; a workgroup takes kAvgPerWg of their children.
+// At least 6 waves per SIMD: left alone the compiler takes more than 80 VGPRs
+// (5 waves) for D3Q27 FP32, 9 % slower on the cylinder set-up.
 template <int Q, int S, bool VEL = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == AMR_F64 ? 1 : 6))) void k_average(const int32_t *__restrict__ list, int n, DevMesh m,
-                                                 typename Store<S>::T *f0, typename Store<S>::T *f1, LevelParams lp,
-                                                 int all_cells, double *U) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == AMR_F64 ? 1 : 6))) void k_average(
+    const int32_t *__restrict__ list, int n, DevMesh m, const typename Store<S>::T *src, typename Store<S>::T *dst,
+    double r_fc, int all_cells, double *U) {
     using Lt = Lat<Q>;
     using R = typename Store<S>::R;
-    constexpr int SPLIT = Lt::NC / avg_children<Q>();
-    __shared__ BlockStage<Lt, avg_children<Q>() + 1> st;
-    __shared__ uint64_t tab[Lt::D == 3 ? avg_children<Q>() + 1 : 1][27];
-    const int item = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT;
+    __shared__ AvgSmem<Lt> sm;
+    const int slot = threadIdx.x / Lt::MB;
+    int64_t unit = (int64_t)blockIdx.x * kAvgPerWg<Lt> + slot;
+    const int item = __builtin_amdgcn_readfirstlane((int)(unit / Lt::NC));  // one parent per wave
     if (item >= n) return;
-    const int P = list[item];
-    if (!average_target(m, P, Lt::NC)) return;
-    const int L = m.level[P];
-    average_parent<Q, S, VEL>(m, P, part * avg_children<Q>(), lp.par[L + 1] ? f1 : f0, lp.par[L] ? f1 : f0,
-                              R(lp.r_fc[L]), all_cells, st, tab, threadIdx.x, U);
+    average_child<Q, S, VEL>(m, list[item], (int)(unit % Lt::NC), src, dst, R(r_fc), all_cells, sm.ctab[slot],
+                             sm.ptab[slot], threadIdx.x % Lt::MB, U);
 }
 
 // Batched interface averaging of level L+1 into level L, persistent
@@ -1311,25 +1380,26 @@ __global__ __launch_bounds__(256) void k_average_batch(const SimDesc *__restrict
                                                        const uint32_t *__restrict__ items,
                                                        const int32_t *__restrict__ count, int L, int par0, int par1) {
     using Lt = Lat<Q>;
-    using ST = Store<S>;
-    using R = typename ST::R;
-    using T = typename ST::T;
-    constexpr int SPLIT = Lt::NC / avg_children<Q>();
-    __shared__ BlockStage<Lt, avg_children<Q>() + 1> st;
-    __shared__ uint64_t tab[Lt::D == 3 ? avg_children<Q>() + 1 : 1][27];
+    using R = typename Store<S>::R;
+    using T = typename Store<S>::T;
+    __shared__ AvgSmem<Lt> sm;
+    const int n = *count;
     int u0, u1;
-    persistent_range(*count * SPLIT, u0, u1);
+    persistent_range((n * Lt::NC + kAvgPerWg<Lt> - 1) / kAvgPerWg<Lt>, u0, u1);
     for (int u = u0; u < u1; u++) {
+        const int tid = opaque_tid(), slot = tid / Lt::MB;
+        const int unit = u * kAvgPerWg<Lt> + slot;
+        const int item = __builtin_amdgcn_readfirstlane(unit / Lt::NC);  // one parent per wave
+        if (item >= n) break;
         int sim, P;
-        decode_item(items[u / SPLIT], sim, P);
-        sim = __builtin_amdgcn_readfirstlane(sim);  // one item per workgroup
+        decode_item(items[item], sim, P);
+        sim = __builtin_amdgcn_readfirstlane(sim);
         P = __builtin_amdgcn_readfirstlane(P);
         CSimDesc *cs = const_view(sims) + sim;
         const DevMesh m = load_mesh(cs);
-        if (average_target(m, P, Lt::NC))
-            average_parent<Q, S>(m, P, (u % SPLIT) * avg_children<Q>(), (const T *)cs->f[par1], (T *)cs->f[par0],
-                                 R(cs->lp.r_fc[L]), 0, st, tab, opaque_tid());
-        __syncthreads();
+        average_child<Q, S>(m, P, unit % Lt::NC, (const T *)cs->f[par1], (T *)cs->f[par0], R(cs->lp.r_fc[L]), 0,
+                            sm.ctab[slot], sm.ptab[slot], tid % Lt::MB);
+        wave_lds_sync();
     }
 }
 
@@ -1548,50 +1618,34 @@ __global__ __launch_bounds__(256) void k_velocity(const int32_t *__restrict__ li
                                                   int children) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
+    using T = typename ST::T;
+    using De = Desc<Lt::D>;
     constexpr int MB = Lt::MB, BPW = 256 / MB;
-    __shared__ BlockStage<Lt, BPW> st;
-    __shared__ int any;
-    const int base = blockIdx.x * BPW;
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
-    if ((int)threadIdx.x < BPW) {
-        const int64_t i = (int64_t)base + threadIdx.x;
-        int B = -1;
-        if (!children) {
-            if (i < n) B = list[i];
-        } else if (i < (int64_t)n * Lt::NC) {
-            const int c0 = m.nbrc[list[i / Lt::NC]];
-            const int C = c0 + (int)(i % Lt::NC);
-            if (c0 >= 0 && (m.bflag[C] & BF_NSKIP)) B = C;
-        }
-        st.id[threadIdx.x] = B;
-        if (B >= 0) any = 1;
+    __shared__ uint64_t tabs[BPW][kTab<Lt>];
+    const int slot = threadIdx.x / MB, l = threadIdx.x % MB;
+    const int64_t i = (int64_t)blockIdx.x * BPW + slot;
+    int B = -1;
+    if (!children) {
+        if (i < n) B = list[i];
+    } else if (i < (int64_t)n * Lt::NC) {
+        const int c0 = m.nbrc[list[i / Lt::NC]];
+        const int C = c0 + (int)(i % Lt::NC);
+        if (c0 >= 0 && (m.bflag[C] & BF_NSKIP)) B = C;
     }
-    __syncthreads();
-    if (!any) return;  // the whole workgroup: nothing to stage
-    stage_blocks<Lt, BPW>(m, st);
-    __shared__ uint64_t tab[Lt::D == 3 ? BPW : 1][27];
-    if constexpr (Lt::D == 3) {
-        fill_row_tables<Lt, BPW>(st, [&](int) -> const DevMesh & { return m; }, [&](int) { return f; }, tab);
-        __syncthreads();
-    }
-    const int s = threadIdx.x / MB, l = threadIdx.x % MB;
-    const int B = st.id[s];
-    if (B < 0) return;
-    if (!velocity_read<Lt>(m, st.link[s], B)) return;
+    if constexpr (Lt::D == 3) B = __builtin_amdgcn_readfirstlane(B);  // one block per wave
+    const int32_t w = desc_word<Lt>(m.desc, B, l);
+    put_rows<Lt>(tabs[slot], w, l, f);
+    wave_lds_sync();
+    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
+    const int h = desc_get<Lt>(w, De::kHid);
+    if (B < 0 || !velocity_read<Lt>(m, w, flag)) return;
+    const CellRows<T> r = cell_rows<Lt, T>(tabs[slot], B, h, l, f, m);
     double fv[Q];
-    bool done = false;
-    if constexpr (Lt::D == 3) {
-        if (!(st.flag[s] & (BF_BOUNDARY | BF_NSKIP))) {
-            // the same values as cell_f64, through the row table
-            gather_interior_by<Lt, ST>(interior_lane<typename ST::T>(tab[s], l & 3, (l >> 2) & 3, l >> 4), fv,
-                                          [](typename ST::R v, int p) {
-                                              return double(v) + (ST::shift ? Lt::w(p) : 0.0);
-                                          });
-            done = true;
-        }
-    }
-    if (!done) cell_f64<Lt, ST>(m, st.link[s], B, st.hid[s], l, f, fv);
+    const auto conv = [](typename ST::R v, int p) { return double(v) + (ST::shift ? Lt::w(p) : 0.0); };
+    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
+        gather_interior_by<Lt, ST>(r.u, fv, conv);
+    else
+        gather_rows_by<Lt, ST, true>(r, fv, conv);
     cell_velocity<Lt>(fv, U, m.capc, (int64_t)B * MB + l);
 }
 
@@ -1931,7 +1985,8 @@ struct Launch {
     static void average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                               int L, int par0, int par1, int grid);
     static void refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
-    static void average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U);
+    static void average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
+                        double *U);
     static void fill_rest(const Ctx &c);
     static void set_rho_u_root(const Ctx &c, const double *ru, int b0, int b1);
     static void velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children);
@@ -1994,7 +2049,7 @@ template <int Q, int S>
 bool Launch<Q, S>::interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
                                   const LevelParams &lp, const BCParams &bc, bool exchange) {
     constexpr int bpw = collide_blocks_per_wg<Q, S>();
-    const int grid = ni + (nblk + bpw - 1) / bpw;
+    const int grid = (ni + kInterpPerWg<Lat<Q>> - 1) / kInterpPerWg<Lat<Q>> + (nblk + bpw - 1) / bpw;
     const bool nts = (int64_t)nblk * Q * c.mb * (int64_t)sizeof(typename Store<S>::T) > c.stream_bytes;
     typename Store<S>::T *f0 = buf<S>(c, 0), *f1 = buf<S>(c, 1);
     if (exchange && !nts) {
@@ -2016,11 +2071,11 @@ bool Launch<Q, S>::interp_collide(const Ctx &c, const int32_t *ilist, int ni, co
 
 template <int Q, int S>
 void Launch<Q, S>::interp(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells) {
-    const int threads = c.dim == 2 ? 64 : 256;
+    const int grid = (n + kInterpPerWg<Lat<Q>> - 1) / kInterpPerWg<Lat<Q>>;
     if (c.m.interp == AMR_INTERP_CUBIC)
-        k_interp<Q, S, 1><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
+        k_interp<Q, S, 1><<<grid, 256, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
     else
-        k_interp<Q, S, 0><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
+        k_interp<Q, S, 0><<<grid, 256, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells);
 }
 
 template <int Q, int S>
@@ -2048,14 +2103,13 @@ void Launch<Q, S>::collide_batch(hipStream_t stream, const SimDesc *sims, const 
 template <int Q, int S>
 void Launch<Q, S>::interp_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                                 int L, int par0, int par1, int grid) {
-    k_interp_batch<Q, S><<<grid, Q == 9 ? 64 : 256, 0, stream>>>(sims, items, count, L, par0, par1);
+    k_interp_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
 }
 
-// one lane per fine cell of the workgroup's children
 template <int Q, int S>
 void Launch<Q, S>::average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                                  int L, int par0, int par1, int grid) {
-    k_average_batch<Q, S><<<grid, Q == 9 ? 64 : 256, 0, stream>>>(sims, items, count, L, par0, par1);
+    k_average_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
 }
 
 template <int Q, int S>
@@ -2065,12 +2119,13 @@ void Launch<Q, S>::refresh_neighbours(const Ctx &c, const int32_t *list, int n, 
 }
 
 template <int Q, int S>
-void Launch<Q, S>::average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U) {
-    // one lane per fine cell of the workgroup's children; 3-D: two workgroups per parent
-    const int split = c.dim == 3 ? 2 : 1;
-    const int threads = c.nc / split * c.mb;
-    if (U) k_average<Q, S, true><<<n * split, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, 1, U);
-    else k_average<Q, S><<<n * split, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp, all_cells, nullptr);
+void Launch<Q, S>::average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
+                           double *U) {
+    const int grid = (int)(((int64_t)n * c.nc + kAvgPerWg<Lat<Q>> - 1) / kAvgPerWg<Lat<Q>>);
+    const typename Store<S>::T *src = buf<S>(c, lp.par[L + 1]);
+    typename Store<S>::T *dst = buf<S>(c, lp.par[L]);
+    if (U) k_average<Q, S, true><<<grid, 256, 0, c.stream>>>(list, n, c.m, src, dst, lp.r_fc[L], 1, U);
+    else k_average<Q, S><<<grid, 256, 0, c.stream>>>(list, n, c.m, src, dst, lp.r_fc[L], all_cells, nullptr);
 }
 
 template <int Q, int S>
@@ -2193,9 +2248,9 @@ void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const L
     k_clear_fresh<<<(n * c.nc + 255) / 256, 256, 0, c.stream>>>(list, n, c.m, c.nc);
 }
 
-void launch_average(const Ctx &c, const int32_t *list, int n, const LevelParams &lp, int all_cells, double *U) {
+void launch_average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells, double *U) {
     if (n <= 0) return;
-    dispatch(c.q, c.storage, [&](auto l) { l.average(c, list, n, lp, all_cells, U); });
+    dispatch(c.q, c.storage, [&](auto l) { l.average(c, list, n, L, lp, all_cells, U); });
 }
 
 void launch_fill_rest(const Ctx &c) {

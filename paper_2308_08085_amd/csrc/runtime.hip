@@ -237,7 +237,7 @@ void step_level(amr_handle *h, int L) {
     step_level(h, L + 1);
     if (h->niface[L] > 0) {
         const LevelParams lp = level_params(h);
-        timed_launch(h, 2, h->niface[L], L, [&] { launch_average(h->c, h->c.iface + L * cap, h->niface[L], lp, 0); });
+        timed_launch(h, 2, h->niface[L], L, [&] { launch_average(h->c, h->c.iface + L * cap, h->niface[L], L, lp, 0); });
     }
 }
 
@@ -558,7 +558,7 @@ amr_status amr_tag(amr_t *h, const amr_tag_params *p, const int8_t *tags_in, int
     const bool vort = !tags_in && (p->kind == AMR_TAG_VORTICITY_REL || p->kind == AMR_TAG_LADDER);
     const bool averaged = vort && h->sync_velocity;
     for (int L = h->lmax - 2; L >= 0; L--)
-        launch_average(c, c.refl + L * cap, h->nref[L], level_params(h), 1, averaged ? c.U : nullptr);
+        launch_average(c, c.refl + L * cap, h->nref[L], L, level_params(h), 1, averaged ? c.U : nullptr);
     if ((ms = mark(h, 1)) != AMR_OK) return ms;
     for (int L = 0; L <= h->lmax - 2; L++)
         if (h->niface[L] > 0) launch_interp(c, c.iface + L * cap, h->niface[L], level_params(h), 0);
