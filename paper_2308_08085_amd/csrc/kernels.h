@@ -15,8 +15,9 @@ struct DevCounters {
     int32_t gtop;
     int32_t n_ref, n_coa, n_rev;
     int32_t nfreed;
-    int32_t n_out;
-    int32_t pad[2];
+    int32_t n_out;   // output cells, and the blocks that hold them
+    int32_t n_outb;
+    int32_t pad[1];
     unsigned long long wmax_bits;
     int32_t totals[kMaxLevels];
     int32_t bases[kMaxLevels];
@@ -54,7 +55,8 @@ struct Ctx {
     int8_t *bins;        // [lmax * cap]
     int32_t *scan_part;  // [nwg_max * 8]
     int32_t *cnt;        // [cap]
-    int32_t *off;        // [cap]
+    int32_t *off;        // [cap] first output cell of each block
+    int32_t *outl;       // [cap] the blocks with output cells, by ID (= cnt, once that has been summed)
     double *crit;        // [cap]
     double *U;           // [3][cap * Mb] FP64 cell velocities for the criterion
     double *part4;       // [cap * 4]
@@ -102,7 +104,9 @@ void launch_set_rho_u_root(const Ctx &c, const double *rho_u_dev, int b0, int b1
 void launch_velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children = false);
 void launch_vorticity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp);
 void launch_block_f(const Ctx &c, int set, int b0, int b1, double *stage, const LevelParams &lp);
-void launch_out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage, const LevelParams &lp);
+// rows of the blocks outl[k0 .. k1) into stage; head[0..1]: first row's number, rows
+void launch_out_gather(const Ctx &c, int kind, int k0, int k1, int n_list, int32_t n_out, int64_t *head, void *stage,
+                       const LevelParams &lp);
 void launch_mass(const Ctx &c, const LevelParams &lp);
 // the same sums through the fixed device array of the library (no arena
 // scratch): its address on `device` (resolved once, with that device
@@ -148,6 +152,5 @@ void launch_effective_tags(const Ctx &c);
 void launch_adapt_assign(const Ctx &c, int n_ref);                 // S2 + S3
 void launch_adapt_build(const Ctx &c, int n_ref);                 // S4 .. S7 (statuses)
 void launch_connectivity(const Ctx &c, int id_bound);             // S8 + masks + interface lists
-void launch_out_count(const Ctx &c);  // per-block output counts + exclusive offsets, n_out
 
 }  // namespace amr

@@ -1517,25 +1517,30 @@ __global__ __launch_bounds__(256) void k_exchange_batch(const SimDesc *__restric
 }
 
 // ---------------------------------------------------------------------------
-// Per-level totals of the momentum exchange over the active blocks (one
-// workgroup per level, fixed summation order): out[L][0..2].
-static __global__ __launch_bounds__(256) void k_force_sum(DevMesh m, double *out) {
-    __shared__ double s[3][256];
-    const int L = blockIdx.x, t = threadIdx.x;
+// Per-level totals of the momentum exchange (one workgroup per level, fixed
+// summation order): out[L][0..2].  Only leaf blocks next to a solid block, the
+// level's list, hold any; reading every block of the capacity instead took
+// 440 us for 3.9e5 blocks (3 levels), the lists 4 us.
+static __global__ __launch_bounds__(1024) void k_force_sum(const double *force, const int32_t *__restrict__ lists,
+                                                           int cap, const DevCounters *ctr, double *out) {
+    __shared__ double s[3][16];
+    const int L = blockIdx.x, t = threadIdx.x, n = ctr->nsolid[L];
     double a[3] = {0.0, 0.0, 0.0};
-    for (int B = t; B < m.cap; B += 256) {
-        if (m.status[B] == ST_INACTIVE || m.level[B] != L) continue;
-        for (int c = 0; c < 3; c++) a[c] += m.force[(int64_t)B * 3 + c];
+    for (int i = t; i < n; i += 1024) {
+        const int64_t B = lists[(int64_t)L * cap + i];
+        for (int c = 0; c < 3; c++) a[c] += force[B * 3 + c];
     }
-    for (int c = 0; c < 3; c++) s[c][t] = a[c];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+        for (int c = 0; c < 3; c++) a[c] += __shfl_xor(a[c], off, 64);
+    if ((t & 63) == 0)
+        for (int c = 0; c < 3; c++) s[c][t >> 6] = a[c];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int c = 0; c < 3; c++) s[c][t] += s[c][t + w];
-        __syncthreads();
+    if (t < 3) {
+        double v = 0.0;
+        for (int w = 0; w < 16; w++) v += s[t][w];
+        out[L * 3 + t] = v;
     }
-    if (t == 0)
-        for (int c = 0; c < 3; c++) out[L * 3 + c] = s[c][0];
 }
 
 static __global__ void k_force_reset(DevMesh m) {
@@ -1601,6 +1606,31 @@ __global__ __launch_bounds__(256) void k_set_rho_u(DevMesh m, typename Store<S>:
 // scaled to root-cell units; block maximum per leaf and the global maximum
 // (atomic max on the bit pattern of a non-negative double).
 template <typename Lt, typename ST>
+__device__ __forceinline__ void cell_f64_desc(const DevMesh &m, uint64_t *tab, int32_t w, int B, int l,
+                                              const typename ST::T *f, double *fv) {
+    using T = typename ST::T;
+    using De = Desc<Lt::D>;
+    put_rows<Lt>(tab, w, l, f);
+    wave_lds_sync();
+    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
+    const CellRows<T> r = cell_rows<Lt, T>(tab, B, desc_get<Lt>(w, De::kHid), l, f, m);
+    const auto conv = [](typename ST::R v, int p) { return double(v) + (ST::shift ? Lt::w(p) : 0.0); };
+    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
+        gather_interior_by<Lt, ST>(r.u, fv, conv);
+    else
+        gather_rows_by<Lt, ST, true>(r, fv, conv);
+}
+
+// ghost cells of a block from its descriptor words
+template <typename Lt>
+__device__ __forceinline__ uint64_t desc_ghost(int32_t w) {
+    using De = Desc<Lt::D>;
+    const uint64_t lo = (uint32_t)desc_get<Lt>(w, De::kGhost);
+    if constexpr (Lt::D == 3) return lo | (uint64_t)(uint32_t)desc_get<Lt>(w, De::kGhost + 1) << 32;
+    else return lo & 0xffff;
+}
+
+template <typename Lt, typename ST>
 __device__ inline void cell_f64(const DevMesh &m, const int32_t *link, int B, int h, int l,
                                 const typename ST::T *f, double *fv) {
 #pragma unroll
@@ -1618,7 +1648,6 @@ __global__ __launch_bounds__(256) void k_velocity(const int32_t *__restrict__ li
                                                   int children) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
-    using T = typename ST::T;
     using De = Desc<Lt::D>;
     constexpr int MB = Lt::MB, BPW = 256 / MB;
     __shared__ uint64_t tabs[BPW][kTab<Lt>];
@@ -1633,19 +1662,11 @@ __global__ __launch_bounds__(256) void k_velocity(const int32_t *__restrict__ li
         if (c0 >= 0 && (m.bflag[C] & BF_NSKIP)) B = C;
     }
     if constexpr (Lt::D == 3) B = __builtin_amdgcn_readfirstlane(B);  // one block per wave
+    if (B < 0) return;  // the block's lanes together
     const int32_t w = desc_word<Lt>(m.desc, B, l);
-    put_rows<Lt>(tabs[slot], w, l, f);
-    wave_lds_sync();
-    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
-    const int h = desc_get<Lt>(w, De::kHid);
-    if (B < 0 || !velocity_read<Lt>(m, w, flag)) return;
-    const CellRows<T> r = cell_rows<Lt, T>(tabs[slot], B, h, l, f, m);
+    if (!velocity_read<Lt>(m, w, (uint32_t)desc_get<Lt>(w, De::kFlags))) return;
     double fv[Q];
-    const auto conv = [](typename ST::R v, int p) { return double(v) + (ST::shift ? Lt::w(p) : 0.0); };
-    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
-        gather_interior_by<Lt, ST>(r.u, fv, conv);
-    else
-        gather_rows_by<Lt, ST, true>(r, fv, conv);
+    cell_f64_desc<Lt, ST>(m, tabs[slot], w, B, l, f, fv);
     cell_velocity<Lt>(fv, U, m.capc, (int64_t)B * MB + l);
 }
 
@@ -1776,37 +1797,47 @@ __global__ __launch_bounds__(256) void k_block_f(DevMesh m, typename Store<S>::T
 }
 
 // output cells: leaf, non-ghost cells in (block ID, cell) order; kind: cells,
-// rho/u, or f
+// rho/u, or f.  Entries [k0, k1) of the list of blocks with output cells, one
+// block per 64 (2-D: 16) lanes; head receives the first row's number and the
+// rows written.  n_list, n_out: the list's length and the rows of all of it.
 template <int Q, int S>
-__global__ __launch_bounds__(256) void k_out_gather(DevMesh m, typename Store<S>::T *f0, typename Store<S>::T *f1,
-                                                    LevelParams lp, int kind, int b0, int b1,
-                                                    const int32_t *__restrict__ off, int32_t off0, void *stage) {
+__global__ __launch_bounds__(256) void k_out_gather(DevMesh m, const typename Store<S>::T *f0,
+                                                    const typename Store<S>::T *f1, LevelParams lp, int kind,
+                                                    const int32_t *__restrict__ list, int k0, int k1, int n_list,
+                                                    const int32_t *__restrict__ off, int32_t n_out, int64_t *head,
+                                                    void *stage) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
+    using De = Desc<Lt::D>;
     constexpr int MB = Lt::MB, BPW = 256 / MB;
-    __shared__ BlockStage<Lt, BPW> st;
-    if ((int)threadIdx.x < BPW) {
-        const int B = b0 + blockIdx.x * BPW + threadIdx.x;
-        st.id[threadIdx.x] = (B < b1 && m.status[B] == ST_UNREF) ? B : -1;
+    __shared__ uint64_t tabs[BPW][kTab<Lt>];
+    const int slot = threadIdx.x / MB, l = threadIdx.x % MB;
+    int k = k0 + blockIdx.x * BPW + slot;
+    if constexpr (Lt::D == 3) k = __builtin_amdgcn_readfirstlane(k);  // one block per wave
+    const int32_t off0 = off[list[k0]];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        head[0] = off0;
+        head[1] = (k1 < n_list ? off[list[k1]] : n_out) - off0;
     }
-    __syncthreads();
-    stage_blocks<Lt, BPW>(m, st);
-    const int s = threadIdx.x / MB, l = threadIdx.x % MB;
-    const int B = st.id[s];
-    if (B < 0) return;
+    if (k >= k1) return;
+    const int B = list[k];
+    const int32_t w = desc_word<Lt>(m.desc, B, l);
     const uint64_t full = MB == 64 ? ~0ull : ((1ull << MB) - 1);
-    const uint64_t outm = ~m.gmask[B] & full;
-    if (!((outm >> l) & 1ull)) return;
+    const uint64_t outm = ~desc_ghost<Lt>(w) & full;
     const int64_t pos = (int64_t)off[B] - off0 + __popcll(outm & ((1ull << l) - 1));
+    const bool out = (outm >> l) & 1ull;
     if (kind == AMR_FIELD_CELLS) {
         int32_t *o = (int32_t *)stage + 2 * pos;
-        o[0] = B;
-        o[1] = l;
+        if (out) {
+            o[0] = B;
+            o[1] = l;
+        }
         return;
     }
-    const typename ST::T *f = lp.par[m.level[B]] ? f1 : f0;
+    const int L = (int)((uint32_t)desc_get<Lt>(w, De::kFlags) >> 16);
     double fv[Q];
-    cell_f64<Lt, ST>(m, st.link[s], B, st.hid[s], l, f, fv);
+    cell_f64_desc<Lt, ST>(m, tabs[slot], w, B, l, lp.par[L] ? f1 : f0, fv);
+    if (!out) return;
     if (kind == AMR_FIELD_RHO_U) {
         double rho = 0.0, j[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -1831,29 +1862,31 @@ __global__ __launch_bounds__(256) void k_out_gather(DevMesh m, typename Store<S>
 // FP64 mass and momentum of the output cells: fixed-order per-block partials,
 // then a single-workgroup fixed-order sum.
 //
-// Body: the partial of the staged blocks with first ID b (256 threads, Mb per
-// block); lane 0 of each block's group returns it in v.
+// Body: the partial of block b + thread / Mb, by its Mb lanes; lane 0 of them
+// returns it in v.  A workgroup of 256 threads has no barrier here, and blocks
+// that are not leaves (most of the capacity of a mesh that may still grow) cost
+// their status only: 41 to 17 us for a 2-D capacity of 3.9e5 blocks.
 template <int Q, int S>
 __device__ __forceinline__ void mass_block_partial(const DevMesh &m, typename Store<S>::T *f0,
                                                    typename Store<S>::T *f1, const LevelParams &lp,
-                                                   BlockStage<Lat<Q>, 256 / Lat<Q>::MB> &st, int64_t b, double *v) {
+                                                   uint64_t (*tabs)[kTab<Lat<Q>>], int64_t b, double *v) {
     using Lt = Lat<Q>;
     using ST = Store<S>;
-    constexpr int MB = Lt::MB, BPW = 256 / MB;
-    if ((int)threadIdx.x < BPW) {
-        const int64_t B = b + threadIdx.x;
-        st.id[threadIdx.x] = (B < m.cap && m.status[B] == ST_UNREF) ? (int)B : -1;
-    }
-    __syncthreads();
-    stage_blocks<Lt, BPW>(m, st);
-    const int s = threadIdx.x / MB, l = threadIdx.x % MB;
-    const int B = st.id[s];
+    using De = Desc<Lt::D>;
+    constexpr int MB = Lt::MB;
+    const int tid = opaque_tid();  // called in a loop: nothing of a cell's addressing is kept across it
+    const int slot = tid / MB, l = tid % MB;
+    int64_t Bw = b + slot;
+    if (Bw >= m.cap || m.status[Bw] != ST_UNREF) Bw = -1;
+    int B = (int)Bw;
+    if constexpr (Lt::D == 3) B = __builtin_amdgcn_readfirstlane(B);  // one block per wave
     for (int a = 0; a < 4; a++) v[a] = 0.0;
-    if (B >= 0 && !((m.gmask[B] >> l) & 1ull)) {
-        const int L = m.level[B];
-        const typename ST::T *f = lp.par[L] ? f1 : f0;
-        double fv[Q];
-        cell_f64<Lt, ST>(m, st.link[s], B, st.hid[s], l, f, fv);
+    if (B < 0) return;  // the block's lanes together
+    const int32_t w = desc_word<Lt>(m.desc, B, l);
+    const int L = (int)((uint32_t)desc_get<Lt>(w, De::kFlags) >> 16);
+    double fv[Q];
+    cell_f64_desc<Lt, ST>(m, tabs[slot], w, B, l, lp.par[L] ? f1 : f0, fv);
+    if (!((desc_ghost<Lt>(w) >> l) & 1ull)) {
         double rho = 0.0, j[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int p = 0; p < Q; p++) {
@@ -1875,9 +1908,9 @@ template <int Q, int S>
 __global__ __launch_bounds__(256) void k_mass_blocks(DevMesh m, typename Store<S>::T *f0, typename Store<S>::T *f1,
                                                      LevelParams lp, double *part4) {
     constexpr int MB = Lat<Q>::MB, BPW = 256 / MB;
-    __shared__ BlockStage<Lat<Q>, BPW> st;
+    __shared__ uint64_t tabs[BPW][kTab<Lat<Q>>];
     double v[4];
-    mass_block_partial<Q, S>(m, f0, f1, lp, st, (int64_t)blockIdx.x * BPW, v);
+    mass_block_partial<Q, S>(m, f0, f1, lp, tabs, (int64_t)blockIdx.x * BPW, v);
     const int64_t Braw = (int64_t)blockIdx.x * BPW + threadIdx.x / MB;
     if (Braw < m.cap && threadIdx.x % MB == 0)
         for (int a = 0; a < 4; a++) part4[Braw * 4 + a] = v[a];
@@ -1932,7 +1965,7 @@ __global__ __launch_bounds__(256) void k_mass_chunks_direct(DevMesh m, typename 
                                                             typename Store<S>::T *f1, LevelParams lp,
                                                             double *chunks) {
     constexpr int MB = Lat<Q>::MB, BPW = 256 / MB;
-    __shared__ BlockStage<Lat<Q>, BPW> st;
+    __shared__ uint64_t tabs[BPW][kTab<Lat<Q>>];
     __shared__ double s_part[256][4];
     __shared__ double s[4][256];
     const int64_t b0 = (int64_t)blockIdx.x * kMassChunk;
@@ -1941,11 +1974,12 @@ __global__ __launch_bounds__(256) void k_mass_chunks_direct(DevMesh m, typename 
     for (int r = 0; r < kMassChunk / 256; r++) {
         for (int i = 0; i < 256 / BPW; i++) {
             double v[4];
-            mass_block_partial<Q, S>(m, f0, f1, lp, st, b0 + 256 * r + BPW * i, v);
+            mass_block_partial<Q, S>(m, f0, f1, lp, tabs, b0 + 256 * r + BPW * i, v);
             if (t % MB == 0)
                 for (int a = 0; a < 4; a++) s_part[BPW * i + t / MB][a] = v[a];
-            __syncthreads();  // the stage is rewritten by the next group
+            wave_lds_sync();
         }
+        __syncthreads();
         if (b0 + 256 * r + t < m.cap)
             for (int a = 0; a < 4; a++) acc[a] += s_part[t][a];
         __syncthreads();
@@ -1991,7 +2025,8 @@ struct Launch {
     static void set_rho_u_root(const Ctx &c, const double *ru, int b0, int b1);
     static void velocity(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, bool children);
     static void block_f(const Ctx &c, int set, int b0, int b1, double *stage, const LevelParams &lp);
-    static void out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage, const LevelParams &lp);
+    static void out_gather(const Ctx &c, int kind, int k0, int k1, int n_list, int32_t n_out, int64_t *head,
+                           void *stage, const LevelParams &lp);
     static void mass_blocks(const Ctx &c, const LevelParams &lp);
     static void mass_chunks_direct(const Ctx &c, const LevelParams &lp, double *chunks);
 };
@@ -2153,10 +2188,10 @@ void Launch<Q, S>::block_f(const Ctx &c, int set, int b0, int b1, double *stage,
 }
 
 template <int Q, int S>
-void Launch<Q, S>::out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage,
-                              const LevelParams &lp) {
-    k_out_gather<Q, S><<<grid_blocks(b1 - b0, c.mb), 256, 0, c.stream>>>(c.m, buf<S>(c, 0), buf<S>(c, 1), lp, kind, b0,
-                                                                         b1, c.off, off0, stage);
+void Launch<Q, S>::out_gather(const Ctx &c, int kind, int k0, int k1, int n_list, int32_t n_out, int64_t *head,
+                              void *stage, const LevelParams &lp) {
+    k_out_gather<Q, S><<<grid_blocks(k1 - k0, c.mb), 256, 0, c.stream>>>(
+        c.m, buf<S>(c, 0), buf<S>(c, 1), lp, kind, c.outl, k0, k1, n_list, c.off, n_out, head, stage);
 }
 
 template <int Q, int S>
@@ -2281,12 +2316,15 @@ void launch_block_f(const Ctx &c, int set, int b0, int b1, double *stage, const 
     dispatch(c.q, c.storage, [&](auto l) { l.block_f(c, set, b0, b1, stage, lp); });
 }
 
-void launch_out_gather(const Ctx &c, int kind, int b0, int b1, int32_t off0, void *stage, const LevelParams &lp) {
-    if (b1 <= b0) return;
-    dispatch(c.q, c.storage, [&](auto l) { l.out_gather(c, kind, b0, b1, off0, stage, lp); });
+void launch_out_gather(const Ctx &c, int kind, int k0, int k1, int n_list, int32_t n_out, int64_t *head, void *stage,
+                       const LevelParams &lp) {
+    if (k1 <= k0) return;
+    dispatch(c.q, c.storage, [&](auto l) { l.out_gather(c, kind, k0, k1, n_list, n_out, head, stage, lp); });
 }
 
-void launch_force_sum(const Ctx &c, double *out) { k_force_sum<<<c.m.lmax, 256, 0, c.stream>>>(c.m, out); }
+void launch_force_sum(const Ctx &c, double *out) { 
+    k_force_sum<<<c.m.lmax, 1024, 0, c.stream>>>(c.m.force, c.solidl, c.m.cap, c.ctr, out);
+ }
 
 void launch_force_reset(const Ctx &c) {
     const int64_t n = (int64_t)c.m.cap * 3;

@@ -714,8 +714,17 @@ __global__ void k_out_count(DevMesh m, int32_t *cnt, int mb) {
     cnt[B] = m.status[B] == ST_UNREF ? (int)__popcll(~m.gmask[B] & full) : 0;
 }
 
-__global__ void k_out_total(const int32_t *cnt, const int32_t *off, int cap, DevCounters *ctr) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) ctr->n_out = cap > 0 ? off[cap - 1] + cnt[cap - 1] : 0;
+__global__ void k_out_bins(const int32_t *cnt, const int32_t *off, int cap, int8_t *bins, DevCounters *ctr) {
+    const int B = blockIdx.x * blockDim.x + threadIdx.x;
+    if (B >= cap) return;
+    bins[B] = cnt[B] > 0 ? 0 : -1;
+    if (B == cap - 1) ctr->n_out = off[B] + cnt[B];
+}
+
+__global__ void k_out_list(const int8_t *bins, const int32_t *rank, int cap, int32_t *outl, DevCounters *ctr) {
+    const int B = blockIdx.x * blockDim.x + threadIdx.x;
+    if (B < cap && bins[B] == 0) outl[rank[B]] = B;
+    if (B == 0) ctr->n_outb = ctr->totals[0];
 }
 
 RootParams root_params(const Ctx &c) {
@@ -836,6 +845,20 @@ __global__ __launch_bounds__(256) void k_target_cells(DevMesh m, const int32_t *
     }
 }
 
+// output cells of each block, their exclusive offsets and the list of the
+// blocks that have any: with them a field read needs no pass over the mesh
+void output_lists(const Ctx &c) {
+    const int cap = c.m.cap;
+    k_out_count<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.cnt, c.mb);
+    const int nwg = (int)((cap + kScanItems - 1) / kScanItems);
+    k_wscan_count<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part);
+    k_scan_part<<<1, 256, 0, c.stream>>>(c.scan_part, nwg, 1, c.ctr);
+    k_wscan_apply<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part, c.off);
+    k_out_bins<<<grid_for(cap), 256, 0, c.stream>>>(c.cnt, c.off, cap, c.bins, c.ctr);
+    run_scan(c, c.bins, cap, 1);
+    k_out_list<<<grid_for(cap), 256, 0, c.stream>>>(c.bins, c.rank, cap, c.outl, c.ctr);
+}
+
 template <typename Dd>
 void masks_and_lists(const Ctx &c) {
     const int cap = c.m.cap;
@@ -867,6 +890,7 @@ void masks_and_lists(const Ctx &c) {
     k_copy_lists<<<grid_for(tot), 256, 0, c.stream>>>(c.ids_tmp, c.sweep, cap, c.m.lmax, c.ctr, 3);
     k_target_reset<<<1, 64, 0, c.stream>>>(c.ctr);
     k_target_cells<Dd><<<dim3(grid_for(cap), c.m.lmax), 256, 0, c.stream>>>(c.m, c.iface, c.ctr);
+    output_lists(c);
 }
 
 template <typename Dd>
@@ -981,15 +1005,5 @@ void launch_adapt_assign(const Ctx &c, int n_ref) { AMR_DIM_DISPATCH(c.dim, adap
 void launch_adapt_build(const Ctx &c, int n_ref) { AMR_DIM_DISPATCH(c.dim, adapt_build_t<Dd>(c, n_ref)); }
 
 void launch_connectivity(const Ctx &c, int) { AMR_DIM_DISPATCH(c.dim, connectivity_t<Dd>(c)); }
-
-void launch_out_count(const Ctx &c) {
-    const int cap = c.m.cap;
-    k_out_count<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.cnt, c.mb);
-    const int nwg = (int)((cap + kScanItems - 1) / kScanItems);
-    k_wscan_count<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part);
-    k_scan_part<<<1, 256, 0, c.stream>>>(c.scan_part, nwg, 1, c.ctr);
-    k_wscan_apply<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part, c.off);
-    k_out_total<<<1, 64, 0, c.stream>>>(c.cnt, c.off, cap, c.ctr);
-}
 
 }  // namespace amr

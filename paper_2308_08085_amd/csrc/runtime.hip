@@ -277,6 +277,8 @@ amr_status refresh_counts(amr_handle *h) {
         h->avg_w[L] = L < h->lmax ? (double)dc.avg_w[L] : 0.0;
     }
     h->gtop = dc.gtop;
+    h->n_out = dc.n_out;
+    h->n_outb = dc.n_outb;
     return AMR_OK;
 }
 
@@ -386,6 +388,7 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
     c.clist = (int32_t *)(a + lay.clist);
     c.cnt = (int32_t *)(a + lay.cnt);
     c.off = (int32_t *)(a + lay.off);
+    c.outl = c.cnt;
     c.rank = (int32_t *)(a + lay.rank);
     c.bins = (int8_t *)(a + lay.bins);
     c.scan_part = (int32_t *)(a + lay.scan_part);
@@ -796,10 +799,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             drop_graphs(h);
             return sync_checked(h);
         }
-        launch_out_count(c);
-        DevCounters dc;
-        if ((s = read_counters(h, &dc)) != AMR_OK) return s;
-        const int64_t n_out = dc.n_out;
+        const int64_t n_out = h->n_out;
         if (kind == AMR_FIELD_N_OUT) {
             if ((s = need(8)) != AMR_OK) return s;
             memcpy(buf, &n_out, 8);
@@ -807,17 +807,15 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         }
         const size_t row = kind == AMR_FIELD_CELLS ? 8 : (kind == AMR_FIELD_RHO_U ? 32 : (size_t)q * 8);
         if ((s = need((uint64_t)n_out * row)) != AMR_OK) return s;
-        std::vector<int32_t> off(cap + 1);
-        HIP_TRY(hipMemcpyAsync(off.data(), c.off, cap * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        off[cap] = (int32_t)n_out;
-        const int per_blocks = (int)(c.staging_bytes / (row * mb));
-        for (int b0 = 0; b0 < (int)cap; b0 += per_blocks) {
-            const int b1 = b0 + per_blocks < (int)cap ? b0 + per_blocks : (int)cap;
-            const int64_t rows = off[b1] - off[b0];
-            if (rows == 0) continue;
-            launch_out_gather(c, kind, b0, b1, off[b0], c.staging, lp);
-            HIP_TRY(hipMemcpyAsync((char *)buf + (size_t)off[b0] * row, c.staging, rows * row,
+        // the staging area: a 64-byte head (first row, rows), then the rows
+        const int per = (int)((c.staging_bytes - 64) / (row * mb));
+        for (int k0 = 0; k0 < h->n_outb; k0 += per) {
+            const int k1 = k0 + per < h->n_outb ? k0 + per : h->n_outb;
+            int64_t head[2];
+            launch_out_gather(c, kind, k0, k1, h->n_outb, h->n_out, (int64_t *)c.staging, (char *)c.staging + 64, lp);
+            HIP_TRY(hipMemcpyAsync(head, c.staging, sizeof(head), hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            HIP_TRY(hipMemcpyAsync((char *)buf + (size_t)head[0] * row, (char *)c.staging + 64, (size_t)head[1] * row,
                                    hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
         }

@@ -41,6 +41,7 @@ struct amr_handle {
     int nids[kMaxLevels], niface[kMaxLevels], nsolid[kMaxLevels], nref[kMaxLevels], nsweep[kMaxLevels];
     double ghost_w[kMaxLevels], avg_w[kMaxLevels];  // cells the grid communication of each level moves
     int gtop;
+    int n_out, n_outb;  // output cells of the mesh, blocks that hold them
     int par[kMaxLevels];
     double force_sweeps[kMaxLevels] = {0};  // collide-stream sweeps per level since the force reset
     bool force_on = true;                   // accumulate the momentum exchange every sweep
