@@ -18,7 +18,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 STORAGES = ("AMR_F64", "AMR_F32", "AMR_F32S", "AMR_F16S", "AMR_BF16S")
 UNITS = [("lbm_q%d_%s" % (q, s[4:].lower()), "lbm_kernels.hip", ["-DAMR_TU_Q=%d" % q, "-DAMR_TU_S=" + s])
          for q in (27, 19, 9) for s in STORAGES] + \
-        [(n, n + ".hip", []) for n in ("lbm_kernels", "mesh_kernels", "runtime", "batch")]
+        [(n, n + ".hip", []) for n in ("lbm_kernels", "mesh_kernels", "runtime", "transfer", "batch")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -343,8 +343,7 @@ amr_status amr_batch_step(amr_batch_t *b, int32_t n, uint32_t flags) {
             amr_t *h = b->sims[i];
             launch_mass(h->c, level_params(h));
             double mass[4];
-            HIP_TRY(hipMemcpyAsync(mass, h->c.ctr->mass, sizeof(mass), hipMemcpyDeviceToHost, b->stream));
-            HIP_TRY(hipStreamSynchronize(b->stream));
+            if ((s = copy_out(h, mass, h->c.ctr->mass, sizeof(mass))) != AMR_OK) return s;
             for (int a = 0; a < 4; a++)
                 if (!std::isfinite(mass[a]) && bad < 0) bad = (int)i;
         }

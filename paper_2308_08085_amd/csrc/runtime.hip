@@ -258,9 +258,7 @@ amr_status collect_timings(amr_handle *h) {
 }
 
 amr_status read_counters(amr_handle *h, DevCounters *out) {
-    HIP_TRY(hipMemcpyAsync(out, h->c.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, h->c.stream));
-    HIP_TRY(hipStreamSynchronize(h->c.stream));
-    return AMR_OK;
+    return copy_out(h, out, h->c.ctr, sizeof(DevCounters));
 }
 
 amr_status refresh_counts(amr_handle *h) {
@@ -455,8 +453,10 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
     launch_force_reset(c);
     launch_init_mesh(c);
     s = sync_checked(h);
+    transfer_add_user(h);
     if (s == AMR_OK) s = refresh_counts(h);
     if (s != AMR_OK) {
+        transfer_drop_user(h);
         delete h;
         return s;
     }
@@ -475,6 +475,7 @@ amr_status amr_destroy(amr_t *h) {
     for (auto e : h->event_pool) hipEventDestroy(e);
     for (auto e : h->step_ev)
         if (e) hipEventDestroy(e);
+    transfer_drop_user(h);
     delete h;
     return AMR_OK;
 }
@@ -522,8 +523,8 @@ amr_status lbm_step(amr_t *h, int32_t n, uint32_t flags) {
     if (flags & AMR_CHECK_FINITE) {
         launch_mass(h->c, level_params(h));
         double mass[4];
-        HIP_TRY(hipMemcpyAsync(mass, h->c.ctr->mass, sizeof(mass), hipMemcpyDeviceToHost, h->c.stream));
-        HIP_TRY(hipStreamSynchronize(h->c.stream));
+        amr_status ms = copy_out(h, mass, h->c.ctr->mass, sizeof(mass));
+        if (ms != AMR_OK) return ms;
         for (int a = 0; a < 4; a++)
             if (!std::isfinite(mass[a])) return fail(AMR_ERR_UNSTABLE, "non-finite mass/momentum after lbm_step");
     }
@@ -568,7 +569,9 @@ amr_status amr_tag(amr_t *h, const amr_tag_params *p, const int8_t *tags_in, int
     if ((ms = mark(h, 2)) != AMR_OK) return ms;
     launch_crit_reset(c);
     if (tags_in) {
-        HIP_TRY(hipMemcpyAsync(c.m.tag, tags_in, cap, hipMemcpyHostToDevice, c.stream));
+        const void *from = tags_in;
+        if (h->pin && cap <= kPinBytes) from = memcpy(h->pin, tags_in, cap);  // read before this call returns
+        HIP_TRY(hipMemcpyAsync(c.m.tag, from, cap, hipMemcpyHostToDevice, c.stream));
     } else if (p->kind == AMR_TAG_VORTICITY_REL || p->kind == AMR_TAG_LADDER) {
         const LevelParams lp = level_params(h);
         for (int L = 0; L < h->lmax; L++) {
@@ -594,8 +597,9 @@ amr_status amr_tag(amr_t *h, const amr_tag_params *p, const int8_t *tags_in, int
     }
     launch_effective_tags(c);
     if ((ms = mark(h, 3)) != AMR_OK) return ms;
-    if (tags_out) HIP_TRY(hipMemcpyAsync(tags_out, c.m.tag, cap, hipMemcpyDeviceToHost, c.stream));
-    const amr_status s = sync_checked(h);
+    amr_status s = AMR_OK;
+    if (tags_out && (s = copy_out(h, tags_out, c.m.tag, cap)) != AMR_OK) return s;
+    s = sync_checked(h);
     if (s != AMR_OK) return s;
     for (int k = 0; k < 3; k++) h->step_ms[AMR_T_SYNC_AVERAGE + k] = between(h, k, k + 1);
     return AMR_OK;
@@ -807,31 +811,42 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         }
         const size_t row = kind == AMR_FIELD_CELLS ? 8 : (kind == AMR_FIELD_RHO_U ? 32 : (size_t)q * 8);
         if ((s = need((uint64_t)n_out * row)) != AMR_OK) return s;
-        // the staging area: a 64-byte head (first row, rows), then the rows
-        const int per = (int)((c.staging_bytes - 64) / (row * mb));
-        for (int k0 = 0; k0 < h->n_outb; k0 += per) {
-            const int k1 = k0 + per < h->n_outb ? k0 + per : h->n_outb;
-            int64_t head[2];
-            launch_out_gather(c, kind, k0, k1, h->n_outb, h->n_out, (int64_t *)c.staging, (char *)c.staging + 64, lp);
-            HIP_TRY(hipMemcpyAsync(head, c.staging, sizeof(head), hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
-            HIP_TRY(hipMemcpyAsync((char *)buf + (size_t)head[0] * row, (char *)c.staging + 64, (size_t)head[1] * row,
-                                   hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
-        }
-        return sync_checked(h);
+        // a chunk: its head (first row, rows), then the rows of whole blocks
+        const uint64_t total = (uint64_t)n_out * row;
+        size_t chunk = transfer_chunk(h, total);
+        if (total + kHeadBytes <= kPinBytes) chunk = (size_t)h->n_outb * row * mb + kHeadBytes;  // in one
+        const int per = std::max(1, (int)((chunk - kHeadBytes) / (row * mb)));
+        s = transfer_out(
+            h, (h->n_outb + per - 1) / per, total,
+            [&](int i, char *to) {
+                launch_out_gather(c, kind, i * per, std::min(h->n_outb, (i + 1) * per), h->n_outb, h->n_out,
+                                  (int64_t *)to, to + kHeadBytes, lp);
+            },
+            [&](int, const int64_t *head) {
+                return Piece{(char *)buf + (size_t)head[0] * row, kHeadBytes, (size_t)head[1] * row};
+            });
+        return s == AMR_OK ? sync_checked(h) : s;
     }
     case AMR_FIELD_BLOCK_F: {
         const size_t row = (size_t)mb * q * 8;
         if ((s = need(cap * row)) != AMR_OK) return s;
+        if (op == AMR_GET) {
+            const int per = std::max(1, (int)(transfer_chunk(h, cap * row) / row));
+            const auto end = [&](int i) { return std::min((int)cap, (i + 1) * per); };
+            s = transfer_out(
+                h, ((int)cap + per - 1) / per, cap * row,
+                [&](int i, char *to) { launch_block_f(c, 0, i * per, end(i), (double *)to, lp); },
+                [&](int i, const int64_t *) {
+                    return Piece{(char *)buf + (size_t)i * per * row, 0, (size_t)(end(i) - i * per) * row};
+                });
+            return s == AMR_OK ? sync_checked(h) : s;
+        }
         const int per_blocks = (int)(c.staging_bytes / row);
         for (int b0 = 0; b0 < (int)cap; b0 += per_blocks) {
             const int b1 = b0 + per_blocks < (int)cap ? b0 + per_blocks : (int)cap;
             char *hb = (char *)buf + (size_t)b0 * row;
-            const size_t nbytes = (size_t)(b1 - b0) * row;
-            if (op == AMR_SET) HIP_TRY(hipMemcpyAsync(c.staging, hb, nbytes, hipMemcpyHostToDevice, st));
-            launch_block_f(c, op == AMR_SET, b0, b1, (double *)c.staging, lp);
-            if (op == AMR_GET) HIP_TRY(hipMemcpyAsync(hb, c.staging, nbytes, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipMemcpyAsync(c.staging, hb, (size_t)(b1 - b0) * row, hipMemcpyHostToDevice, st));
+            launch_block_f(c, 1, b0, b1, (double *)c.staging, lp);
             HIP_TRY(hipStreamSynchronize(st));
         }
         return sync_checked(h);
@@ -839,35 +854,29 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
     case AMR_FIELD_LEVEL:
     case AMR_FIELD_STATUS: {
         if ((s = need(cap)) != AMR_OK) return s;
-        HIP_TRY(hipMemcpyAsync(buf, kind == AMR_FIELD_LEVEL ? (void *)c.m.level : (void *)c.m.status, cap,
-                               hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, buf, kind == AMR_FIELD_LEVEL ? (void *)c.m.level : (void *)c.m.status, cap);
     }
     case AMR_FIELD_COORD: {
         if ((s = need(cap * 12)) != AMR_OK) return s;
-        HIP_TRY(hipMemcpyAsync(buf, c.m.X, cap * 12, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, buf, c.m.X, cap * 12);
     }
     case AMR_FIELD_NBR:
     case AMR_FIELD_NBR_CHILD: {
         if ((s = need(cap * nb * 4)) != AMR_OK) return s;
-        HIP_TRY(hipMemcpyAsync(buf, kind == AMR_FIELD_NBR ? c.m.nbr : c.m.nbrc, cap * nb * 4, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, buf, kind == AMR_FIELD_NBR ? c.m.nbr : c.m.nbrc, cap * nb * 4);
     }
     case AMR_FIELD_IDSET: {
         const size_t lmax = (size_t)h->lmax;
         if ((s = need((lmax + lmax * cap) * 4)) != AMR_OK) return s;
         int32_t *o = (int32_t *)buf;
         for (size_t L = 0; L < lmax; L++) o[L] = h->nids[L];
-        HIP_TRY(hipMemcpyAsync(o + lmax, c.ids, lmax * cap * 4, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, o + lmax, c.ids, lmax * cap * 4);
     }
     case AMR_FIELD_GAP: {
         if ((s = need((1 + cap) * 4)) != AMR_OK) return s;
         int32_t *o = (int32_t *)buf;
         o[0] = h->gtop;
-        if (h->gtop > 0) HIP_TRY(hipMemcpyAsync(o + 1, c.gap, (size_t)h->gtop * 4, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, o + 1, c.gap, (size_t)h->gtop * 4);
     }
     case AMR_FIELD_COUNTS: {
         if ((s = need((size_t)h->lmax * 4)) != AMR_OK) return s;
@@ -877,13 +886,11 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
     case AMR_FIELD_MASS_MOM: {
         if ((s = need(32)) != AMR_OK) return s;
         launch_mass(c, lp);
-        HIP_TRY(hipMemcpyAsync(buf, c.ctr->mass, 32, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, buf, c.ctr->mass, 32);
     }
     case AMR_FIELD_CRIT: {
         if ((s = need(cap * 8)) != AMR_OK) return s;
-        HIP_TRY(hipMemcpyAsync(buf, c.crit, cap * 8, hipMemcpyDeviceToHost, st));
-        return sync_checked(h);
+        return copy_out(h, buf, c.crit, cap * 8);
     }
     case AMR_FIELD_KERNEL_STATS: {
         if ((s = need(sizeof(h->kstats))) != AMR_OK) return s;
@@ -900,8 +907,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         double *dev = (double *)c.staging;  // >= 1 MB
         launch_force_sum(c, dev);
         std::vector<double> tot((size_t)h->lmax * 3);
-        HIP_TRY(hipMemcpyAsync(tot.data(), dev, tot.size() * 8, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
+        if ((s = copy_out(h, tot.data(), dev, tot.size() * 8)) != AMR_OK) return s;
         double *out = (double *)buf;
         for (int L = 0; L < h->lmax; L++) {
             for (int a = 0; a < 3; a++) out[L * 4 + a] = tot[(size_t)L * 3 + a];

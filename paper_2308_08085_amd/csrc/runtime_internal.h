@@ -3,6 +3,7 @@
 // its arena layout, error reporting.
 #pragma once
 
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -48,6 +49,9 @@ struct amr_handle {
     bool sync_velocity = true;              // criterion velocities from the synchronisation's averaging
     bool skip_parents = false;              // sweeps leave out refined blocks without N_SKIP children
     int batches = 0;                        // batches this handle is a member of
+    char *pin = nullptr;                    // pinned memory for small transfers (kPinBytes), may be null
+    uint64_t read_total = 0;                // bytes transferred to the host so far
+    int reads = 0;                          // transfers made without `pin`
     double tau[kMaxLevels];
     BCParams bc;
     std::vector<uint8_t> solid;
@@ -71,6 +75,29 @@ namespace amr {
 
 // relaxation and rescaling of every level, with the current buffer parities
 LevelParams level_params(const amr_handle *h);
+
+// ---- device to host (transfer.hip) ----
+constexpr size_t kPinBytes = size_t(64) << 10, kSlotBytes = size_t(4) << 20, kHeadBytes = 64;
+
+// where a filled chunk goes: `bytes` from `offset` in the chunk to host memory
+struct Piece {
+    char *dst;
+    size_t offset, bytes;
+};
+
+void transfer_add_user(amr_handle *h);   // with the handle's creation
+void transfer_drop_user(amr_handle *h);  // with its end
+size_t transfer_chunk(const amr_handle *h, uint64_t total);  // chunk size for a transfer of `total` bytes
+// n chunks of at most transfer_chunk() bytes: fill(i, to) enqueues what writes
+// chunk i to `to` (pinned host or device memory) on the handle's stream, and
+// piece(i, head) says where it goes, given the chunk's first kHeadBytes.
+// Without pinned memory: `plain`, if given, enqueues the whole transfer, else
+// the chunks go through the staging area.  Synchronises the stream.
+amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::function<void(int, char *)> &fill,
+                        const std::function<Piece(int, const int64_t *)> &piece,
+                        const std::function<hipError_t()> &plain = nullptr);
+// a range of device memory to pageable host memory; synchronises the stream
+amr_status copy_out(amr_handle *h, void *dst, const void *dev, size_t bytes);
 
 
 }  // namespace amr
