@@ -330,14 +330,15 @@ amr_status amr_mass_mom_static(amr_t *h, double *out_dev);
  * number of lbm_step calls on it alone.  Members of equal lattice and storage
  * advance each level sweep in one persistent launch (collide-stream, ghost
  * interpolation, interface averaging); the work lists are rebuilt on the
- * device from the members' own lists at the start of every coarse step, so a
+ * device from the members' own lists at the start of every batch step, so a
  * captured coarse step stays valid while members adapt between batch steps. */
 typedef struct amr_batch amr_batch_t;
 
 typedef struct {
     int32_t threads;    /* threads per workgroup of the collide-stream launches: 64, 128 or 256
                            (3-D: 1, 2 or 4 blocks per workgroup; 2-D: 4, 8 or 16) */
-    int32_t wg_per_cu;  /* persistent grid = wg_per_cu x compute units, 1 .. 64 */
+    int32_t wg_per_cu;  /* persistent grid = wg_per_cu x compute units, 1 .. 64 (of these, as many
+                           as the kernel's registers let run at a time) */
     int32_t schedule;   /* 0: groups of different lattice/storage one after another;
                            1: each group on its own concurrent branch of the step */
 } amr_batch_tuning;

@@ -2,7 +2,7 @@
 // are grouped by (lattice, storage); each group advances every level sweep of
 // all its members in one persistent launch (collide-stream, ghost
 // interpolation, interface averaging), with the work items rebuilt on the
-// device from each member's own lists at the start of every coarse step, so a
+// device from each member's own lists at the start of every call, so a
 // captured coarse step stays valid while members adapt.  An autotuner picks
 // the workgroup shape, the persistent grid size and whether the groups run as
 // concurrent branches of the graph.
@@ -18,6 +18,7 @@ namespace {
 struct Group {
     int q = 0, storage = 0, lmax = 0, cap_max = 0;
     bool solid = false;        // some member has solid root blocks
+    bool cubic = false;        // some member interpolates with the cubic scheme
     std::vector<int> members;  // indices into amr_batch::sims, in batch order
     std::vector<bool> force_on;  // each member's momentum-exchange switch in the uploaded descriptors
     SimDesc *desc = nullptr;   // device [members]
@@ -45,6 +46,7 @@ size_t plan_groups(amr_t *const *sims, int n, std::vector<Group> &groups) {
         }
         g->members.push_back(i);
         g->solid = g->solid || h->c.n_solid > 0;
+        g->cubic = g->cubic || h->c.m.interp == AMR_INTERP_CUBIC;
         g->lmax = std::max(g->lmax, sim_lmax(h));
         g->cap_max = std::max(g->cap_max, h->c.m.cap);
         g->stride += h->c.m.cap;
@@ -125,20 +127,18 @@ SimDesc make_desc(const amr_t *h) {
     return d;
 }
 
-int collide_grid(const amr_batch *b) { return std::max(1, b->tune.wg_per_cu * b->n_cu); }
-
 // one coarse step of one group: step(L) = ghost fill of L+1, collide-stream
 // of L, step(L+1) twice, interface averaging of L+1 into L
 void group_level(const amr_batch *b, const Group &g, hipStream_t st, int L, int *par) {
     if (L >= g.lmax) return;
-    const int grid = collide_grid(b);
+    const BatchShape shape{b->n_cu, b->tune.wg_per_cu, b->tune.threads, g.cubic};
     const bool finer = L + 1 < g.lmax;
     const int64_t s = g.stride;
     if (finer)
         launch_interp_batch(st, g.q, g.storage, g.desc, g.items + (3 * L + 1) * s, g.counts + 3 * L + 1, L, par[L],
-                            par[L + 1], grid);
+                            par[L + 1], shape);
     launch_collide_batch(st, g.q, g.storage, g.desc, g.items + (3 * L) * s, g.counts + 3 * L, L, par[L],
-                         b->tune.threads, grid);
+                         shape);
     par[L] ^= 1;
     if (g.solid)  // momentum exchange with solid blocks, from the buffer just written
         launch_exchange_batch(st, g.q, g.storage, g.desc, g.items + (3 * L + 2) * s, g.counts + 3 * L + 2, par[L],
@@ -147,12 +147,11 @@ void group_level(const amr_batch *b, const Group &g, hipStream_t st, int L, int 
         group_level(b, g, st, L + 1, par);
         group_level(b, g, st, L + 1, par);
         launch_average_batch(st, g.q, g.storage, g.desc, g.items + (3 * L + 1) * s, g.counts + 3 * L + 1, L, par[L],
-                             par[L + 1], grid);
+                             par[L + 1], shape);
     }
 }
 
 void group_step(const amr_batch *b, const Group &g, hipStream_t st, int par0) {
-    launch_batch_items(st, g.desc, (int)g.members.size(), g.lmax, g.cap_max, g.items, g.stride, g.counts);
     int par[kMaxLevels] = {0};
     par[0] = par0;
     group_level(b, g, st, 0, par);
@@ -216,6 +215,12 @@ amr_status refresh_descs(amr_batch *b) {
 }
 
 amr_status run_steps(amr_batch *b, int32_t n, bool use_graph) {
+    // members adapt between calls only, so their work lists serve every step
+    // of this one (rebuilt in each captured step they cost 20 us per group of
+    // 16 simulations)
+    if (n > 0)
+        for (auto &g : b->groups)
+            launch_batch_items(b->stream, g.desc, (int)g.members.size(), g.lmax, g.cap_max, g.items, g.stride, g.counts);
     for (int32_t k = 0; k < n; k++) {
         if (use_graph) {
             if (!b->graph_ok) {

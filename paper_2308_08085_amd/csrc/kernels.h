@@ -124,12 +124,17 @@ void launch_force_reset(const Ctx &c);
 
 // ---- batched solver launches: one persistent launch per level over every
 // simulation of a batch (items = simulation << 24 | block, counts on the device)
+struct BatchShape {
+    int n_cu, wg_per_cu;  // persistent grid: up to wg_per_cu workgroups on each of n_cu compute units
+    int threads;          // of a collide-stream workgroup
+    bool cubic;           // some member interpolates with the cubic scheme
+};
 void launch_collide_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                          const int32_t *count, int L, int par, int nt, int grid);
+                          const int32_t *count, int L, int par, const BatchShape &s);
 void launch_interp_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                         const int32_t *count, int L, int par0, int par1, int grid);
+                         const int32_t *count, int L, int par0, int par1, const BatchShape &s);
 void launch_average_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                          const int32_t *count, int L, int par0, int par1, int grid);
+                          const int32_t *count, int L, int par0, int par1, const BatchShape &s);
 // items[(3 L + kind) * stride + ...], counts[3 L + kind]: kind 0 launch order, 1 interface parents,
 // 2 leaf blocks next to a solid block
 void launch_batch_items(hipStream_t stream, const SimDesc *sims, int nsims, int lmax, int cap_max, uint32_t *items,

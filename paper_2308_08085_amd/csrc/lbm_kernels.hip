@@ -1086,7 +1086,9 @@ __global__ __launch_bounds__(256) void k_interp_collide(const int32_t *__restric
 
 // Batched ghost fill of level L+1 from level L (interface parents of every
 // simulation), persistent teams; par0/par1 = buffers of levels L, L+1.
-template <int Q, int S>
+// CUB: 0 every member linear, 2 the member's choice (131 instead of 70 VGPRs for
+// D3Q19, so groups without a cubic member do not carry it).
+template <int Q, int S, int CUB>
 __global__ __launch_bounds__(256) void k_interp_batch(const SimDesc *__restrict__ sims,
                                                       const uint32_t *__restrict__ items,
                                                       const int32_t *__restrict__ count, int L, int par0, int par1) {
@@ -1107,7 +1109,7 @@ __global__ __launch_bounds__(256) void k_interp_batch(const SimDesc *__restrict_
         P = __builtin_amdgcn_readfirstlane(P);
         CSimDesc *cs = const_view(sims) + sim;
         const DevMesh m = load_mesh(cs);
-        interp_parent<Q, S, 2>(
+        interp_parent<Q, S, CUB>(
             m, P, [&](int) { return (const T *)cs->f[par0]; }, [&](int) { return (T *)cs->f[par1]; },
             [&](int) { return R(cs->lp.r_cf[L]); }, 0, sm[team], opaque_tid() % kTeamThreads<Lt>);
         team_sync<Lt>();
@@ -1415,16 +1417,17 @@ __device__ inline int item_count(const SimDesc &d, int L, int kind) {
 static __global__ void k_batch_items(const SimDesc *__restrict__ sims, int nsims, uint32_t *__restrict__ items,
                               int64_t stride, int32_t *__restrict__ counts) {
     const int s = blockIdx.y, L = blockIdx.z / 3, kind = blockIdx.z % 3;
-    __shared__ int s_off, s_n;
-    if (threadIdx.x == 0) {
-        int off = 0;
-        for (int t = 0; t < s; t++) off += item_count(sims[t], L, kind);
-        const int n = item_count(sims[s], L, kind);
-        s_off = off;
-        s_n = n;
-        if (s == nsims - 1 && blockIdx.x == 0) counts[blockIdx.z] = off + n;
-    }
+    __shared__ int s_part[4], s_n;
+    // items of the simulations before this one: their counts loaded side by side
+    int off = 0;
+    for (int t = threadIdx.x; t < s; t += blockDim.x) off += item_count(sims[t], L, kind);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
+    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = off;
+    if (threadIdx.x == 0) s_n = item_count(sims[s], L, kind);
     __syncthreads();
+    const int s_off = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    if (threadIdx.x == 0 && s == nsims - 1 && blockIdx.x == 0) counts[blockIdx.z] = s_off + s_n;
     const SimDesc &sd = sims[s];
     const int32_t *src = (kind == 0 ? sd.order : (kind == 1 ? sd.iface : sd.solid)) + (int64_t)L * sd.m.cap;
     uint32_t *dst = items + (int64_t)blockIdx.z * stride + s_off;
@@ -2013,11 +2016,11 @@ struct Launch {
     static void exchange_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                                int par, int grid);
     static void collide_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                              int L, int par, int nt, int grid);
+                              int L, int par, const BatchShape &s);
     static void interp_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                             int L, int par0, int par1, int grid);
+                             int L, int par0, int par1, const BatchShape &s);
     static void average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                              int L, int par0, int par1, int grid);
+                              int L, int par0, int par1, const BatchShape &s);
     static void refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
     static void average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
                         double *U);
@@ -2124,26 +2127,49 @@ void Launch<Q, S>::exchange_batch(hipStream_t stream, const SimDesc *sims, const
     k_exchange_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, par);
 }
 
+// Workgroups of a persistent launch: wg_per_cu per compute unit, but no more
+// than fit at a time.  The workgroups share the items evenly, so those that
+// start when others have ended would double the launch: D3Q19 sweeps of 28,000
+// blocks with 8 asked and 6 resident workgroups per unit took 35 us, now 25 us.
+template <typename K>
+static int resident(K kernel, int threads) {
+    int fit = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, kernel, threads, 0) != hipSuccess || fit < 1) fit = 64;
+    return fit;
+}
+static int persistent_grid(const BatchShape &s, int fit) { return std::max(1, s.n_cu * std::min(s.wg_per_cu, fit)); }
+
+template <int Q, int S, int NT>
+static void collide_batch_nt(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
+                             int L, int par, const BatchShape &s) {
+    static const int fit = resident(k_collide_stream_batch<Q, S, NT>, NT);
+    const int grid = persistent_grid(s, fit);
+    k_collide_stream_batch<Q, S, NT><<<grid, NT, 0, stream>>>(sims, items, count, L, par);
+}
+
 template <int Q, int S>
 void Launch<Q, S>::collide_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                                 int L, int par, int nt, int grid) {
-    if (nt == 64)
-        k_collide_stream_batch<Q, S, 64><<<grid, 64, 0, stream>>>(sims, items, count, L, par);
-    else if (nt == 128)
-        k_collide_stream_batch<Q, S, 128><<<grid, 128, 0, stream>>>(sims, items, count, L, par);
-    else
-        k_collide_stream_batch<Q, S, 256><<<grid, 256, 0, stream>>>(sims, items, count, L, par);
+                                 int L, int par, const BatchShape &s) {
+    if (s.threads == 64) collide_batch_nt<Q, S, 64>(stream, sims, items, count, L, par, s);
+    else if (s.threads == 128) collide_batch_nt<Q, S, 128>(stream, sims, items, count, L, par, s);
+    else collide_batch_nt<Q, S, 256>(stream, sims, items, count, L, par, s);
 }
 
 template <int Q, int S>
 void Launch<Q, S>::interp_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                                int L, int par0, int par1, int grid) {
-    k_interp_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
+                                int L, int par0, int par1, const BatchShape &s) {
+    static const int fit[2] = {resident(k_interp_batch<Q, S, 0>, 256),
+                               resident(k_interp_batch<Q, S, 2>, 256)};
+    const int grid = persistent_grid(s, fit[s.cubic ? 1 : 0]);
+    if (s.cubic) k_interp_batch<Q, S, 2><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
+    else k_interp_batch<Q, S, 0><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
 }
 
 template <int Q, int S>
 void Launch<Q, S>::average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
-                                 int L, int par0, int par1, int grid) {
+                                 int L, int par0, int par1, const BatchShape &s) {
+    static const int fit = resident(k_average_batch<Q, S>, 256);
+    const int grid = persistent_grid(s, fit);
     k_average_batch<Q, S><<<grid, 256, 0, stream>>>(sims, items, count, L, par0, par1);
 }
 
@@ -2256,18 +2282,18 @@ void launch_exchange_batch(hipStream_t stream, int q, int storage, const SimDesc
 }
 
 void launch_collide_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                          const int32_t *count, int L, int par, int nt, int grid) {
-    dispatch(q, storage, [&](auto l) { l.collide_batch(stream, sims, items, count, L, par, nt, grid); });
+                          const int32_t *count, int L, int par, const BatchShape &s) {
+    dispatch(q, storage, [&](auto l) { l.collide_batch(stream, sims, items, count, L, par, s); });
 }
 
 void launch_interp_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                         const int32_t *count, int L, int par0, int par1, int grid) {
-    dispatch(q, storage, [&](auto l) { l.interp_batch(stream, sims, items, count, L, par0, par1, grid); });
+                         const int32_t *count, int L, int par0, int par1, const BatchShape &s) {
+    dispatch(q, storage, [&](auto l) { l.interp_batch(stream, sims, items, count, L, par0, par1, s); });
 }
 
 void launch_average_batch(hipStream_t stream, int q, int storage, const SimDesc *sims, const uint32_t *items,
-                          const int32_t *count, int L, int par0, int par1, int grid) {
-    dispatch(q, storage, [&](auto l) { l.average_batch(stream, sims, items, count, L, par0, par1, grid); });
+                          const int32_t *count, int L, int par0, int par1, const BatchShape &s) {
+    dispatch(q, storage, [&](auto l) { l.average_batch(stream, sims, items, count, L, par0, par1, s); });
 }
 
 void launch_batch_items(hipStream_t stream, const SimDesc *sims, int nsims, int lmax, int cap_max, uint32_t *items,
