@@ -193,7 +193,8 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats);
  * AMR_ERR_UNSTABLE if it is not finite.
  * Errors: AMR_ERR_ARG (n < 0), AMR_ERR_UNSTABLE, AMR_ERR_DEVICE. */
 #define AMR_CHECK_FINITE 1u
-#define AMR_USE_GRAPH 2u   /* replay one captured coarse step (HIP graph) instead of eager launches */
+#define AMR_USE_GRAPH 2u   /* accepted and without effect: plain launches run ahead of the GPU and were
+                              measured faster than replaying a captured coarse step (HIP graph) */
 #define AMR_PROFILE 4u     /* time every solver launch with HIP events on the stream (eager; see
                               AMR_FIELD_KERNEL_STATS); synchronises the stream */
 amr_status lbm_step(amr_t *h, int32_t n_coarse_steps, uint32_t flags);
@@ -237,15 +238,13 @@ amr_status lbm_step(amr_t *h, int32_t n_coarse_steps, uint32_t flags);
  *   AMR_FIELD_FORCE_ON     GET/SET int32[1]: 1 (the default) = accumulate the momentum
  *                          exchange in every lbm_step and batch step, 0 = skip its launches
  *                          and sweep counts (for runs that sample the force only part of the
- *                          time); SET accepts 0 or 1 (else AMR_ERR_ARG) and re-captures the
- *                          step graphs when the value changes
+ *                          time); SET accepts 0 or 1 (else AMR_ERR_ARG)
  *   AMR_FIELD_STREAM_BYTES GET/SET int64[1]: store policy of the collide-stream sweeps: a
  *                          level whose sweep writes more than this many bytes is written with
  *                          non-temporal stores (its output is read again only by the next sweep,
  *                          after the whole level has passed through the caches); default
  *                          128 MiB (half the 256 MB Infinity Cache), 0 = every level, any
- *                          value >= 0 (else AMR_ERR_ARG).  Results do not depend on it; SET
- *                          re-captures the step graphs when the value changes
+ *                          value >= 0 (else AMR_ERR_ARG).  Results do not depend on it
  *   AMR_FIELD_SYNC_VELOCITY GET/SET int32[1]: 1 (the default) = the averaging of the
  *                          pre-adaptation synchronisation also computes the
  *                          vorticity criterion's velocities of the children it reads (those
@@ -262,9 +261,8 @@ amr_status lbm_step(amr_t *h, int32_t n_coarse_steps, uint32_t flags);
  *                          averages them again, so leaf cells, output fields, forces and tags
  *                          are unchanged bit for bit; the skipped blocks' own cells (and cells of
  *                          neighbouring parents away from any coarse leaf) hold stale values
- *                          until then.  SET 1 needs linear interpolation (else AMR_ERR_ARG); SET
- *                          re-captures the step graphs when the value changes.  Batch steps
- *                          always advance every block.
+ *                          until then.  SET 1 needs linear interpolation (else AMR_ERR_ARG).  Batch
+ *                          steps always advance every block.
  *   AMR_FIELD_KERNEL_STATS GET double[3][4]: for the collide-stream, interpolation and averaging
  *                          kernels: launches, summed event time (ms), blocks processed, and the
  *                          distribution bytes those blocks must move, accumulated over lbm_step
@@ -298,7 +296,6 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
  * rescaling stay those of BGK (Secs. "Linear Interpolation", "Averaging"), whose
  * derivation assumes BGK.  Batches (amr_batch_create) accept BGK members only.
  * kind: enum amr_collision; s_high in (0, 2), ignored for AMR_COLLIDE_BGK.
- * Captured step graphs are re-captured.
  * Errors: AMR_ERR_ARG (unknown kind, lattice other than D3Q27, FP64 storage
  * with AMR_COLLIDE_MRT_MFMA, s_high out of range, handle in a batch). */
 enum amr_collision { AMR_COLLIDE_BGK = 0, AMR_COLLIDE_MRT = 1, AMR_COLLIDE_MRT_MFMA = 2 };
@@ -330,8 +327,8 @@ amr_status amr_mass_mom_static(amr_t *h, double *out_dev);
  * number of lbm_step calls on it alone.  Members of equal lattice and storage
  * advance each level sweep in one persistent launch (collide-stream, ghost
  * interpolation, interface averaging); the work lists are rebuilt on the
- * device from the members' own lists at the start of every batch step, so a
- * captured coarse step stays valid while members adapt between batch steps. */
+ * device from the members' own lists at the start of every batch step, so
+ * members may adapt between batch steps. */
 typedef struct amr_batch amr_batch_t;
 
 typedef struct {
@@ -340,7 +337,7 @@ typedef struct {
     int32_t wg_per_cu;  /* persistent grid = wg_per_cu x compute units, 1 .. 64 (of these, as many
                            as the kernel's registers let run at a time) */
     int32_t schedule;   /* 0: groups of different lattice/storage one after another;
-                           1: each group on its own concurrent branch of the step */
+                           1: each group on its own stream, concurrent within the step */
 } amr_batch_tuning;
 
 /* Device arena a batch of `n` simulations needs (descriptors and work lists).
@@ -364,12 +361,12 @@ amr_status amr_batch_create(amr_t *const *sims, int32_t n, void *dev_arena, uint
  * member named in amr_last_error), AMR_ERR_DEVICE. */
 amr_status amr_batch_step(amr_batch_t *b, int32_t n_coarse_steps, uint32_t flags);
 
-/* Launch shape of the batch (drops its captured graphs).  Errors: AMR_ERR_ARG. */
+/* Launch shape of the batch.  Errors: AMR_ERR_ARG. */
 amr_status amr_batch_set_tuning(amr_batch_t *b, const amr_batch_tuning *t);
 amr_status amr_batch_get_tuning(amr_batch_t *b, amr_batch_tuning *t);
 
 /* Time every launch shape (threads x wg_per_cu x schedule) over `trial_steps`
- * graph-replayed coarse steps each, keep the fastest and return it with its
+ * coarse steps each, keep the fastest and return it with its
  * time per coarse step.  The members advance (2 + trial_steps) coarse steps
  * per shape tried; results do not depend on the shape.
  * Errors: AMR_ERR_ARG, AMR_ERR_STATE, AMR_ERR_DEVICE. */

@@ -2,10 +2,9 @@
 // are grouped by (lattice, storage); each group advances every level sweep of
 // all its members in one persistent launch (collide-stream, ghost
 // interpolation, interface averaging), with the work items rebuilt on the
-// device from each member's own lists at the start of every call, so a
-// captured coarse step stays valid while members adapt.  An autotuner picks
-// the workgroup shape, the persistent grid size and whether the groups run as
-// concurrent branches of the graph.
+// device from each member's own lists at the start of every call.  An autotuner
+// picks the workgroup shape, the persistent grid size and whether the groups
+// run concurrently.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -76,8 +75,6 @@ struct amr_batch {
     int par0 = 0;                   // level-0 buffer parity shared by every member
     int n_cu = 256;
     amr_batch_tuning tune;
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    bool graph_ok = false;
 };
 
 namespace {
@@ -157,7 +154,7 @@ void group_step(const amr_batch *b, const Group &g, hipStream_t st, int par0) {
     group_level(b, g, st, 0, par);
 }
 
-// one coarse step of the batch on b->stream (eager or under capture)
+// one coarse step of the batch on b->stream
 amr_status batch_coarse_step(amr_batch *b, int par0) {
     const bool concurrent = b->tune.schedule == 1 && b->groups.size() > 1;
     if (!concurrent) {
@@ -175,15 +172,6 @@ amr_status batch_coarse_step(amr_batch *b, int par0) {
     return AMR_OK;
 }
 
-void drop_batch_graphs(amr_batch *b) {
-    for (int i = 0; i < 2; i++)
-        if (b->gexec[i]) {
-            hipGraphExecDestroy(b->gexec[i]);
-            b->gexec[i] = nullptr;
-        }
-    b->graph_ok = false;
-}
-
 void set_member_parity(amr_batch *b) {
     for (auto *h : b->sims) h->par[0] = b->par0;
 }
@@ -196,7 +184,7 @@ void count_member_sweeps(amr_batch *b, int32_t n) {
 
 // A member whose momentum-exchange switch changed since its descriptor was
 // uploaded gets its group's descriptors again (the work lists are built from
-// them on the device, so captured steps stay valid).
+// them on the device).
 amr_status refresh_descs(amr_batch *b) {
     for (auto &g : b->groups) {
         bool stale = false;
@@ -214,37 +202,19 @@ amr_status refresh_descs(amr_batch *b) {
     return AMR_OK;
 }
 
-amr_status run_steps(amr_batch *b, int32_t n, bool use_graph) {
+// Plain launches, with or without AMR_USE_GRAPH: the host stays ahead of the GPU
+// (2.5 us per launch), and a captured coarse step replayed no faster (32 mixed
+// cavities: 593 us against 588 with schedule 0, 495 against 441 with schedule 1).
+amr_status run_steps(amr_batch *b, int32_t n) {
     // members adapt between calls only, so their work lists serve every step
-    // of this one (rebuilt in each captured step they cost 20 us per group of
-    // 16 simulations)
+    // of this one (rebuilt in each step they cost 20 us per group of 16
+    // simulations)
     if (n > 0)
         for (auto &g : b->groups)
             launch_batch_items(b->stream, g.desc, (int)g.members.size(), g.lmax, g.cap_max, g.items, g.stride, g.counts);
     for (int32_t k = 0; k < n; k++) {
-        if (use_graph) {
-            if (!b->graph_ok) {
-                for (int p = 0; p < 2; p++) {
-                    hipGraph_t g;
-                    HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-                    amr_status s = batch_coarse_step(b, p);
-                    hipError_t e = hipStreamEndCapture(b->stream, &g);
-                    if (s != AMR_OK) return s;
-                    if (e != hipSuccess) return fail(AMR_ERR_DEVICE, "graph capture: %s", hipGetErrorString(e));
-                    e = hipGraphInstantiate(&b->gexec[p], g, nullptr, nullptr, 0);
-                    hipGraphDestroy(g);
-                    if (e != hipSuccess) {
-                        drop_batch_graphs(b);
-                        return fail(AMR_ERR_DEVICE, "graph instantiate: %s", hipGetErrorString(e));
-                    }
-                }
-                b->graph_ok = true;
-            }
-            HIP_TRY(hipGraphLaunch(b->gexec[b->par0], b->stream));
-        } else {
-            amr_status s = batch_coarse_step(b, b->par0);
-            if (s != AMR_OK) return s;
-        }
+        amr_status s = batch_coarse_step(b, b->par0);
+        if (s != AMR_OK) return s;
         b->par0 ^= 1;
     }
     set_member_parity(b);
@@ -340,7 +310,7 @@ amr_status amr_batch_step(amr_batch_t *b, int32_t n, uint32_t flags) {
         if (h->par[0] != b->par0) return fail(AMR_ERR_STATE, "a member was stepped outside the batch");
     amr_status s = refresh_descs(b);
     if (s != AMR_OK) return s;
-    s = run_steps(b, n, (flags & AMR_USE_GRAPH) != 0);
+    s = run_steps(b, n);
     if (s != AMR_OK) return s;
     if (flags & AMR_CHECK_FINITE) {
         int bad = -1;
@@ -363,7 +333,6 @@ amr_status amr_batch_set_tuning(amr_batch_t *b, const amr_batch_tuning *t) {
     if (s != AMR_OK) return s;
     HIP_TRY(hipStreamSynchronize(b->stream));
     b->tune = *t;
-    drop_batch_graphs(b);
     return AMR_OK;
 }
 
@@ -396,11 +365,11 @@ amr_status amr_batch_autotune(amr_batch_t *b, int32_t trial_steps, amr_batch_tun
                 c.schedule = sc;
                 s = amr_batch_set_tuning(b, &c);
                 if (s != AMR_OK) break;
-                // the first step captures the graphs; time the replays only
-                s = run_steps(b, 2, true);
+                // two untimed steps first
+                s = run_steps(b, 2);
                 if (s != AMR_OK) break;
                 if (hipEventRecord(t0, b->stream) != hipSuccess) { s = fail(AMR_ERR_DEVICE, "event record"); break; }
-                s = run_steps(b, trial_steps, true);
+                s = run_steps(b, trial_steps);
                 if (s != AMR_OK) break;
                 float ms = 0.f;
                 if (hipEventRecord(t1, b->stream) != hipSuccess || hipEventSynchronize(t1) != hipSuccess ||
@@ -427,7 +396,6 @@ amr_status amr_batch_autotune(amr_batch_t *b, int32_t trial_steps, amr_batch_tun
 amr_status amr_batch_destroy(amr_batch_t *b) {
     if (!b) return AMR_OK;
     if (b->stream || !b->sims.empty()) hipStreamSynchronize(b->stream);
-    drop_batch_graphs(b);
     for (auto st : b->side) {
         hipStreamSynchronize(st);
         hipStreamDestroy(st);

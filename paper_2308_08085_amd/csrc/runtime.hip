@@ -1,6 +1,6 @@
 // runtime.hip -- host runtime behind the C ABI of include/amr_lbm.h: arena
-// carve-up, the recursive sub-cycled schedule (optionally replayed from a HIP
-// graph), tagging and adaptation sequencing, field access.
+// carve-up, the recursive sub-cycled schedule, tagging and adaptation
+// sequencing, field access.
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
@@ -280,15 +280,6 @@ amr_status refresh_counts(amr_handle *h) {
     return AMR_OK;
 }
 
-void drop_graphs(amr_handle *h) {
-    for (int i = 0; i < 2; i++)
-        if (h->gexec[i]) {
-            hipGraphExecDestroy(h->gexec[i]);
-            h->gexec[i] = nullptr;
-        }
-    h->graph_ok = false;
-}
-
 amr_status sync_checked(amr_handle *h) {
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(h->c.stream));
@@ -467,7 +458,6 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
 amr_status amr_destroy(amr_t *h) {
     if (!h) return AMR_OK;
     hipStreamSynchronize(h->c.stream);
-    drop_graphs(h);
     for (auto &t : h->timed) {
         hipEventDestroy(t.a);
         hipEventDestroy(t.b);
@@ -484,34 +474,13 @@ amr_status lbm_step(amr_t *h, int32_t n, uint32_t flags) {
     if (!h) return fail(AMR_ERR_ARG, "handle is NULL");
     if (n < 0) return fail(AMR_ERR_ARG, "n_coarse_steps must be >= 0");
     h->profiling = (flags & AMR_PROFILE) != 0;
-    const bool use_graph = (flags & AMR_USE_GRAPH) != 0 && !h->profiling;
-    for (int32_t sidx = 0; sidx < n; sidx++) {
-        if (use_graph) {
-            const int p0 = h->par[0];
-            if (!h->graph_ok) {
-                // capture one coarse step for each parity of level 0; every level
-                // other than 0 returns to its parity at the end of a coarse step
-                for (int k = 0; k < 2; k++) {
-                    hipGraph_t g;
-                    HIP_TRY(hipStreamBeginCapture(h->c.stream, hipStreamCaptureModeThreadLocal));
-                    step_level(h, 0);
-                    HIP_TRY(hipStreamEndCapture(h->c.stream, &g));
-                    hipError_t e = hipGraphInstantiate(&h->gexec[(p0 + k) & 1], g, nullptr, nullptr, 0);
-                    hipGraphDestroy(g);
-                    if (e != hipSuccess) {
-                        drop_graphs(h);
-                        return fail(AMR_ERR_DEVICE, "graph instantiate: %s", hipGetErrorString(e));
-                    }
-                }
-                h->graph_ok = true;
-                // capturing advanced the host-side parities by two steps; level 0 is back
-            }
-            HIP_TRY(hipGraphLaunch(h->gexec[h->par[0]], h->c.stream));
-            h->par[0] ^= 1;
-        } else {
-            step_level(h, 0);
-        }
-    }
+    // With or without AMR_USE_GRAPH: plain launches.  They cost the host 2.5 us
+    // each, less than any of the step's kernels lasts, so the GPU never waits for
+    // them; replaying a captured coarse step cost 11 to 19 us of host time that
+    // the GPU did wait for (single level of 256 D2Q9 blocks 16.0 against 5.7 us a
+    // step, D2Q9 cylinder on three levels 66.1 against 61.9 us, D3Q19 cavity 207.1
+    // against 202.4 us), and every adaptation another capture (0.25 ms).
+    for (int32_t sidx = 0; sidx < n; sidx++) step_level(h, 0);
     HIP_TRY(hipGetLastError());
     if (h->force_on)
         for (int L = 0; L < h->lmax; L++) h->force_sweeps[L] += (double)n * (double)(1 << L);
@@ -652,7 +621,6 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats) {
     if (s != AMR_OK) return s;
     s = refresh_counts(h);
     if (s != AMR_OK) return s;
-    drop_graphs(h);
     if (stats) {
         stats->n_refine = n_ref;
         stats->n_coarsen = dc.n_coa;
@@ -667,10 +635,7 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats) {
 amr_status amr_set_collision(amr_t *h, int32_t kind, double s_high) {
     if (!h) return fail(AMR_ERR_ARG, "handle is NULL");
     if (kind == AMR_COLLIDE_BGK) {
-        if (h->c.coll != AMR_COLLIDE_BGK) {
-            h->c.coll = AMR_COLLIDE_BGK;
-            drop_graphs(h);
-        }
+        h->c.coll = AMR_COLLIDE_BGK;
         return AMR_OK;
     }
     if (kind != AMR_COLLIDE_MRT && kind != AMR_COLLIDE_MRT_MFMA)
@@ -680,11 +645,8 @@ amr_status amr_set_collision(amr_t *h, int32_t kind, double s_high) {
         return fail(AMR_ERR_ARG, "AMR_COLLIDE_MRT_MFMA needs a storage with FP32 arithmetic");
     if (!(s_high > 0.0 && s_high < 2.0)) return fail(AMR_ERR_ARG, "s_high must lie in (0, 2), not %g", s_high);
     if (h->batches > 0) return fail(AMR_ERR_ARG, "the handle is in a batch, which advances BGK members only");
-    if (kind != h->c.coll || s_high != h->c.s_high) {
-        h->c.coll = kind;
-        h->c.s_high = s_high;
-        drop_graphs(h);  // captured steps hold the collide kernels and the rate
-    }
+    h->c.coll = kind;
+    h->c.s_high = s_high;
     return AMR_OK;
 }
 
@@ -717,10 +679,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             return AMR_OK;
         }
         if (*v != 0 && *v != 1) return fail(AMR_ERR_ARG, "AMR_FIELD_FORCE_ON takes 0 or 1, not %d", *v);
-        if ((*v == 1) != h->force_on) {
-            h->force_on = *v == 1;
-            drop_graphs(h);  // captured steps hold the exchange launches, or not
-        }
+        h->force_on = *v == 1;
         return AMR_OK;
     }
     if (kind == AMR_FIELD_SYNC_VELOCITY) {
@@ -745,10 +704,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         if (*v == 1 && h->c.m.interp != AMR_INTERP_LINEAR)
             return fail(AMR_ERR_ARG, "AMR_FIELD_SKIP_PARENTS needs linear interpolation (cubic stencils reach "
                                      "into neighbouring parents)");
-        if ((*v == 1) != h->skip_parents) {
-            h->skip_parents = *v == 1;
-            drop_graphs(h);  // captured steps hold the sweep lists' counts
-        }
+        h->skip_parents = *v == 1;
         return AMR_OK;
     }
     if (kind == AMR_FIELD_STREAM_BYTES) {
@@ -759,10 +715,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             return AMR_OK;
         }
         if (*v < 0) return fail(AMR_ERR_ARG, "AMR_FIELD_STREAM_BYTES must be >= 0, not %lld", (long long)*v);
-        if (*v != h->c.stream_bytes) {
-            h->c.stream_bytes = *v;
-            drop_graphs(h);  // captured steps hold the store policy of each launch
-        }
+        h->c.stream_bytes = *v;
         return AMR_OK;
     }
     if (op == AMR_SET && kind == AMR_FIELD_FORCE) {
@@ -800,7 +753,6 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
                 launch_set_rho_u_root(c, (const double *)c.staging, b0, b1);
                 HIP_TRY(hipStreamSynchronize(st));
             }
-            drop_graphs(h);
             return sync_checked(h);
         }
         const int64_t n_out = h->n_out;

@@ -55,9 +55,6 @@ struct amr_handle {
     double tau[kMaxLevels];
     BCParams bc;
     std::vector<uint8_t> solid;
-    // graph of one coarse step, per level-0 parity
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    bool graph_ok = false;
     // AMR_PROFILE: events around each solver launch (kind, start, stop, blocks, bytes)
     bool profiling = false;
     struct Timed { int kind; hipEvent_t a, b; double blocks, bytes; };
