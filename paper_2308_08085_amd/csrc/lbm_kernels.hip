@@ -157,6 +157,16 @@ __device__ __forceinline__ uint64_t row_entry(const InteriorLane &u) {
     return *(const __attribute__((address_space(3))) uint64_t *)(uintptr_t)(ex + ey + ez);
 }
 
+// that region's slot
+template <typename Lt, int P>
+__device__ __forceinline__ int region_slot(const InteriorLane &u) {
+    constexpr int cx = Lt::cx(P), cy = Lt::cy(P), cz = Lt::cz(P);
+    const uint32_t ex = cx < 0 ? u.xm : (cx > 0 ? u.xp : u.x0);
+    const uint32_t ey = cy < 0 ? u.ym : (cy > 0 ? u.yp : 0u);
+    const uint32_t ez = cz < 0 ? u.zm : (cz > 0 ? u.zp : 0u);
+    return (int)(ex + ey + ez - u.x0) / 8 + kCenterSlot<Lt>;
+}
+
 // byte offset of population P from a row-table entry plus the lane's own offset
 template <typename Lt, typename T, int P>
 constexpr int64_t row_offset() {
@@ -233,19 +243,54 @@ __device__ __forceinline__ void put_rows(uint64_t *tab, int32_t w, int lane, con
     }
 }
 
+// The regions whose links are walls (domain faces, solid blocks) and coarser
+// neighbours, as bits in region-slot order: of a wave's block, or of any of the
+// four blocks of a 2-D wave.  They are the same for the whole wave, so a
+// direction none of whose regions is among them costs one scalar test.
+struct LinkMask {
+    uint32_t wall, skip;
+};
+
+// from the descriptor words of the wave's blocks (lane: of the block)
+template <typename Lt>
+__device__ __forceinline__ LinkMask wave_links(int32_t w, int lane) {
+    const bool link = lane < Desc<Lt::D>::kLinks;
+    uint64_t wall = __ballot(link && w < 0 && w != kNSkip), skip = __ballot(link && w == kNSkip);
+    if constexpr (Lt::D == 2) {
+        wall |= wall >> 32;
+        wall = (wall | wall >> 16) & 0x1ff;
+        skip |= skip >> 32;
+        skip = (skip | skip >> 16) & 0x1ff;
+    }
+    return {(uint32_t)wall, (uint32_t)skip};
+}
+
+// regions outside the block that population P of some cell streams from
+template <typename Lt, int P>
+constexpr uint32_t source_regions() {
+    uint32_t m = 0;
+    for (int k = 1; k < 8; k++) {
+        const int rx = k & 1 ? -Lt::cx(P) : 0, ry = k & 2 ? -Lt::cy(P) : 0, rz = k & 4 ? -Lt::cz(P) : 0;
+        if (rx || ry || rz) m |= 1u << (offset_slot(rx, ry, rz) - (Lt::D == 2 ? 9 : 0));
+    }
+    return m;
+}
+
 // Addresses of the populations of one cell of a block with any links.
 template <typename T>
 struct CellRows {
     InteriorLane u;
+    LinkMask any;    // over the wave
     uint64_t own;    // the cell's own slot of population 0
     uint64_t halo;   // the block's halo record
     uint64_t below;  // bits of the cells below the lane's cell
 };
 
 template <typename Lt, typename T>
-__device__ __forceinline__ CellRows<T> cell_rows(const uint64_t *tab, int B, int h, int l, const T *base,
-                                                 const DevMesh &m) {
+__device__ __forceinline__ CellRows<T> cell_rows(const uint64_t *tab, LinkMask any, int B, int h, int l,
+                                                 const T *base, const DevMesh &m) {
     CellRows<T> r;
+    r.any = any;
     r.u = interior_lane<T, Lt>(tab, l & 3, (l >> 2) & 3, l >> 4);
     r.own = (uint64_t)(uintptr_t)(base + (int64_t)B * (Lt::Q * Lt::MB)) + r.u.own;
     r.halo = (uint64_t)(uintptr_t)(base + (m.halo_base + (int64_t)h * m.nh));
@@ -263,18 +308,22 @@ __device__ __forceinline__ uint32_t halo_entry(uint64_t below) {
 }
 
 // address of population P: its source's slot on the same level, the halo
-// record (HALO: the block has a coarser neighbour), or the cell's own opposite slot
+// record (HALO: some source lies under a coarser neighbour), or the cell's own
+// opposite slot
 template <typename Lt, typename T, int P, bool HALO>
 __device__ __forceinline__ uint64_t slot_address(const CellRows<T> &r) {
-    if constexpr (P == 0) return r.own;
-    const uint64_t e = row_entry<Lt, P>(r.u);
-    const uint64_t in = e + r.u.own + row_offset<Lt, T, P>();
-    uint64_t a = (int64_t)e >= 0 ? in : r.own + (uint64_t)Lt::opp(P) * (Lt::MB * sizeof(T));
-    if constexpr (HALO) {
-        const uint64_t ha = r.halo + halo_entry<Lt, P>(r.below) * (uint32_t)sizeof(T);
-        a = e == (uint64_t)(int64_t)kNSkip ? ha : a;
+    if constexpr (P == 0) {
+        return r.own;
+    } else {
+        const uint64_t e = row_entry<Lt, P>(r.u);
+        uint64_t a = e + r.u.own + row_offset<Lt, T, P>();
+        a = (int64_t)e >= 0 ? a : r.own + (uint64_t)Lt::opp(P) * (Lt::MB * sizeof(T));
+        if constexpr (HALO) {
+            const uint64_t ha = r.halo + halo_entry<Lt, P>(r.below) * (uint32_t)sizeof(T);
+            a = e == (uint64_t)(int64_t)kNSkip ? ha : a;
+        }
+        return a;
     }
-    return a;
 }
 
 // The same for a population known only at run time (uniform over the wave).
@@ -304,7 +353,7 @@ __device__ __forceinline__ uint64_t slot_address_any(const CellRows<T> &r, const
 // gather of a cell of a block with any links: every population's address by
 // selects, so all loads are in flight together
 template <typename Lt, typename ST, bool HALO, typename Out, typename Conv>
-__device__ __forceinline__ void gather_rows_by(const CellRows<typename ST::T> &r, Out *out, Conv conv) {
+__device__ __forceinline__ void gather_rows_by_(const CellRows<typename ST::T> &r, Out *out, Conv conv) {
     using T = typename ST::T;
     static_for<Lt::Q>([&](auto pc) {
         constexpr int P = decltype(pc)::value;
@@ -312,18 +361,20 @@ __device__ __forceinline__ void gather_rows_by(const CellRows<typename ST::T> &r
     });
 }
 
-// The shifted populations of a cell of a block with flags `flag` (RAW: the
-// stored values); `r` from cell_rows.
+template <typename Lt, typename ST, typename Out, typename Conv>
+__device__ __forceinline__ void gather_rows_by(const CellRows<typename ST::T> &r, Out *out, Conv conv) {
+    if (r.any.skip) gather_rows_by_<Lt, ST, true>(r, out, conv);
+    else gather_rows_by_<Lt, ST, false>(r, out, conv);
+}
+
+// The shifted populations of a cell (RAW: the stored values); `r` from cell_rows.
 template <typename Lt, typename ST, bool RAW = false>
-__device__ __forceinline__ void gather_rows_flag(const CellRows<typename ST::T> &r, uint32_t flag, typename ST::R *g) {
+__device__ __forceinline__ void gather_rows(const CellRows<typename ST::T> &r, typename ST::R *g) {
     using R = typename ST::R;
-    const auto conv = [](R v, int p) { return (ST::shift || RAW) ? v : v - R(Lt::w(p)); };
-    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
+    if (!(r.any.wall | r.any.skip))
         gather_interior<Lt, ST, RAW>(r.u, g);
-    else if (flag & BF_NSKIP)
-        gather_rows_by<Lt, ST, true>(r, g, conv);
     else
-        gather_rows_by<Lt, ST, false>(r, g, conv);
+        gather_rows_by<Lt, ST>(r, g, [](R v, int p) { return (ST::shift || RAW) ? v : v - R(Lt::w(p)); });
 }
 
 // BGK relaxation of one cell in the shifted variables: moments, then
@@ -643,13 +694,14 @@ struct CollideSmem {
     FaceTable<Lt, R> face[64 / Lt::MB];
 };
 
-// Keeps a 2-D block's result in FP32 until it is stored.  The conversion to
-// FP16 would otherwise fuse with the last multiply-add on the path for interior
-// blocks and not on the other, and which path a 2-D block takes depends on the
-// three that share its wave.
-template <typename Lt, int S, typename R>
+// Keeps a result in FP32 until it is stored: the conversion to FP16 may fuse
+// with the multiply-add before it and then rounds once instead of twice.  Used
+// where that must not depend on the code around it: for every population of a
+// block with walls or coarser neighbours, and in 2-D for every block, since which
+// path a 2-D block takes depends on the three that share its wave.
+template <int S, typename R>
 __device__ __forceinline__ void pin_result(R &g) {
-    if constexpr (Lt::D == 2 && S == AMR_F16S) asm volatile("" : "+v"(g));
+    if constexpr (S == AMR_F16S) asm volatile("" : "+v"(g));
 }
 
 // Body: cell l of block B (B < 0: none), whole wave; `glane` = the lane's
@@ -671,42 +723,83 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, co
     wave_lds_sync();
     const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
     const int h = desc_get<Lt>(w, De::kHid);
+    const LinkMask any = wave_links<Lt>(w, l);
     if (B < 0) return;
-    FaceTable<Lt, R> &face = sm.face[Lt::D == 3 ? 0 : lane >> 4];
-    const bool wall = __any(flag & BF_BOUNDARY);
-    if (wall) face.put(bc, l);
 
     R g[Q];
     R drho, ux, uy, uz, uu;
     // Interior blocks (every region link a same-level block; 2-D: all four of the wave)
-    if (!__any(flag & (BF_BOUNDARY | BF_NSKIP))) {
+    if (!(any.wall | any.skip)) {
         gather_interior<Lt, ST>(interior_lane<T, Lt>(tab, l & 3, (l >> 2) & 3, l >> 4), g);
         relax<Lt, R, COLL>(g, om, sh, drho, ux, uy, uz, uu);
 #pragma unroll
         for (int p = 0; p < Q; p++) {
-            pin_result<Lt, S>(g[p]);
+            if constexpr (Lt::D == 2) pin_result<S>(g[p]);
             store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, p, l), p, g[p]);
         }
         return;
     }
-    const CellRows<T> r = cell_rows<Lt, T>(tab, B, h, l, src, m);
-    const bool halo = __any(flag & BF_NSKIP);
-    const auto conv = [](R v, int p) { return ST::shift ? v : v - R(Lt::w(p)); };
-    if (halo)
-        gather_rows_by<Lt, ST, true>(r, g, conv);
-    else
-        gather_rows_by<Lt, ST, false>(r, g, conv);
+    // Walls.  Most blocks meet one face or solid only: `code`, whose data then
+    // sit in registers; where some block of the wave meets several, each link
+    // looks its own up in LDS.  A small level is bound by this serial path of its
+    // wall blocks: with a look-up per link and direction a sweep took, us, D3Q27
+    // of 64 blocks FP32 10.0 (now 9.1), of 4096 blocks FP16 12.4 (11.8), D3Q19 of
+    // 64 blocks 7.8 (7.1), D2Q9 of 16384 blocks FP64 8.7 (8.2).
+    FaceTable<Lt, R> &face = sm.face[Lt::D == 3 ? 0 : lane >> 4];
+    uint32_t wall = any.wall;  // of the block
+    int code = kSolid, kind = 0;
+    bool one = true;
+    R wx = R(0), wy = R(0), wz = R(0);
+    if (any.wall) {
+        const bool is_wall = l < De::kLinks && w < 0 && w != kNSkip;
+        if constexpr (Lt::D == 2) wall = (uint32_t)(__ballot(is_wall) >> (lane & 48)) & 0x1ff;
+        code = desc_get<Lt>(w, wall ? __builtin_ctz(wall) : 0);
+        one = !__any(is_wall && w != code);
+        if (!one) face.put(bc, l);
+        const int f = code >= -8 && code <= -3 ? -3 - code : 0;
+        kind = bc.kind[f];
+        wx = R(bc.u[f][0]);
+        wy = R(bc.u[f][1]);
+        if constexpr (Lt::D == 3) wz = R(bc.u[f][2]);
+    }
+    const CellRows<T> r = cell_rows<Lt, T>(tab, any, B, h, l, src, m);
+    gather_rows_by<Lt, ST>(r, g, [](R v, int p) { return ST::shift ? v : v - R(Lt::w(p)); });
     relax<Lt, R, COLL>(g, om, sh, drho, ux, uy, uz, uu);
     wave_lds_sync();
+    // index, links and velocity hidden from common subexpressions: what the
+    // gather and the relaxation computed per population is not kept for the
+    // stores
+    int lf = l;
+    asm volatile("" : "+v"(lf));
+    const InteriorLane u = interior_lane<T, Lt>(tab, lf & 3, (lf >> 2) & 3, lf >> 4);
+    uint32_t walls = any.wall, skips = any.skip;
+    asm volatile("" : "+s"(walls), "+s"(skips));
+    asm volatile("" : "+v"(ux), "+v"(uy), "+v"(uz), "+v"(uu));
 
     [[maybe_unused]] double fx = 0.0, fy = 0.0, fz = 0.0;
     static_for<Q>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         R val = g[q];
-        if (wall) {
-            const int64_t e = (int64_t)row_entry<Lt, Lt::opp(q)>(r.u);  // where population q leaves to
-            if (e < 0 && e != kNSkip) {
-                if (e == kSolid) {
+        if (walls & source_regions<Lt, Lt::opp(q)>()) {  // regions that population q leaves to
+            bool hit;
+            int c = code, kd = kind;
+            R vx = wx, vy = wy, vz = wz;
+            if (one) {
+                hit = (wall >> region_slot<Lt, Lt::opp(q)>(u)) & 1u;
+            } else {
+                const int64_t e = (int64_t)row_entry<Lt, Lt::opp(q)>(u);
+                hit = e < 0 && e != kNSkip;
+                c = (int)e;
+                if (hit && c != kSolid) {
+                    const int f = -3 - c;
+                    kd = face.kind[f];
+                    vx = face.u[f][0];
+                    vy = face.u[f][1];
+                    vz = face.u[f][2];
+                }
+            }
+            if (hit) {
+                if (c == kSolid) {
                     if constexpr (EX) {
                         // 2 f*_q c_q from the value as stored (rounded to the storage type)
                         T t;
@@ -717,10 +810,9 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, co
                         fz += two_f * Lt::cz(q);
                     }
                 } else {
-                    const int f = -3 - (int)e;
                     const R cx = R(Lt::cx(q)), cy = R(Lt::cy(q)), cz = R(Lt::cz(q));
-                    if (face.kind[f] == AMR_FACE_VELOCITY) {
-                        const R cuw = cx * face.u[f][0] + cy * face.u[f][1] + cz * face.u[f][2];
+                    if (kd == AMR_FACE_VELOCITY) {
+                        const R cuw = cx * vx + cy * vy + cz * vz;
                         val = g[q] - R(6) * R(Lt::w(q)) * cuw;
                     } else {
                         const R cu = cx * ux + cy * uy + cz * uz;
@@ -730,7 +822,9 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, co
             }
         }
         // outside the fluid the slot now holds population opposite(q) of this cell
+        pin_result<S>(val);
         store_g<Lt, ST, NTS>(dst, mslot<Lt>(B, q, l), q, val);
+        __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (EX) {
         // uniform over the block's lanes: sum over the block, one lane adds
@@ -748,14 +842,15 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, co
             }
         }
     }
-    if (halo) {
+    if (skips) {
         const int64_t rec = m.halo_base + (int64_t)h * m.nh;
         static_for<Q>([&](auto pc) {
             constexpr int p = decltype(pc)::value;
-            if constexpr (p > 0) {
-                if (row_entry<Lt, p>(r.u) == (uint64_t)(int64_t)kNSkip)
-                    store_g<Lt, ST, NTS>(dst, rec + halo_entry<Lt, p>(r.below), p, g[p]);
+            if (skips & source_regions<Lt, p>()) {
+                if (row_entry<Lt, p>(u) == (uint64_t)(int64_t)kNSkip)
+                    store_g<Lt, ST, NTS>(dst, rec + halo_entry<Lt, p>((uint64_t(1) << lf) - 1), p, g[p]);
             }
+            __builtin_amdgcn_sched_barrier(0);
         });
     }
 }
@@ -976,9 +1071,9 @@ __device__ __forceinline__ void interp_parent(const DevMesh &m, int P, SrcOf src
     if (grp == 0) {
         put_rows<Lt>(sm.ptab, pw, l, src);
         wave_lds_sync();
-        const CellRows<T> r = cell_rows<Lt, T>(sm.ptab, P, desc_get<Lt>(pw, De::kHid), l, src, m);
+        const CellRows<T> r = cell_rows<Lt, T>(sm.ptab, wave_links<Lt>(pw, l), P, desc_get<Lt>(pw, De::kHid), l, src, m);
         R g[Q];
-        gather_rows_flag<Lt, ST>(r, pflag, g);
+        gather_rows<Lt, ST>(r, g);
         R drho, ux, uy, uz;
         moments_g<Lt, R>(g, drho, ux, uy, uz);
         const R uu = ux * ux + uy * uy + uz * uz, sc = r_of(L);
@@ -1001,14 +1096,14 @@ __device__ __forceinline__ void interp_parent(const DevMesh &m, int P, SrcOf src
         if constexpr (Lt::D == 3) gm |= (uint64_t)(uint32_t)desc_get<Lt>(wk, De::kGhost + 1) << 32;
         else gm &= 0xffff;
         if (all_cells) gm = ~0ull;
-        const uint32_t flag = (uint32_t)desc_get<Lt>(wk, De::kFlags);
         const int h = desc_get<Lt>(wk, De::kHid);
+        const LinkMask any = wave_links<Lt>(wk, l);
         if (!((gm >> l) & 1ull)) continue;
         // the cell's index hidden from loop-invariant code motion: per
         // population offsets kept across the two turns would take 50 VGPRs
         int lf = l;
         asm volatile("" : "+v"(lf));
-        const CellRows<T> r = cell_rows<Lt, T>(sm.tab[c], first + c, h, lf, dst, m);
+        const CellRows<T> r = cell_rows<Lt, T>(sm.tab[c], any, first + c, h, lf, dst, m);
         const auto put = [&](auto pc, auto halo, R v) {
             constexpr int p = decltype(pc)::value;
             T *a = global_ptr<T>(slot_address<Lt, T, p, decltype(halo)::value>(r));
@@ -1024,7 +1119,7 @@ __device__ __forceinline__ void interp_parent(const DevMesh &m, int P, SrcOf src
                 T *a = global_ptr<T>(slot_address_any<Lt, T>(r, sm.tab[c], lf, p));
                 ST::st(a, ST::shift ? v : v + R(Lt::w(p)));
             }
-        } else if (flag & BF_NSKIP) {
+        } else if (any.skip) {
             static_for<Q>([&](auto pc) {
                 put(pc, std::true_type(), lin_value<Lt, R>(sm.coef[c][decltype(pc)::value], lf));
             });
@@ -1296,8 +1391,8 @@ __device__ __forceinline__ void average_child(const DevMesh &m, int P, int c, co
     wave_lds_sync();
     const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
     const int h = desc_get<Lt>(w, De::kHid);
-    const uint32_t pflag = (uint32_t)desc_get<Lt>(pw, De::kFlags);
     const int ph = desc_get<Lt>(pw, De::kHid);
+    const LinkMask any = wave_links<Lt>(w, lf), pany = wave_links<Lt>(pw, lf);
     // the 2^d lanes of one parent cell (cell-index bits 0, 2 and, in 3-D, 4)
     // are exactly the partners of the sums below: a group whose parent cell
     // is not written loads nothing
@@ -1306,7 +1401,7 @@ __device__ __forceinline__ void average_child(const DevMesh &m, int P, int c, co
     if constexpr (VEL) read = !(flag & BF_NSKIP) && velocity_read<Lt>(m, w, flag);
     R g[Q];
     if ((im >> lead) & 1ull) {
-        gather_rows_flag<Lt, ST, RAW>(cell_rows<Lt, T>(ctab, child, h, lf, src, m), flag, g);
+        gather_rows<Lt, ST, RAW>(cell_rows<Lt, T>(ctab, any, child, h, lf, src, m), g);
     } else {
 #pragma unroll
         for (int p = 0; p < Q; p++) g[p] = R(0);
@@ -1339,13 +1434,13 @@ __device__ __forceinline__ void average_child(const DevMesh &m, int P, int c, co
     const int i = lf & 3, j = (lf >> 2) & 3, k = lf >> 4;
     if (lf != lead || !((im >> lf) & 1ull)) return;
     const int l = ((c & 1) * 2 + (i >> 1)) + 4 * (((c >> 1) & 1) * 2 + (j >> 1)) + 16 * ((c >> 2) * 2 + (k >> 1));
-    const CellRows<T> pr = cell_rows<Lt, T>(ptab, P, ph, l, dst, m);
+    const CellRows<T> pr = cell_rows<Lt, T>(ptab, pany, P, ph, l, dst, m);
     const auto put = [&](auto pc, auto halo) {
         constexpr int p = decltype(pc)::value;
         const R v = g[p] / R(NC);
         ST::st(global_ptr<T>(slot_address<Lt, T, p, decltype(halo)::value>(pr)), ST::shift ? v : v + R(Lt::w(p)));
     };
-    if (pflag & BF_NSKIP) static_for<Q>([&](auto pc) { put(pc, std::true_type()); });
+    if (pany.skip) static_for<Q>([&](auto pc) { put(pc, std::true_type()); });
     else static_for<Q>([&](auto pc) { put(pc, std::false_type()); });
 }
 
@@ -1615,13 +1710,12 @@ __device__ __forceinline__ void cell_f64_desc(const DevMesh &m, uint64_t *tab, i
     using De = Desc<Lt::D>;
     put_rows<Lt>(tab, w, l, f);
     wave_lds_sync();
-    const uint32_t flag = (uint32_t)desc_get<Lt>(w, De::kFlags);
-    const CellRows<T> r = cell_rows<Lt, T>(tab, B, desc_get<Lt>(w, De::kHid), l, f, m);
+    const CellRows<T> r = cell_rows<Lt, T>(tab, wave_links<Lt>(w, l), B, desc_get<Lt>(w, De::kHid), l, f, m);
     const auto conv = [](typename ST::R v, int p) { return double(v) + (ST::shift ? Lt::w(p) : 0.0); };
-    if (!(flag & (BF_BOUNDARY | BF_NSKIP)))
+    if (!(r.any.wall | r.any.skip))
         gather_interior_by<Lt, ST>(r.u, fv, conv);
     else
-        gather_rows_by<Lt, ST, true>(r, fv, conv);
+        gather_rows_by<Lt, ST>(r, fv, conv);
 }
 
 // ghost cells of a block from its descriptor words
