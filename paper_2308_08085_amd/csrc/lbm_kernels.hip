@@ -864,6 +864,21 @@ __device__ __forceinline__ void collide_block(const DevMesh &m, int B, int l, co
 template <int S>
 constexpr int collide_threads() { return 256; }
 
+// Waves per SIMD of the large 3-D sweeps (those stored past the caches): more
+// waves keep more loads in flight but also more blocks, and the rows that
+// neighbouring blocks share have to stay in the XCD's 4 MB L2 until the last of
+// them has read its part.  D3Q27 cylinder, us per sweep with 2, 3, 4, 5, 6, 7
+// waves: FP32 1398, 1264, 1250, 1289, 1306, 1364; FP16 (half the bytes per block)
+// 1140, 876, 760, 742, 739, 779.  Uniform D3Q19 FP32 level of 256^3 cells with
+// 3, 4, 5, 6, 7: 531, 510, 517, 520, 526.  FP64 is left to the compiler (2256 to
+// 2386 over runs; 2 to 4 waves 2298 to 2462, 4 with spills).  Smaller levels do
+// not depend on it; BGK only, the other collisions were not swept.
+template <int Q, int S, bool NTS, int COLL>
+constexpr int collide_waves(bool most) {
+    if (!(NTS && COLL == 0 && Lat<Q>::D == 3) || S == AMR_F64) return most ? 8 : 1;  // the compiler's choice
+    return sizeof(typename Store<S>::T) == 2 ? 6 : 4;
+}
+
 // blocks per workgroup of k_collide_stream (one per 64-lane group)
 template <int Q, int S>
 constexpr int collide_blocks_per_wg() { return collide_threads<S>() / Lat<Q>::MB; }
@@ -891,7 +906,8 @@ __device__ __forceinline__ void collide_wg(const int32_t *__restrict__ list, int
 }
 
 template <int Q, int S, bool NTS, int COLL = 0, bool EX = false>
-__global__ __launch_bounds__(collide_threads<S>()) void k_collide_stream(
+__global__ __launch_bounds__(collide_threads<S>())
+    __attribute__((amdgpu_waves_per_eu(collide_waves<Q, S, NTS, COLL>(false), collide_waves<Q, S, NTS, COLL>(true)))) void k_collide_stream(
     const int32_t *__restrict__ list, int n, DevMesh m, const typename Store<S>::T *__restrict__ src,
     typename Store<S>::T *__restrict__ dst, double omega_d, BCParams bc, double s_high) {
     collide_wg<Q, S, NTS, COLL, EX>(list, n, m, src, dst, omega_d, bc, s_high, xcd_remap(blockIdx.x, gridDim.x));
