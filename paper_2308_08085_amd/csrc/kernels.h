@@ -19,8 +19,8 @@ struct DevCounters {
     int32_t n_outb;
     int32_t pad[1];
     unsigned long long wmax_bits;
-    int32_t totals[kMaxLevels];
-    int32_t bases[kMaxLevels];
+    int32_t totals[kMaxLevels];  // of the last list of an adaptation
+    int32_t pad2[kMaxLevels];
     double mass[4];
     // cells the solver's grid communication moves from level L, per coarse
     // step of L: ghost cells its interpolation writes into level L+1, parent
@@ -49,14 +49,10 @@ struct Ctx {
     int32_t *solidl;     // [lmax][cap] leaf blocks next to a solid block, per level
     int32_t *gap;        // [cap]
     int32_t *first;      // [cap]
-    int32_t *rank;       // [lmax * cap]
     int32_t *rlist;      // [cap]
-    int32_t *clist;      // [cap]
-    int8_t *bins;        // [lmax * cap]
-    int32_t *scan_part;  // [nwg_max * 8]
-    int32_t *cnt;        // [cap]
+    int32_t *scan_part;  // counts of the ordered lists
     int32_t *off;        // [cap] first output cell of each block
-    int32_t *outl;       // [cap] the blocks with output cells, by ID (= cnt, once that has been summed)
+    int32_t *outl;       // [cap] the blocks with output cells, by ID
     double *crit;        // [cap]
     double *U;           // [3][cap * Mb] FP64 cell velocities for the criterion
     double *part4;       // [cap * 4]

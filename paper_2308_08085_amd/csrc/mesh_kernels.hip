@@ -6,6 +6,8 @@
 // scans, never from atomics, so tables are deterministic.
 #include "kernels.h"
 
+#include <tuple>
+
 namespace amr {
 
 namespace {
@@ -17,32 +19,64 @@ constexpr int kScanItems = kScanTPB * kScanPer;
 inline int grid_for(int64_t n, int tpb = 256) { return (int)((n + tpb - 1) / tpb); }
 
 // ---------------------------------------------------------------------------
-// Binned exclusive scan: for every element with bin b >= 0, rank = number of
-// earlier elements (in index order) with the same bin.  Three passes: per-
-// workgroup counts (wave ballots), a single-workgroup scan of the counts, then
-// per-element ranks (ballot + popcount of the lanes below).
-__global__ __launch_bounds__(256) void k_scan_count(const int8_t *__restrict__ bins, int64_t n, int K,
-                                                    int32_t *__restrict__ part) {
+// Ordered lists.  A job gives every index of its range a bin (-1: none); its
+// rank is the number of earlier indexes (in order) with the same bin, and the
+// job's put() places it by that rank.  A job with kSum gives a value instead,
+// and the rank is the sum of the earlier values.
+//   K        bins
+//   n(m)     indexes
+//   bin(m, ctr, i)
+//   put(m, ctr, i, bin, rank, tot)   tot: all K totals; called for every index
+//   done(m, ctr, tot)                one thread, beside the puts: may write
+//                                    only what no bin() or put() of the launch reads
+// Two launches: the counts of every 1024 indexes, then ranks and puts, for which
+// every workgroup adds up the counts before its own.  Independent jobs share
+// both (grid y).  Small meshes are bound by the number of launches (6 to 7 us
+// each, gap included): bins, counts, their scan, ranks, compaction and copy were
+// six per list and 87 for a mesh change with three levels, now 31.  64 x 64 2-D
+// cavity with four changes 10.5 -> 9.6 ms, eight steps and one change of a 52^3
+// cavity 4.8 -> 4.5 ms.
+// Above kScanDirect workgroups a single one scans the counts in between, since
+// the counts that every workgroup reads grow with the square.
+constexpr int kScanDirect = 1024;
+
+inline __host__ __device__ int scan_groups(int64_t n) { return (int)((n + kScanItems - 1) / kScanItems); }
+
+template <typename J>
+__device__ __forceinline__ void scan_count(const J &j, const DevMesh &m, const DevCounters *ctr, int32_t *part) {
+    const int64_t n = j.n(m);
+    const int wg = blockIdx.x, lane = threadIdx.x & 63;
     __shared__ int32_t s_cnt[kMaxLevels];
-    if ((int)threadIdx.x < K) s_cnt[threadIdx.x] = 0;
+    if (wg >= scan_groups(n)) return;
+    if ((int)threadIdx.x < kMaxLevels) s_cnt[threadIdx.x] = 0;
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    for (int r = 0; r < kScanPer; r++) {
-        const int64_t idx = (int64_t)blockIdx.x * kScanItems + r * kScanTPB + threadIdx.x;
-        const int b = idx < n ? bins[idx] : -1;
-        for (int k = 0; k < K; k++) {
-            const uint64_t msk = __ballot(b == k);
-            if (lane == 0 && msk) atomicAdd(&s_cnt[k], (int)__popcll(msk));
+    if constexpr (J::kSum) {
+        int sum = 0;
+        for (int r = 0; r < kScanPer; r++) {
+            const int64_t i = (int64_t)wg * kScanItems + r * kScanTPB + threadIdx.x;
+            if (i < n) sum += j.bin(m, ctr, i);
+        }
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane == 0) atomicAdd(&s_cnt[0], sum);
+    } else {
+        for (int r = 0; r < kScanPer; r++) {
+            const int64_t i = (int64_t)wg * kScanItems + r * kScanTPB + threadIdx.x;
+            const int b = i < n ? j.bin(m, ctr, i) : -1;
+            for (int k = 0; k < j.K; k++) {
+                const uint64_t msk = __ballot(b == k);
+                if (lane == 0 && msk) atomicAdd(&s_cnt[k], (int)__popcll(msk));
+            }
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < K) part[(int64_t)blockIdx.x * K + threadIdx.x] = s_cnt[threadIdx.x];
+    if ((int)threadIdx.x < j.K) part[(int64_t)wg * j.K + threadIdx.x] = s_cnt[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void k_scan_part(int32_t *__restrict__ part, int nwg, int K, DevCounters *ctr) {
+// exclusive scan of the counts of one job in place, the totals behind them
+template <typename J>
+__device__ __forceinline__ void scan_part(const J &j, const DevMesh &m, int32_t *part) {
     __shared__ int32_t s[256];
-    __shared__ int32_t s_tot[kMaxLevels];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, K = j.K, nwg = scan_groups(j.n(m));
     const int chunk = (nwg + 255) / 256;
     for (int k = 0; k < K; k++) {
         const int lo = min(nwg, t * chunk), hi = min(nwg, lo + chunk);
@@ -62,103 +96,136 @@ __global__ __launch_bounds__(256) void k_scan_part(int32_t *__restrict__ part, i
             part[(int64_t)i * K + k] = run;
             run += v;
         }
-        if (t == 255) s_tot[k] = s[255];
+        if (t == 255) part[(int64_t)nwg * K + k] = s[255];
         __syncthreads();
-    }
-    if (t == 0) {
-        int acc = 0;
-        for (int k = 0; k < kMaxLevels; k++) {
-            const int v = k < K ? s_tot[k] : 0;
-            ctr->totals[k] = v;
-            ctr->bases[k] = acc;
-            acc += v;
-        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_scan_rank(const int8_t *__restrict__ bins, int64_t n, int K,
-                                                   const int32_t *__restrict__ part, int32_t *__restrict__ rank) {
-    __shared__ int32_t s_run[kMaxLevels];
+template <typename J>
+__device__ __forceinline__ void scan_put(const J &j, const DevMesh &m, DevCounters *ctr, const int32_t *part,
+                                         bool scanned) {
+    const int64_t n = j.n(m);
+    const int K = j.K, nwg = scan_groups(n), wg = blockIdx.x, t = threadIdx.x;
+    __shared__ int32_t s_run[kMaxLevels], s_tot[kMaxLevels];
     __shared__ int32_t s_wt[4][kMaxLevels];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if ((int)threadIdx.x < K) s_run[threadIdx.x] = part[(int64_t)blockIdx.x * K + threadIdx.x];
+    if (wg >= nwg) return;
+    if (t < kMaxLevels) {
+        s_run[t] = scanned && t < K ? part[(int64_t)wg * K + t] : 0;
+        s_tot[t] = scanned && t < K ? part[(int64_t)nwg * K + t] : 0;
+    }
     __syncthreads();
+    if (!scanned) {
+        // a thread's entries all have the same bin
+        const int step = 256 / K * K, all = nwg * K, mine = wg * K;
+        int run = 0, tot = 0;
+        if (t < step)
+            for (int e = t; e < all; e += step) {
+                const int v = part[e];
+                tot += v;
+                run += e < mine ? v : 0;
+            }
+        if (tot) atomicAdd(&s_tot[t % K], tot);
+        if (run) atomicAdd(&s_run[t % K], run);
+        __syncthreads();
+    }
+    const int lane = t & 63, wave = t >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     for (int r = 0; r < kScanPer; r++) {
-        const int64_t idx = (int64_t)blockIdx.x * kScanItems + r * kScanTPB + threadIdx.x;
-        const int b = idx < n ? bins[idx] : -1;
+        const int64_t i = (int64_t)wg * kScanItems + r * kScanTPB + t;
+        int b = J::kSum ? 0 : -1;
+        if (i < n) b = j.bin(m, ctr, i);
         int my = 0;
-        for (int k = 0; k < K; k++) {
-            const uint64_t msk = __ballot(b == k);
-            if (b == k) my = (int)__popcll(msk & below);
-            if (lane == 0) s_wt[wave][k] = (int)__popcll(msk);
+        if constexpr (J::kSum) {
+            int x = b;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(x, off, 64);
+                if (lane >= off) x += y;
+            }
+            my = x - b;
+            if (lane == 63) s_wt[wave][0] = x;
+        } else {
+            for (int k = 0; k < K; k++) {
+                const uint64_t msk = __ballot(b == k);
+                if (b == k) my = (int)__popcll(msk & below);
+                if (lane == 0) s_wt[wave][k] = (int)__popcll(msk);
+            }
         }
         __syncthreads();
-        if (b >= 0) {
-            int pre = s_run[b];
-            for (int w = 0; w < wave; w++) pre += s_wt[w][b];
-            rank[idx] = pre + my;
+        if (i < n) {
+            int rank = 0;
+            if (J::kSum || b >= 0) {
+                const int k = J::kSum ? 0 : b;
+                rank = s_run[k] + my;
+                for (int w = 0; w < wave; w++) rank += s_wt[w][k];
+            }
+            j.put(m, ctr, i, b, rank, s_tot);
         }
         __syncthreads();
-        if ((int)threadIdx.x < K) {
-            const int k = threadIdx.x;
-            s_run[k] += s_wt[0][k] + s_wt[1][k] + s_wt[2][k] + s_wt[3][k];
-        }
+        if (t < K) s_run[t] += s_wt[0][t] + s_wt[1][t] + s_wt[2][t] + s_wt[3][t];
         __syncthreads();
     }
+    if (wg == 0 && t == 0) j.done(m, ctr, s_tot);
 }
 
-void run_scan(const Ctx &c, const int8_t *bins, int64_t n, int K) {
-    const int nwg = (int)((n + kScanItems - 1) / kScanItems);
-    k_scan_count<<<nwg, kScanTPB, 0, c.stream>>>(bins, n, K, c.scan_part);
-    k_scan_part<<<1, 256, 0, c.stream>>>(c.scan_part, nwg, K, c.ctr);
-    k_scan_rank<<<nwg, kScanTPB, 0, c.stream>>>(bins, n, K, c.scan_part, c.rank);
+template <typename J>
+struct Scan {
+    J j;
+    int32_t *part;
+};
+
+template <typename... Js>
+__global__ __launch_bounds__(256) void k_scan_count(DevMesh m, const DevCounters *ctr, Scan<Js>... s) {
+    int y = 0;
+    ((blockIdx.y == y++ ? scan_count(s.j, m, ctr, s.part) : void()), ...);
 }
 
-// exclusive prefix sum of non-negative int32 values (output-cell offsets)
-__global__ __launch_bounds__(256) void k_wscan_count(const int32_t *__restrict__ v, int64_t n,
-                                                     int32_t *__restrict__ part) {
-    __shared__ int32_t s[256];
-    int sum = 0;
-    for (int e = 0; e < kScanPer; e++) {
-        const int64_t idx = (int64_t)blockIdx.x * kScanItems + threadIdx.x * kScanPer + e;
-        if (idx < n) sum += v[idx];
-    }
-    s[threadIdx.x] = sum;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+template <typename... Js>
+__global__ __launch_bounds__(256) void k_scan_part(DevMesh m, Scan<Js>... s) {
+    int y = 0;
+    ((blockIdx.y == y++ ? scan_part(s.j, m, s.part) : void()), ...);
 }
 
-__global__ __launch_bounds__(256) void k_wscan_apply(const int32_t *__restrict__ v, int64_t n,
-                                                     const int32_t *__restrict__ part, int32_t *__restrict__ out) {
-    __shared__ int32_t s[256];
-    const int t = threadIdx.x;
-    int loc[kScanPer];
-    int sum = 0;
-    for (int e = 0; e < kScanPer; e++) {
-        const int64_t idx = (int64_t)blockIdx.x * kScanItems + t * kScanPer + e;
-        loc[e] = idx < n ? v[idx] : 0;
-        sum += loc[e];
-    }
-    s[t] = sum;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int x = t >= off ? s[t - off] : 0;
-        __syncthreads();
-        s[t] += x;
-        __syncthreads();
-    }
-    int run = part[blockIdx.x] + s[t] - sum;
-    for (int e = 0; e < kScanPer; e++) {
-        const int64_t idx = (int64_t)blockIdx.x * kScanItems + t * kScanPer + e;
-        if (idx < n) out[idx] = run;
-        run += loc[e];
-    }
+template <typename... Js>
+__global__ __launch_bounds__(256) void k_scan_put(DevMesh m, DevCounters *ctr, bool scanned, Scan<Js>... s) {
+    int y = 0;
+    ((blockIdx.y == y++ ? scan_put(s.j, m, ctr, s.part, scanned) : void()), ...);
 }
+
+template <typename... Js>
+void run_lists(const Ctx &c, Js... js) {
+    int nwg = 0;
+    int32_t *part = c.scan_part;
+    const auto place = [&](auto j) {
+        const int g = scan_groups(j.n(c.m));
+        Scan<decltype(j)> s{j, part};
+        part += (int64_t)(g + 1) * j.K;
+        nwg = g > nwg ? g : nwg;
+        return s;
+    };
+    const auto go = [&](auto... s) {
+        const dim3 grid(nwg, sizeof...(s));
+        const bool scanned = nwg > kScanDirect;
+        k_scan_count<<<grid, kScanTPB, 0, c.stream>>>(c.m, c.ctr, s...);
+        if (scanned) k_scan_part<<<dim3(1, sizeof...(s)), 256, 0, c.stream>>>(c.m, s...);
+        k_scan_put<<<grid, kScanTPB, 0, c.stream>>>(c.m, c.ctr, scanned, s...);
+    };
+    std::apply(go, std::tuple{place(js)...});  // braces: left to right
+}
+
+// jobs over all block IDs
+struct BlockJob {
+    static constexpr bool kSum = false;
+    int K = 1;
+    __host__ __device__ int64_t n(const DevMesh &m) const { return m.cap; }
+    __device__ void done(const DevMesh &, DevCounters *, const int32_t *) const {}
+};
+
+// jobs over the virtual concatenation of per-level lists: index = L * cap + i
+struct LevelJob {
+    static constexpr bool kSum = false;
+    int K;  // = lmax
+    __host__ __device__ int64_t n(const DevMesh &m) const { return (int64_t)m.lmax * m.cap; }
+};
 
 // ---------------------------------------------------------------------------
 struct RootParams {
@@ -194,7 +261,7 @@ __device__ int32_t root_link(const RootParams &rp, const uint8_t *solid, int bi,
 }
 
 template <typename Dd>
-__global__ void k_init_blocks(DevMesh m, RootParams rp, const uint8_t *solid, int8_t *bins) {
+__global__ void k_init_blocks(DevMesh m, RootParams rp, const uint8_t *solid) {
     const int B = blockIdx.x * blockDim.x + threadIdx.x;
     if (B >= m.cap) return;
     m.tag[B] = 0;
@@ -209,7 +276,6 @@ __global__ void k_init_blocks(DevMesh m, RootParams rp, const uint8_t *solid, in
     if (B >= rp.nroot) {
         m.status[B] = ST_INACTIVE;
         for (int a = 0; a < 3; a++) m.X[(int64_t)a * m.cap + B] = 0;
-        bins[B] = -1;
         return;
     }
     const int bi = B % rp.root[0], bj = (B / rp.root[0]) % rp.root[1], bk = B / (rp.root[0] * rp.root[1]);
@@ -219,7 +285,6 @@ __global__ void k_init_blocks(DevMesh m, RootParams rp, const uint8_t *solid, in
     m.X[(int64_t)2 * m.cap + B] = bk * W0;
     const bool sol = solid && solid[B];
     m.status[B] = sol ? ST_INACTIVE : ST_UNREF;
-    bins[B] = sol ? -1 : 0;
     for (int p = 0; p < Dd::NB; p++) {
         const int32_t n = sol ? 0 : root_link<Dd>(rp, solid, bi, bj, bk, p);
         m.nbr[(int64_t)p * m.cap + B] = n;
@@ -232,18 +297,23 @@ __global__ void k_init_gap(int32_t *gap, int cap, int nroot) {
     if (g < cap - nroot) gap[g] = cap - 1 - g;
 }
 
-__global__ void k_init_ids(const int8_t *bins, const int32_t *rank, int cap, int32_t *ids, DevCounters *ctr, int nroot) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B < cap && bins[B] == 0) ids[rank[B]] = B;
-    if (B == 0) {
-        ctr->nids[0] = ctr->totals[0];
+// the root blocks that are not solid, and the counters of a new mesh
+struct InitJob : BlockJob {
+    int32_t *ids;
+    int nroot;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const { return m.status[B] == ST_UNREF ? 0 : -1; }
+    __device__ void put(const DevMesh &, DevCounters *, int64_t B, int b, int r, const int32_t *) const {
+        if (b == 0) ids[r] = (int32_t)B;
+    }
+    __device__ void done(const DevMesh &m, DevCounters *ctr, const int32_t *tot) const {
+        ctr->nids[0] = tot[0];
         for (int L = 1; L < kMaxLevels; L++) ctr->nids[L] = 0;
-        for (int L = 0; L < kMaxLevels; L++) ctr->niface[L] = ctr->nref[L] = ctr->nsweep[L] = 0;
-        ctr->gtop = cap - nroot;
+        for (int L = 0; L < kMaxLevels; L++) ctr->niface[L] = ctr->nref[L] = ctr->nsweep[L] = ctr->nsolid[L] = 0;
+        ctr->gtop = m.cap - nroot;
         ctr->n_ref = ctr->n_coa = ctr->n_rev = ctr->nfreed = 0;
         ctr->wmax_bits = 0;
     }
-}
+};
 
 // ---------------------------------------------------------------------------
 // Cell classes (Sec. "Grid Communication"): a cell of a block on level > 0 is a
@@ -251,8 +321,9 @@ __global__ void k_init_ids(const int8_t *bins, const int32_t *rank, int cap, int
 // region is at most 2, an interface cell at 3 or 4.  Also the per-block flags
 // used by the solver kernels.
 template <typename Dd>
-__global__ void k_block_masks(DevMesh m) {
+__global__ void k_block_masks(DevMesh m, DevCounters *ctr) {
     const int B = blockIdx.x * blockDim.x + threadIdx.x;
+    if (B < kMaxLevels) ctr->ghost_w[B] = ctr->avg_w[B] = 0;  // for k_target_cells
     if (B >= m.cap) return;
     if (m.status[B] == ST_INACTIVE) {
         m.bflag[B] = 0;
@@ -451,44 +522,28 @@ __global__ void k_effective_tags(DevMesh m, DevCounters *ctr) {
 
 // ---------------------------------------------------------------------------
 // Adaptation.
-__global__ void k_bins_refine(const DevMesh m, int8_t *bins, int by_level) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    const int t = m.tag[B];
-    bins[B] = (t == 1 || t == 2) ? (int8_t)(by_level ? m.level[B] : 0) : (int8_t)-1;
-}
-
-__global__ void k_bins_coarsen(const DevMesh m, int8_t *bins) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    bins[B] = m.tag[B] == -1 ? m.level[B] : (int8_t)-1;
-}
-
 // S2: the r-th refine-marked block (ascending ID) takes the N_c gaps below
 // the top of the gap stack; its first child is gap[top - 1 - N_c r]
-__global__ void k_assign_first(DevMesh m, const int32_t *rank, const int32_t *gap, const DevCounters *ctr,
-                               int32_t *first, int32_t *rlist, int nc) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    const int t = m.tag[B];
-    if (t == 1 || t == 2) {
-        const int r = rank[B];
-        first[B] = gap[ctr->gtop - 1 - nc * r];
-        rlist[r] = B;
-    } else {
-        first[B] = -1;
+struct RefineJob : BlockJob {
+    const int32_t *gap;
+    int32_t *first, *rlist;
+    int nc;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const {
+        const int t = m.tag[B];
+        return t == 1 || t == 2 ? 0 : -1;
     }
-}
-
-__global__ void k_gtop_add(DevCounters *ctr, int delta_const, int use_freed) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) ctr->gtop += use_freed ? ctr->nfreed : delta_const;
-}
+    __device__ void put(const DevMesh &, DevCounters *ctr, int64_t B, int b, int r, const int32_t *) const {
+        first[B] = b == 0 ? gap[ctr->gtop - 1 - nc * r] : -1;
+        if (b == 0) rlist[r] = (int32_t)B;
+    }
+};
 
 // S3: a leaf is violating if any provisional neighbour-child (this call's new
 // children included, and its own at p = 0) is a valid ID
 template <typename Dd>
-__global__ void k_violating(DevMesh m, const int32_t *first) {
+__global__ void k_violating(DevMesh m, const int32_t *first, DevCounters *ctr, int taken) {
     const int B = blockIdx.x * blockDim.x + threadIdx.x;
+    if (B == 0) ctr->gtop -= taken;
     if (B >= m.cap) return;
     int8_t v = 0;
     if (m.status[B] == ST_UNREF) {
@@ -543,99 +598,88 @@ __global__ void k_build_children(DevMesh m, const int32_t *rlist, const int32_t 
 
 // S5: freed children in (parent level, parent ID, child) order F; the gap
 // stack receives reverse(F) on top
-template <typename Dd>
-__global__ void k_coarsen(DevMesh m, const int32_t *rank, int32_t *gap, DevCounters *ctr) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap || m.tag[B] != -1) return;
-    const int lm = m.lmax - 1;
-    const int nF = Dd::NC * (ctr->bases[lm] + ctr->totals[lm]);
-    const int pos = ctr->bases[m.level[B]] + rank[B];
-    const int c0 = m.nbrc[B];
-    for (int c = 0; c < Dd::NC; c++) {
-        const int k = pos * Dd::NC + c;
-        gap[ctr->gtop + nF - 1 - k] = c0 + c;
-        m.status[c0 + c] = ST_REMOVE;
+struct CoarsenJob : BlockJob {
+    int32_t *gap;
+    int nc;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const { return m.tag[B] == -1 ? m.level[B] : -1; }
+    __device__ void put(const DevMesh &m, DevCounters *ctr, int64_t B, int b, int r, const int32_t *tot) const {
+        if (b < 0) return;
+        int nF = 0, pos = r;
+        for (int k = 0; k < K; k++) {
+            nF += tot[k];
+            if (k < b) pos += tot[k];
+        }
+        nF *= nc;
+        const int c0 = m.nbrc[B];
+        for (int c = 0; c < nc; c++) {
+            gap[ctr->gtop + nF - 1 - (pos * nc + c)] = c0 + c;
+            m.status[c0 + c] = ST_REMOVE;
+        }
+        m.nbrc[B] = kNone;
     }
-    m.nbrc[B] = kNone;
-    if (pos == 0) {
-        ctr->nfreed = nF;
-        ctr->n_coa = nF / Dd::NC;
+    // the stack's new top: once every put has read the old one (k_copy_kept)
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const {
+        int n = 0;
+        for (int k = 0; k < K; k++) n += tot[k];
+        ctr->nfreed = nc * n;
+        ctr->n_coa = n;
     }
-}
+};
 
-__global__ void k_zero_freed(DevCounters *ctr) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        ctr->nfreed = 0;
-        ctr->n_coa = 0;
+// the blocks of each ID set that are not freed
+struct KeepJob : LevelJob {
+    const int32_t *ids;
+    int32_t *kept;
+    __device__ int bin(const DevMesh &m, const DevCounters *ctr, int64_t e) const {
+        const int L = (int)(e / m.cap), i = (int)(e - (int64_t)L * m.cap);
+        return i < ctr->nids[L] && m.status[ids[e]] != ST_REMOVE ? L : -1;
     }
-}
+    __device__ void put(const DevMesh &m, DevCounters *, int64_t e, int b, int r, const int32_t *) const {
+        if (b >= 0) kept[(int64_t)b * m.cap + r] = ids[e];
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const {
+        for (int k = 0; k < kMaxLevels; k++) ctr->totals[k] = k < K ? tot[k] : 0;
+    }
+};
 
-// virtual concatenation of the per-level ID lists: element e = L*cap + i
-__global__ void k_bins_keep(const DevMesh m, const int32_t *ids, const DevCounters *ctr, int8_t *bins, int mode) {
+// ... copied back (other workgroups were reading the ID sets)
+__global__ void k_copy_kept(const int32_t *src, int32_t *dst, int cap, int lmax, DevCounters *ctr) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t tot = (int64_t)m.lmax * m.cap;
-    if (e >= tot) return;
-    const int L = (int)(e / m.cap), i = (int)(e - (int64_t)L * m.cap);
-    int8_t b = -1;
-    if (i < ctr->nids[L]) {
-        const int B = ids[e];
-        if (mode == 0) b = m.status[B] != ST_REMOVE ? (int8_t)L : (int8_t)-1;
-        else if (mode == 1) b = (m.bflag[B] & BF_PARENT_MASK) ? (int8_t)L : (int8_t)-1;
-        else if (mode == 2) b = is_refined(m.status[B]) ? (int8_t)L : (int8_t)-1;
-        else b = (is_refined(m.status[B]) && !(m.bflag[B] & BF_PARENT_MASK)) ? (int8_t)-1 : (int8_t)L;
-    }
-    bins[e] = b;
-}
-
-__global__ void k_compact(const int8_t *bins, const int32_t *rank, const int32_t *src, int32_t *dst, int cap,
-                          int64_t tot) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= tot) return;
-    const int b = bins[e];
-    if (b >= 0) dst[(int64_t)b * cap + rank[e]] = src[e];
-}
-
-// copy back the compacted lists; the new sizes are the scan totals
-// which: 0 = interface parents (niface), 1 = ID sets (nids), 2 = refined blocks (nref),
-// 3 = sweep lists (nsweep)
-__global__ void k_copy_lists(const int32_t *src, int32_t *dst, int cap, int lmax, DevCounters *ctr, int which) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t tot = (int64_t)lmax * cap;
-    if (e < tot) {
+    if (e < (int64_t)lmax * cap) {
         const int L = (int)(e / cap), i = (int)(e - (int64_t)L * cap);
         if (i < ctr->totals[L]) dst[e] = src[e];
     }
     if (e == 0) {
-        for (int L = 0; L < lmax; L++) {
-            if (which == 1) ctr->nids[L] = ctr->totals[L];
-            else if (which == 2) ctr->nref[L] = ctr->totals[L];
-            else if (which == 3) ctr->nsweep[L] = ctr->totals[L];
-            else ctr->niface[L] = ctr->totals[L];
-        }
+        for (int L = 0; L < lmax; L++) ctr->nids[L] = ctr->totals[L];
+        ctr->gtop += ctr->nfreed;
     }
 }
 
-// S6: append new children to id_set_{L+1} in (parent ID, child) order
-template <typename Dd>
-__global__ void k_append(DevMesh m, const int32_t *rank, const int32_t *first, int32_t *ids, const DevCounters *ctr) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    const int t = m.tag[B];
-    if (t != 1 && t != 2) return;
-    const int L = m.level[B];
-    const int base = ctr->nids[L + 1] + Dd::NC * rank[B];
-    for (int c = 0; c < Dd::NC; c++) ids[(int64_t)(L + 1) * m.cap + base + c] = first[B] + c;
-}
-
-template <typename Dd>
-__global__ void k_nids_after_append(DevCounters *ctr, int lmax) {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        for (int L = lmax - 2; L >= 0; L--) ctr->nids[L + 1] += Dd::NC * ctr->totals[L];
-}
+// S6: append new children to id_set_{L+1} in (parent ID, child) order; the
+// counts follow in k_finalize_status
+struct AppendJob : BlockJob {
+    const int32_t *first;
+    int32_t *ids;
+    int nc;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const {
+        const int t = m.tag[B];
+        return t == 1 || t == 2 ? m.level[B] : -1;
+    }
+    __device__ void put(const DevMesh &m, DevCounters *ctr, int64_t B, int b, int r, const int32_t *) const {
+        if (b < 0) return;
+        const int base = ctr->nids[b + 1] + nc * r;
+        for (int c = 0; c < nc; c++) ids[(int64_t)(b + 1) * m.cap + base + c] = first[B] + c;
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const {
+        for (int k = 0; k < kMaxLevels; k++) ctr->totals[k] = k < K ? tot[k] : 0;
+    }
+};
 
 // S7: finalise statuses, then branch / leaf
-__global__ void k_finalize_status(DevMesh m) {
+__global__ void k_finalize_status(DevMesh m, DevCounters *ctr, int appended) {  // appended: children per block of totals
     const int B = blockIdx.x * blockDim.x + threadIdx.x;
+    if (B == 0)
+        for (int L = 0; L + 1 < m.lmax; L++) ctr->nids[L + 1] += appended * ctr->totals[L];
     if (B >= m.cap) return;
     const int t = m.tag[B];
     int st = m.status[B];
@@ -707,26 +751,6 @@ __global__ void k_child_links(DevMesh m, const int32_t *ids, const DevCounters *
     }
 }
 
-__global__ void k_out_count(DevMesh m, int32_t *cnt, int mb) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    const uint64_t full = mb == 64 ? ~0ull : ((1ull << mb) - 1);
-    cnt[B] = m.status[B] == ST_UNREF ? (int)__popcll(~m.gmask[B] & full) : 0;
-}
-
-__global__ void k_out_bins(const int32_t *cnt, const int32_t *off, int cap, int8_t *bins, DevCounters *ctr) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= cap) return;
-    bins[B] = cnt[B] > 0 ? 0 : -1;
-    if (B == cap - 1) ctr->n_out = off[B] + cnt[B];
-}
-
-__global__ void k_out_list(const int8_t *bins, const int32_t *rank, int cap, int32_t *outl, DevCounters *ctr) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B < cap && bins[B] == 0) outl[rank[B]] = B;
-    if (B == 0) ctr->n_outb = ctr->totals[0];
-}
-
 RootParams root_params(const Ctx &c) {
     RootParams rp;
     rp.dim = c.dim;
@@ -741,81 +765,115 @@ RootParams root_params(const Ctx &c) {
 }
 
 // halo records: one per active block with an N_SKIP link, numbered in block-ID order
-__global__ void k_bins_halo(const DevMesh m, int8_t *bins) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    bins[B] = (m.status[B] != ST_INACTIVE && (m.bflag[B] & BF_NSKIP)) ? 0 : -1;
-}
-
-__global__ void k_set_hid(DevMesh m, const int8_t *bins, const int32_t *rank) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    m.hid[B] = bins[B] == 0 ? rank[B] : -1;
-}
-
-// Launch order of level L+1 from that of level L: the children of every
-// refined block, in its order (children are numbered as Morton digits).
-__global__ void k_bins_order(const DevMesh m, const int32_t *order, const DevCounters *ctr, int L, int8_t *bins) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= m.cap) return;
-    int8_t b = -1;
-    if (n < ctr->nids[L]) {
-        const int32_t first = m.nbrc[order[n]];
-        if (first >= 0 && first < m.cap) b = 0;
+struct HaloJob : BlockJob {
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const {
+        return m.status[B] != ST_INACTIVE && (m.bflag[B] & BF_NSKIP) ? 0 : -1;
     }
-    bins[n] = b;
-}
-
-template <typename Dd>
-__global__ void k_expand_order(const DevMesh m, const int32_t *order, const int8_t *bins, const int32_t *rank,
-                               int32_t *next) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)m.cap * Dd::NC) return;
-    const int n = (int)(e / Dd::NC), c = (int)(e - (int64_t)n * Dd::NC);
-    if (bins[n] != 0) return;
-    const int64_t at = (int64_t)rank[n] * Dd::NC + c;
-    if (at < m.cap) next[at] = m.nbrc[order[n]] + c;
-}
-
-template <typename Dd>
-void build_order(const Ctx &c) {
-    const int cap = c.m.cap;
-    for (int L = 0; L + 1 < c.m.lmax; L++) {
-        const int32_t *cur = c.order + (size_t)L * cap;
-        k_bins_order<<<grid_for(cap), 256, 0, c.stream>>>(c.m, cur, c.ctr, L, c.bins);
-        run_scan(c, c.bins, cap, 1);
-        k_expand_order<Dd><<<grid_for((int64_t)cap * Dd::NC), 256, 0, c.stream>>>(c.m, cur, c.bins, c.rank,
-                                                                                  c.order + (size_t)(L + 1) * cap);
+    __device__ void put(const DevMesh &m, DevCounters *, int64_t B, int b, int r, const int32_t *) const {
+        m.hid[B] = b == 0 ? r : -1;
     }
-}
+};
 
 // leaf blocks with a link into a solid block, per level in ID order (the
 // blocks whose momentum exchange is summed after each sweep)
-__global__ void k_bins_solid(const DevMesh m, int8_t *bins) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B >= m.cap) return;
-    bins[B] = (m.status[B] == ST_UNREF && (m.bflag[B] & BF_SOLID)) ? m.level[B] : int8_t(-1);
+struct SolidJob : BlockJob {
+    int32_t *list;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const {
+        return m.status[B] == ST_UNREF && (m.bflag[B] & BF_SOLID) ? m.level[B] : -1;
+    }
+    __device__ void put(const DevMesh &m, DevCounters *, int64_t B, int b, int r, const int32_t *) const {
+        if (b >= 0) list[(int64_t)b * m.cap + r] = (int32_t)B;
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const {
+        for (int L = 0; L < kMaxLevels; L++) ctr->nsolid[L] = L < K ? tot[L] : 0;
+    }
+};
+
+// output cells of each block: the list of the blocks that have any and their
+// exclusive offsets; with them a field read needs no pass over the mesh
+__device__ __forceinline__ int output_cells(const DevMesh &m, int64_t B, int mb) {
+    const uint64_t full = mb == 64 ? ~0ull : ((1ull << mb) - 1);
+    return m.status[B] == ST_UNREF ? (int)__popcll(~m.gmask[B] & full) : 0;
 }
 
-__global__ void k_solid_lists(const DevMesh m, const int8_t *bins, const int32_t *rank, int32_t *solidl,
-                              DevCounters *ctr) {
-    const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B < m.cap && bins[B] >= 0) solidl[(int64_t)bins[B] * m.cap + rank[B]] = B;
-    if (B == 0)
-        for (int L = 0; L < kMaxLevels; L++) ctr->nsolid[L] = L < m.lmax ? ctr->totals[L] : 0;
-}
+struct OutListJob : BlockJob {
+    int32_t *list;
+    int mb;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const { return output_cells(m, B, mb) > 0 ? 0 : -1; }
+    __device__ void put(const DevMesh &, DevCounters *, int64_t B, int b, int r, const int32_t *) const {
+        if (b == 0) list[r] = (int32_t)B;
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const { ctr->n_outb = tot[0]; }
+};
+
+struct OutOffsetJob : BlockJob {
+    static constexpr bool kSum = true;
+    int32_t *off;
+    int mb;
+    __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const { return output_cells(m, B, mb); }
+    __device__ void put(const DevMesh &, DevCounters *, int64_t B, int, int r, const int32_t *) const { off[B] = r; }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const { ctr->n_out = tot[0]; }
+};
+
+// the refined blocks of each ID set, and those of them that are interface parents
+template <bool IFACE>
+struct RefinedJob : LevelJob {
+    const int32_t *ids;
+    int32_t *list;
+    __device__ int bin(const DevMesh &m, const DevCounters *ctr, int64_t e) const {
+        const int L = (int)(e / m.cap), i = (int)(e - (int64_t)L * m.cap);
+        if (i >= ctr->nids[L]) return -1;
+        const int B = ids[e];
+        return (IFACE ? (m.bflag[B] & BF_PARENT_MASK) != 0 : is_refined(m.status[B])) ? L : -1;
+    }
+    __device__ void put(const DevMesh &m, DevCounters *, int64_t e, int b, int r, const int32_t *) const {
+        if (b >= 0) list[(int64_t)b * m.cap + r] = ids[e];
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const {
+        for (int L = 0; L < K; L++) (IFACE ? ctr->niface : ctr->nref)[L] = tot[L];
+    }
+};
+
+// Launch order of level L+1 from that of level L: the children of every
+// refined block, in its order (children are numbered as Morton digits).
+struct OrderJob : BlockJob {
+    const int32_t *order;
+    int32_t *next;
+    int L, nc;
+    __device__ int bin(const DevMesh &m, const DevCounters *ctr, int64_t n) const {
+        if (n >= ctr->nids[L]) return -1;
+        const int32_t first = m.nbrc[order[n]];
+        return first >= 0 && first < m.cap ? 0 : -1;
+    }
+    __device__ void put(const DevMesh &m, DevCounters *, int64_t n, int b, int r, const int32_t *) const {
+        if (b < 0) return;
+        const int32_t first = m.nbrc[order[n]];
+        for (int c = 0; c < nc; c++)
+            if ((int64_t)r * nc + c < m.cap) next[(int64_t)r * nc + c] = first + c;
+    }
+};
+
+// sweep list of level L: its launch order without the refined blocks none of
+// whose children has an N_SKIP link
+struct SweepJob : BlockJob {
+    const int32_t *order;
+    int32_t *list;
+    int L;
+    __device__ int bin(const DevMesh &m, const DevCounters *ctr, int64_t n) const {
+        if (n >= ctr->nids[L]) return -1;
+        const int B = order[n];
+        return is_refined(m.status[B]) && !(m.bflag[B] & BF_PARENT_MASK) ? -1 : 0;
+    }
+    __device__ void put(const DevMesh &, DevCounters *, int64_t n, int b, int r, const int32_t *) const {
+        if (b == 0) list[r] = order[n];
+    }
+    __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const { ctr->nsweep[L] = tot[0]; }
+};
 
 // Cells the interpolation and the averaging of each level move (for the
 // byte counts of the solver's kernel statistics): over the interface parents
 // of level L, the ghost cells of their children and the parent cells whose
 // first fine cell (even i, j, k) is an interface cell.
-__global__ void k_target_reset(DevCounters *ctr) {
-    if (threadIdx.x < kMaxLevels) {
-        ctr->ghost_w[threadIdx.x] = 0;
-        ctr->avg_w[threadIdx.x] = 0;
-    }
-}
-
 // One thread per interface parent of one level (grid y = level); the sums
 // are reduced over the wave before one atomic per wave.
 template <typename Dd>
@@ -845,99 +903,52 @@ __global__ __launch_bounds__(256) void k_target_cells(DevMesh m, const int32_t *
     }
 }
 
-// output cells of each block, their exclusive offsets and the list of the
-// blocks that have any: with them a field read needs no pass over the mesh
-void output_lists(const Ctx &c) {
-    const int cap = c.m.cap;
-    k_out_count<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.cnt, c.mb);
-    const int nwg = (int)((cap + kScanItems - 1) / kScanItems);
-    k_wscan_count<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part);
-    k_scan_part<<<1, 256, 0, c.stream>>>(c.scan_part, nwg, 1, c.ctr);
-    k_wscan_apply<<<nwg, kScanTPB, 0, c.stream>>>(c.cnt, cap, c.scan_part, c.off);
-    k_out_bins<<<grid_for(cap), 256, 0, c.stream>>>(c.cnt, c.off, cap, c.bins, c.ctr);
-    run_scan(c, c.bins, cap, 1);
-    k_out_list<<<grid_for(cap), 256, 0, c.stream>>>(c.bins, c.rank, cap, c.outl, c.ctr);
-}
-
 template <typename Dd>
 void masks_and_lists(const Ctx &c) {
-    const int cap = c.m.cap;
-    k_block_masks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
-    k_bins_halo<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins);
-    run_scan(c, c.bins, cap, 1);
-    k_set_hid<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins, c.rank);
+    const int cap = c.m.cap, lmax = c.m.lmax;
+    k_block_masks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.ctr);
     k_parent_mask<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
+    run_lists(c, HaloJob{}, SolidJob{{lmax}, c.solidl}, OutListJob{{1}, c.outl, c.mb}, OutOffsetJob{{1}, c.off, c.mb},
+              RefinedJob<true>{{lmax}, c.ids, c.iface}, RefinedJob<false>{{lmax}, c.ids, c.refl});
     k_block_desc<Dd><<<grid_for(cap, 64), 256, 0, c.stream>>>(c.m);
-    const int64_t tot = (int64_t)c.m.lmax * cap;
-    k_bins_keep<<<grid_for(tot), 256, 0, c.stream>>>(c.m, c.ids, c.ctr, c.bins, 1);
-    run_scan(c, c.bins, tot, c.m.lmax);
-    k_compact<<<grid_for(tot), 256, 0, c.stream>>>(c.bins, c.rank, c.ids, c.ids_tmp, cap, tot);
-    k_copy_lists<<<grid_for(tot), 256, 0, c.stream>>>(c.ids_tmp, c.iface, cap, c.m.lmax, c.ctr, 0);
-    k_bins_keep<<<grid_for(tot), 256, 0, c.stream>>>(c.m, c.ids, c.ctr, c.bins, 2);
-    run_scan(c, c.bins, tot, c.m.lmax);
-    k_compact<<<grid_for(tot), 256, 0, c.stream>>>(c.bins, c.rank, c.ids, c.ids_tmp, cap, tot);
-    k_copy_lists<<<grid_for(tot), 256, 0, c.stream>>>(c.ids_tmp, c.refl, cap, c.m.lmax, c.ctr, 2);
-    k_bins_solid<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins);
-    run_scan(c, c.bins, cap, c.m.lmax);
-    k_solid_lists<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins, c.rank, c.solidl, c.ctr);
-    build_order<Dd>(c);
-    // sweep lists: the launch order of each level without the refined blocks
-    // none of whose children has an N_SKIP link (bins over the order lists,
-    // which hold the same blocks as the ID sets)
-    k_bins_keep<<<grid_for(tot), 256, 0, c.stream>>>(c.m, c.order, c.ctr, c.bins, 3);
-    run_scan(c, c.bins, tot, c.m.lmax);
-    k_compact<<<grid_for(tot), 256, 0, c.stream>>>(c.bins, c.rank, c.order, c.ids_tmp, cap, tot);
-    k_copy_lists<<<grid_for(tot), 256, 0, c.stream>>>(c.ids_tmp, c.sweep, cap, c.m.lmax, c.ctr, 3);
-    k_target_reset<<<1, 64, 0, c.stream>>>(c.ctr);
-    k_target_cells<Dd><<<dim3(grid_for(cap), c.m.lmax), 256, 0, c.stream>>>(c.m, c.iface, c.ctr);
-    output_lists(c);
+    for (int L = 0; L < lmax; L++) {
+        const int32_t *cur = c.order + (size_t)L * cap;
+        const SweepJob sweep{{1}, cur, c.sweep + (size_t)L * cap, L};
+        if (L + 1 < lmax) run_lists(c, OrderJob{{1}, cur, c.order + (size_t)(L + 1) * cap, L, Dd::NC}, sweep);
+        else run_lists(c, sweep);
+    }
+    k_target_cells<Dd><<<dim3(grid_for(cap), lmax), 256, 0, c.stream>>>(c.m, c.iface, c.ctr);
 }
 
 template <typename Dd>
 void init_mesh_t(const Ctx &c) {
     const int cap = c.m.cap;
-    k_init_blocks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, root_params(c), c.solid, c.bins);
+    k_init_blocks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, root_params(c), c.solid);
     if (cap > c.nroot) k_init_gap<<<grid_for(cap - c.nroot), 256, 0, c.stream>>>(c.gap, cap, c.nroot);
-    run_scan(c, c.bins, cap, 1);
-    k_init_ids<<<grid_for(cap), 256, 0, c.stream>>>(c.bins, c.rank, cap, c.ids, c.ctr, c.nroot);
+    run_lists(c, InitJob{{1}, c.ids, c.nroot});
     masks_and_lists<Dd>(c);
 }
 
 template <typename Dd>
 void adapt_assign_t(const Ctx &c, int n_ref) {
     const int cap = c.m.cap;
-    k_bins_refine<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins, 0);
-    run_scan(c, c.bins, cap, 1);
-    k_assign_first<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.rank, c.gap, c.ctr, c.first, c.rlist, Dd::NC);
-    k_gtop_add<<<1, 64, 0, c.stream>>>(c.ctr, -Dd::NC * n_ref, 0);
-    k_violating<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.first);
+    run_lists(c, RefineJob{{1}, c.gap, c.first, c.rlist, Dd::NC});
+    k_violating<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.first, c.ctr, Dd::NC * n_ref);
     k_revert<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.ctr);
 }
 
 template <typename Dd>
 void adapt_build_t(const Ctx &c, int n_ref) {
-    const int cap = c.m.cap;
-    const int64_t tot = (int64_t)c.m.lmax * cap;
+    const int cap = c.m.cap, lmax = c.m.lmax;
     // S4
     if (n_ref > 0) k_build_children<Dd><<<grid_for((int64_t)n_ref * Dd::NC), 256, 0, c.stream>>>(c.m, c.rlist, c.first, n_ref);
     // S5
-    k_zero_freed<<<1, 64, 0, c.stream>>>(c.ctr);
-    k_bins_coarsen<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins);
-    run_scan(c, c.bins, cap, c.m.lmax);
-    k_coarsen<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.rank, c.gap, c.ctr);
-    k_gtop_add<<<1, 64, 0, c.stream>>>(c.ctr, 0, 1);
-    k_bins_keep<<<grid_for(tot), 256, 0, c.stream>>>(c.m, c.ids, c.ctr, c.bins, 0);
-    run_scan(c, c.bins, tot, c.m.lmax);
-    k_compact<<<grid_for(tot), 256, 0, c.stream>>>(c.bins, c.rank, c.ids, c.ids_tmp, cap, tot);
-    k_copy_lists<<<grid_for(tot), 256, 0, c.stream>>>(c.ids_tmp, c.ids, cap, c.m.lmax, c.ctr, 1);
+    run_lists(c, CoarsenJob{{lmax}, c.gap, Dd::NC});
+    run_lists(c, KeepJob{{lmax}, c.ids, c.ids_tmp});
+    k_copy_kept<<<grid_for((int64_t)lmax * cap), 256, 0, c.stream>>>(c.ids_tmp, c.ids, cap, lmax, c.ctr);
     // S6
-    if (n_ref > 0) {
-        k_bins_refine<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.bins, 1);
-        run_scan(c, c.bins, cap, c.m.lmax);
-        k_append<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.rank, c.first, c.ids, c.ctr);
-        k_nids_after_append<Dd><<<1, 64, 0, c.stream>>>(c.ctr, c.m.lmax);
-    }
-    k_finalize_status<<<grid_for(cap), 256, 0, c.stream>>>(c.m);
+    if (n_ref > 0) run_lists(c, AppendJob{{lmax}, c.first, c.ids, Dd::NC});
+    k_finalize_status<<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.ctr, n_ref > 0 ? Dd::NC : 0);
     k_branch_leaf<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
 }
 

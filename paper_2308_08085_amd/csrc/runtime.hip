@@ -112,12 +112,10 @@ void make_layout(const amr_config *c, Layout *L) {
     L->gap = take(cap * 4);
     L->first = take(cap * 4);
     L->rlist = take(cap * 4);
-    L->clist = take(cap * 4);
-    L->cnt = take(cap * 4);
+    L->outl = take(cap * 4);
     L->off = take(cap * 4);
-    L->rank = take(lmax * cap * 4);
-    L->bins = take(lmax * cap);
-    L->scan_part = take(((lmax * cap + 1023) / 1024 + 1) * kMaxLevels * 4);
+    // six lists at once, each at most kMaxLevels counts per 1024 indexes and one more
+    L->scan_part = take(6 * ((lmax * cap + 1023) / 1024 + 1) * kMaxLevels * 4);
     L->crit = take(cap * 8);
     L->part4 = take(cap * 32);
     L->solid = take(nroot);
@@ -374,12 +372,8 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
     c.gap = (int32_t *)(a + lay.gap);
     c.first = (int32_t *)(a + lay.first);
     c.rlist = (int32_t *)(a + lay.rlist);
-    c.clist = (int32_t *)(a + lay.clist);
-    c.cnt = (int32_t *)(a + lay.cnt);
     c.off = (int32_t *)(a + lay.off);
-    c.outl = c.cnt;
-    c.rank = (int32_t *)(a + lay.rank);
-    c.bins = (int8_t *)(a + lay.bins);
+    c.outl = (int32_t *)(a + lay.outl);
     c.scan_part = (int32_t *)(a + lay.scan_part);
     c.crit = (double *)(a + lay.crit);
     c.part4 = (double *)(a + lay.part4);

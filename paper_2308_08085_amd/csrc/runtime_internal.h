@@ -25,7 +25,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
     size_t f[2], nbr, nbrc, X, level, status, tag, ldes, viol, bflag, gmask, imask;
-    size_t ids, ids_tmp, iface, refl, sweep, order, force, solidl, gap, first, rlist, clist, cnt, off, rank, bins, scan_part;
+    size_t ids, ids_tmp, iface, refl, sweep, order, force, solidl, gap, first, rlist, outl, off, scan_part;
     size_t crit, part4, solid, solid_list, ctr, staging, staging_bytes, total, hid, U, parent, fresh, desc;
 };
 
