@@ -206,7 +206,8 @@ __device__ __forceinline__ void gather_interior(const InteriorLane &u, typename 
 // workgroup (three barriers, one cache line per link and block) and a branch
 // per population for blocks with walls or coarser neighbours, a D3Q27 sweep of
 // the cylinder (4.2e5 blocks) took 1,360 us with FP32 and 871 us with FP16
-// storage, now 1,297 and 744 us (4.55 and 4.00 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0, now
+// storage, now 1,297 and 744 us (1,258 and 741 with
+// the wave limit of collide_waves: 4.67 and 4.01 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0, now
 // 30.2 us; a D2Q9 FP64 sweep of 64 blocks 7.2, now 5.3 us; a coarse step of 32
 // mixed cavities in a batch 870, now 700 us.  An entry whose link is not a block holds the link code,
 // sign extended, so it is negative as an int64.
@@ -601,13 +602,21 @@ __device__ void stage_blocks(const DevMesh &m, BlockStage<Lt, NBLK> &st) {
 }
 
 // Contiguous range of work units [u0, u1) of a persistent workgroup: the
-// count is read on the device, so one launch shape serves every mesh.
+// count is read on the device, so one launch shape serves every mesh.  With
+// fewer units than workgroups only the first `units` workgroups work, which
+// dispatch spreads over the XCDs, and shares differ by one unit at most.  When
+// the ranges were numbered over the whole grid, the units of a small level
+// went to the first XCDs only: D2Q9 sweeps of the 16 cavities of a batch 9.4,
+// now 6.6 us, their interpolation 7.3 and 5.4, averaging 6.9 and 5.0; a batch
+// of 32 mixed cavities, 50 coarse steps, 30.0 and 26.3 ms.
 __device__ inline void persistent_range(int units, int &u0, int &u1) {
-    const int G = gridDim.x;
+    const int G = min((int)gridDim.x, units);
+    u0 = u1 = 0;
+    if ((int)blockIdx.x >= G) return;
     const int wg = xcd_remap(blockIdx.x, G);
-    const int per = (units + G - 1) / G;
-    u0 = min(units, wg * per);
-    u1 = min(units, u0 + per);
+    const int per = units / G, more = units - per * G;
+    u0 = wg * per + min(wg, more);
+    u1 = u0 + per + (wg < more ? 1 : 0);
 }
 
 // Read-only view of the batch descriptors in the constant address space: with
@@ -2239,8 +2248,7 @@ void Launch<Q, S>::exchange_batch(hipStream_t stream, const SimDesc *sims, const
 
 // Workgroups of a persistent launch: wg_per_cu per compute unit, but no more
 // than fit at a time.  The workgroups share the items evenly, so those that
-// start when others have ended would double the launch: D3Q19 sweeps of 28,000
-// blocks with 8 asked and 6 resident workgroups per unit took 35 us, now 25 us.
+// start only when others have ended would double the launch.
 template <typename K>
 static int resident(K kernel, int threads) {
     int fit = 0;
