@@ -206,11 +206,11 @@ __device__ __forceinline__ void gather_interior(const InteriorLane &u, typename 
 // workgroup (three barriers, one cache line per link and block) and a branch
 // per population for blocks with walls or coarser neighbours, a D3Q27 sweep of
 // the cylinder (4.2e5 blocks) took 1,360 us with FP32 and 871 us with FP16
-// storage, now 1,297 and 744 us (1,258 and 741 with
-// the wave limit of collide_waves: 4.67 and 4.01 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0, now
-// 30.2 us; a D2Q9 FP64 sweep of 64 blocks 7.2, now 5.3 us; a coarse step of 32
-// mixed cavities in a batch 870, now 700 us.  An entry whose link is not a block holds the link code,
-// sign extended, so it is negative as an int64.
+// storage, now 1,297 and 744 us (1,258 and 741 with the wave limit of
+// collide_waves: 4.67 and 4.01 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0,
+// now 30.2 us; a D2Q9 FP64 sweep of 64 blocks 7.2, now 5.3 us; a coarse step of
+// 32 mixed cavities in a batch 870, now 700 us.  An entry whose link is not a
+// block holds the link code, sign extended, so it is negative as an int64.
 template <typename Lt> constexpr int kTab = Desc<Lt::D>::kWords;  // table entries per block
 
 // orders the LDS writes of a wave before its later LDS reads
@@ -2193,8 +2193,12 @@ bool Launch<Q, S>::collide_stream(const Ctx &c, const int32_t *list, int n, int 
             }
         }
     }
-    if (exchange && !nts) {
-        k_collide_stream<Q, S, false, 0, true><<<grid, tpb, 0, c.stream>>>(list, n, c.m, src, dst, om, bc, om);
+    // The sweep that adds the momentum exchange itself costs no wave per SIMD with
+    // streaming stores, and saves a pass over the solid neighbours per sweep: half-size
+    // D3Q27 channel, FP16, 36.6 -> 35.4 ms for 32 coarse steps, full size FP32 663 -> 658 for 64.
+    if (exchange) {
+        if (nts) k_collide_stream<Q, S, true, 0, true><<<grid, tpb, 0, c.stream>>>(list, n, c.m, src, dst, om, bc, om);
+        else k_collide_stream<Q, S, false, 0, true><<<grid, tpb, 0, c.stream>>>(list, n, c.m, src, dst, om, bc, om);
         return true;
     }
     if (nts) k_collide_stream<Q, S, true><<<grid, tpb, 0, c.stream>>>(list, n, c.m, src, dst, om, bc, om);

@@ -167,9 +167,8 @@ void timed_launch(amr_handle *h, int kind, int blocks, int L, F &&fn) {
 }
 
 // Outside profiled runs (which time each kernel on its own) BGK sweeps save
-// launch gaps (~10 us each): a sweep with ordinary stores adds the momentum
-// exchange itself (the variant needs at most 3 more VGPRs, with no loss of
-// occupancy), and on small levels the ghost interpolation into level L+1 joins
+// launch gaps: a sweep adds the momentum exchange itself (the variant needs at
+// most 7 more VGPRs), and on small levels the ghost interpolation into level L+1 joins
 // the sweep.  Large levels keep the interpolation apart: the joined kernel
 // needs more registers (99 VGPRs for D3Q27 at 16-bit storage against 68) and
 // their launches are long.
