@@ -225,7 +225,7 @@ def run_batch(steps, warmup, theta, trial_steps=2):
         tot_u += u
         tot_ms += ms
         tot_a += ams
-    # the same members one after another, each replaying its own graph
+    # the same members one after another, each stepping on its own
     u = updates()
     for g in sims:  # capture outside the timed region
         g.step(2, graph=True)
