@@ -20,7 +20,6 @@ struct DevCounters {
     int32_t pad[1];
     unsigned long long wmax_bits;
     int32_t totals[kMaxLevels];  // of the last list of an adaptation
-    int32_t pad2[kMaxLevels];
     double mass[4];
     // cells the solver's grid communication moves from level L, per coarse
     // step of L: ghost cells its interpolation writes into level L+1, parent
