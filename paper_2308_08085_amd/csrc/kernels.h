@@ -47,7 +47,7 @@ struct Ctx {
     int32_t *order;      // [lmax][cap] solver launch order per level (Morton)
     int32_t *solidl;     // [lmax][cap] leaf blocks next to a solid block, per level
     int32_t *gap;        // [cap]
-    int32_t *first;      // [cap]
+    int32_t *first;      // [cap] first new child; once these are in place, the halo records' numbers before the change
     int32_t *rlist;      // [cap]
     int32_t *scan_part;  // counts of the ordered lists
     int32_t *off;        // [cap] first output cell of each block
@@ -80,6 +80,10 @@ void launch_interp(const Ctx &c, const int32_t *list, int n, const LevelParams &
 // after new children (parents in `list`) were interpolated: the populations of
 // existing same-level neighbour cells that now stream from the new blocks
 void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
+// halo records to their new numbers (m.hid), with what streamed in from blocks
+// that this mesh change removed; old: their numbers before.  After the new
+// numbers, before the new descriptors.
+void launch_move_records(const Ctx &c, const int32_t *old);
 // list: refined blocks of level L; mode 0: interface parent cells; 1: every parent cell
 // U (all_cells = 1): the averaging also writes the criterion velocities of
 // the children it reads that have no N_SKIP link

@@ -1312,6 +1312,71 @@ __global__ __launch_bounds__(256) void k_refresh_neighbours(const int32_t *__res
     }
 }
 
+// Halo records across a mesh change.  Records are numbered in block order, so
+// a block that stays (not new) may have another number than before; and where
+// its neighbour C was removed, the populations that streamed from C's cells are
+// in C's rows and belong to the record from now on.  The next step's ghost
+// fill rewrites all of it, but a synchronisation may come first, and its
+// averaging reads it.  BACK = false: what the block needs, to its new number in
+// the buffer that is free between steps; true: back from there.  (Not moved,
+// records held another block's values or zeros after a change that no step
+// followed.  Records at the block's own ID would not have to move, but so
+// spread out they cost the steps of the 64^3 D3Q19 cavity 2 to 4 %.)
+//
+// 64 block IDs per workgroup: their numbers in one coalesced read, then each
+// block that has something to move by one wave.  Bound by their launches, two
+// beside the 31 others of a mesh change with three levels.
+template <int Q, int S, bool BACK>
+__global__ __launch_bounds__(256) void k_move_records(DevMesh m, const DevCounters *ctr, const int32_t *__restrict__ old,
+                                                      const typename Store<S>::T *__restrict__ src,
+                                                      typename Store<S>::T *__restrict__ dst) {
+    using Lt = Lat<Q>;
+    using De = Desc<Lt::D>;
+    __shared__ int32_t links[4][De::kLinks];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int B0 = blockIdx.x * 64;
+    // a number that stays may still gain entries from a removed block
+    const bool removed = ctr->nfreed > 0;
+    int now = -1, was = -1;
+    if (B0 + lane < m.cap) {
+        now = m.hid[B0 + lane];
+        was = old[B0 + lane];
+    }
+    const bool move = now >= 0 && (removed || now != was) && !m.fresh[B0 + lane];
+    int k = 0;
+    for (uint64_t todo = __ballot(move); todo; todo &= todo - 1) {
+        if ((k++ & 3) != wave) continue;
+        const int i = __builtin_ctzll(todo), B = B0 + i;
+        const int nw = __shfl(now, i, 64), wa = __shfl(was, i, 64);
+        // the links before the change: N_SKIP, a block that was removed, or nothing to move
+        int32_t w = kNone;
+        if (lane < De::kLinks) {
+            w = m.desc[(int64_t)B * De::kWords + lane];
+            if (w >= 0) w = m.status[w] == ST_INACTIVE ? w : kNone;
+            else if (w != kNSkip || wa < 0 || wa == nw) w = kNone;
+            links[wave][lane] = w;
+        }
+        if (!__any(w != kNone)) continue;
+        wave_lds_sync();
+        typedef typename Store<S>::T T;
+        T *rec = dst + (m.halo_base + (int64_t)nw * m.nh);
+        const T *at = src + (m.halo_base + (int64_t)(BACK ? nw : wa) * m.nh);
+        if (lane < Lt::MB)
+            static_for<Q>([&](auto pc) {
+                constexpr int p = decltype(pc)::value;
+                const int sx = (lane & 3) - Lt::cx(p), sy = ((lane >> 2) & 3) - Lt::cy(p), sz = (lane >> 4) - Lt::cz(p);
+                const int rg = region_of<Lt>(sx, sy, sz);
+                const int32_t code = rg == kCenterSlot<Lt> ? kNone : links[wave][rg];
+                if (code != kNone) {
+                    const uint32_t e = halo_entry<Lt, p>((uint64_t(1) << lane) - 1);
+                    rec[e] = BACK || code < 0 ? at[e]
+                                              : src[mslot<Lt>(code, p, (sx & 3) + 4 * (sy & 3) + 16 * (sz & 3))];
+                }
+            });
+        wave_lds_sync();
+    }
+}
+
 static __global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, DevMesh m, int nc) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n * nc) return;
@@ -2141,6 +2206,7 @@ struct Launch {
     static void average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                               int L, int par0, int par1, const BatchShape &s);
     static void refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
+    static void move_records(const Ctx &c, const int32_t *old);
     static void average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
                         double *U);
     static void fill_rest(const Ctx &c);
@@ -2301,6 +2367,15 @@ void Launch<Q, S>::refresh_neighbours(const Ctx &c, const int32_t *list, int n, 
     k_refresh_neighbours<Q, S><<<n, threads, 0, c.stream>>>(list, n, c.m, buf<S>(c, 0), buf<S>(c, 1), lp);
 }
 
+// Buffers: mesh changes come between coarse steps, when every level above 0 is
+// back in buffer 0; level 0 has no records.
+template <int Q, int S>
+void Launch<Q, S>::move_records(const Ctx &c, const int32_t *old) {
+    const int grid = (c.m.cap + 63) / 64;
+    k_move_records<Q, S, false><<<grid, 256, 0, c.stream>>>(c.m, c.ctr, old, buf<S>(c, 0), buf<S>(c, 1));
+    k_move_records<Q, S, true><<<grid, 256, 0, c.stream>>>(c.m, c.ctr, old, buf<S>(c, 1), buf<S>(c, 0));
+}
+
 template <int Q, int S>
 void Launch<Q, S>::average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
                            double *U) {
@@ -2429,6 +2504,10 @@ void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const L
     if (n <= 0) return;
     dispatch(c.q, c.storage, [&](auto l) { l.refresh_neighbours(c, list, n, lp); });
     k_clear_fresh<<<(n * c.nc + 255) / 256, 256, 0, c.stream>>>(list, n, c.m, c.nc);
+}
+
+void launch_move_records(const Ctx &c, const int32_t *old) {
+    dispatch(c.q, c.storage, [&](auto l) { l.move_records(c, old); });
 }
 
 void launch_average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells, double *U) {

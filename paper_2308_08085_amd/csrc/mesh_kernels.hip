@@ -764,12 +764,15 @@ RootParams root_params(const Ctx &c) {
     return rp;
 }
 
-// halo records: one per active block with an N_SKIP link, numbered in block-ID order
+// halo records: one per active block with an N_SKIP link, numbered in block-ID
+// order; the numbers before go to `old`
 struct HaloJob : BlockJob {
+    int32_t *old;
     __device__ int bin(const DevMesh &m, const DevCounters *, int64_t B) const {
         return m.status[B] != ST_INACTIVE && (m.bflag[B] & BF_NSKIP) ? 0 : -1;
     }
     __device__ void put(const DevMesh &m, DevCounters *, int64_t B, int b, int r, const int32_t *) const {
+        old[B] = m.hid[B];
         m.hid[B] = b == 0 ? r : -1;
     }
 };
@@ -903,13 +906,15 @@ __global__ __launch_bounds__(256) void k_target_cells(DevMesh m, const int32_t *
     }
 }
 
+// changed: the mesh was another one before, whose descriptors are still there
 template <typename Dd>
-void masks_and_lists(const Ctx &c) {
+void masks_and_lists(const Ctx &c, bool changed) {
     const int cap = c.m.cap, lmax = c.m.lmax;
     k_block_masks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, c.ctr);
     k_parent_mask<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
-    run_lists(c, HaloJob{}, SolidJob{{lmax}, c.solidl}, OutListJob{{1}, c.outl, c.mb}, OutOffsetJob{{1}, c.off, c.mb},
+    run_lists(c, HaloJob{{1}, c.first}, SolidJob{{lmax}, c.solidl}, OutListJob{{1}, c.outl, c.mb}, OutOffsetJob{{1}, c.off, c.mb},
               RefinedJob<true>{{lmax}, c.ids, c.iface}, RefinedJob<false>{{lmax}, c.ids, c.refl});
+    if (changed) launch_move_records(c, c.first);
     k_block_desc<Dd><<<grid_for(cap, 64), 256, 0, c.stream>>>(c.m);
     for (int L = 0; L < lmax; L++) {
         const int32_t *cur = c.order + (size_t)L * cap;
@@ -926,7 +931,7 @@ void init_mesh_t(const Ctx &c) {
     k_init_blocks<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m, root_params(c), c.solid);
     if (cap > c.nroot) k_init_gap<<<grid_for(cap - c.nroot), 256, 0, c.stream>>>(c.gap, cap, c.nroot);
     run_lists(c, InitJob{{1}, c.ids, c.nroot});
-    masks_and_lists<Dd>(c);
+    masks_and_lists<Dd>(c, false);
 }
 
 template <typename Dd>
@@ -960,7 +965,7 @@ void connectivity_t(const Ctx &c) {
         if (L < c.m.lmax - 1)
             k_child_links<Dd><<<grid_for((int64_t)cap * Dd::NC), 256, 0, c.stream>>>(c.m, c.ids, c.ctr, L);
     }
-    masks_and_lists<Dd>(c);
+    masks_and_lists<Dd>(c, true);
 }
 
 template <typename Dd>
