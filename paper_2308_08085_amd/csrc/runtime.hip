@@ -762,13 +762,14 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         if (total + kHeadBytes <= kPinBytes) chunk = (size_t)h->n_outb * row * mb + kHeadBytes;  // in one
         const int per = std::max(1, (int)((chunk - kHeadBytes) / (row * mb)));
         s = transfer_out(
-            h, (h->n_outb + per - 1) / per, total,
+            h, buf, (h->n_outb + per - 1) / per, total,
             [&](int i, char *to) {
                 launch_out_gather(c, kind, i * per, std::min(h->n_outb, (i + 1) * per), h->n_outb, h->n_out,
                                   (int64_t *)to, to + kHeadBytes, lp);
+                return hipGetLastError();
             },
             [&](int, const int64_t *head) {
-                return Piece{(char *)buf + (size_t)head[0] * row, kHeadBytes, (size_t)head[1] * row};
+                return Piece{(uint64_t)head[0] * row, kHeadBytes, (size_t)head[1] * row};
             });
         return s == AMR_OK ? sync_checked(h) : s;
     }
@@ -779,10 +780,13 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             const int per = std::max(1, (int)(transfer_chunk(h, cap * row) / row));
             const auto end = [&](int i) { return std::min((int)cap, (i + 1) * per); };
             s = transfer_out(
-                h, ((int)cap + per - 1) / per, cap * row,
-                [&](int i, char *to) { launch_block_f(c, 0, i * per, end(i), (double *)to, lp); },
+                h, buf, ((int)cap + per - 1) / per, cap * row,
+                [&](int i, char *to) {
+                    launch_block_f(c, 0, i * per, end(i), (double *)to, lp);
+                    return hipGetLastError();
+                },
                 [&](int i, const int64_t *) {
-                    return Piece{(char *)buf + (size_t)i * per * row, 0, (size_t)(end(i) - i * per) * row};
+                    return Piece{(uint64_t)i * per * row, 0, (size_t)(end(i) - i * per) * row};
                 });
             return s == AMR_OK ? sync_checked(h) : s;
         }

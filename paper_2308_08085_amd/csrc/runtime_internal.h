@@ -76,24 +76,28 @@ LevelParams level_params(const amr_handle *h);
 // ---- device to host (transfer.hip) ----
 constexpr size_t kPinBytes = size_t(64) << 10, kSlotBytes = size_t(4) << 20, kHeadBytes = 64;
 
-// where a filled chunk goes: `bytes` from `offset` in the chunk to host memory
+// where a filled chunk goes: `bytes` from `offset` in the chunk to byte `at` of
+// the destination
 struct Piece {
-    char *dst;
+    uint64_t at;
     size_t offset, bytes;
 };
 
 void transfer_add_user(amr_handle *h);   // with the handle's creation
 void transfer_drop_user(amr_handle *h);  // with its end
 size_t transfer_chunk(const amr_handle *h, uint64_t total);  // chunk size for a transfer of `total` bytes
-// n chunks of at most transfer_chunk() bytes: fill(i, to) enqueues what writes
-// chunk i to `to` (pinned host or device memory) on the handle's stream, and
+// n chunks of at most transfer_chunk() bytes to the `total` bytes at dst:
+// fill(i, to) enqueues what writes chunk i to `to` (pinned host or device
+// memory) on the handle's stream and returns whether that was accepted, and
 // piece(i, head) says where it goes, given the chunk's first kHeadBytes.
 // Without pinned memory: `plain`, if given, enqueues the whole transfer, else
-// the chunks go through the staging area.  Synchronises the stream.
-amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::function<void(int, char *)> &fill,
+// the chunks go through the staging area.  Synchronises the stream.  Fails, with
+// nothing moved, if an earlier launch was refused, and never writes outside dst.
+amr_status transfer_out(amr_handle *h, void *dst, int n, uint64_t total,
+                        const std::function<hipError_t(int, char *)> &fill,
                         const std::function<Piece(int, const int64_t *)> &piece,
                         const std::function<hipError_t()> &plain = nullptr);
-// a range of device memory to pageable host memory; synchronises the stream
+// a range of device memory to pageable host memory, as transfer_out
 amr_status copy_out(amr_handle *h, void *dst, const void *dev, size_t bytes);
 
 

@@ -57,15 +57,15 @@ class Workers {
         ready_.notify_all();
         for (auto &t : threads_) t.join();
     }
-    void give(int i, const Piece &p, const char *from) {
+    void give(int i, const Piece &p, const char *from, char *dst) {
         if (threads_.empty()) {
-            memcpy(p.dst, from + p.offset, p.bytes);
+            memcpy(dst + p.at, from + p.offset, p.bytes);
             done_[i] = 1;
             return;
         }
         {
             std::lock_guard<std::mutex> l(m_);
-            jobs_.push_back({i, p, from});
+            jobs_.push_back({i, p, from, dst});
         }
         ready_.notify_one();
     }
@@ -83,6 +83,7 @@ class Workers {
         int i;
         Piece p;
         const char *from;
+        char *dst;
     };
     void loop() {
         std::unique_lock<std::mutex> l(m_);
@@ -91,7 +92,7 @@ class Workers {
             if (next_ >= jobs_.size()) return;
             const Job j = jobs_[next_++];
             l.unlock();
-            memcpy(j.p.dst, j.from + j.p.offset, j.p.bytes);
+            memcpy(j.dst + j.p.at, j.from + j.p.offset, j.p.bytes);
             l.lock();
             done_[j.i] = 1;
             moved_.notify_all();
@@ -106,41 +107,54 @@ class Workers {
     std::vector<std::thread> threads_;
 };
 
+// whether a piece of a chunk lies in the chunk and in the destination
+bool fits(const Piece &p, uint64_t total, size_t chunk) {
+    return p.at <= total && p.bytes <= total - p.at && p.offset <= chunk && p.bytes <= chunk - p.offset;
+}
+amr_status misfit(const Piece &p, uint64_t total) {
+    return fail(AMR_ERR_DEVICE, "field transfer: %llu bytes at %llu of %llu", (unsigned long long)p.bytes,
+                (unsigned long long)p.at, (unsigned long long)total);
+}
+
 // through the ring (held by the caller)
-amr_status through_ring(amr_handle *h, int n, uint64_t total, const std::function<void(int, char *)> &fill,
+amr_status through_ring(amr_handle *h, char *dst, int n, uint64_t total,
+                        const std::function<hipError_t(int, char *)> &fill,
                         const std::function<Piece(int, const int64_t *)> &piece) {
     hipStream_t st = h->c.stream;
     const int slots = n < kSlots ? n : kSlots;
     hipEvent_t ev[kSlots] = {nullptr};
     hipError_t e = hipSuccess;
+    amr_status s = AMR_OK;
     for (int k = 0; k < slots && e == hipSuccess; k++) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
     try {
         const uint64_t want = total / kWorkerBytes;
         Workers w(n, n > 1 && want > 1 ? (int)(want < kMaxWorkers ? want : kMaxWorkers) : 0);
         int launched = 0;
-        for (int i = 0; i < n && e == hipSuccess; i++) {
+        for (int i = 0; i < n && e == hipSuccess && s == AMR_OK; i++) {
             while (launched < n && launched < i + slots && e == hipSuccess) {
                 const int before = launched - slots;  // the chunk this slot held
                 if (before >= 0 && !w.done(before)) {
                     if (launched > i) break;
                     w.wait(before);
                 }
-                fill(launched, g_ring.mem + (size_t)(launched % slots) * kSlotBytes);
-                e = hipEventRecord(ev[launched % slots], st);
+                e = fill(launched, g_ring.mem + (size_t)(launched % slots) * kSlotBytes);
+                if (e == hipSuccess) e = hipEventRecord(ev[launched % slots], st);
                 launched++;
             }
             if (e == hipSuccess) e = hipEventSynchronize(ev[i % slots]);
             if (e != hipSuccess) break;
             const char *from = g_ring.mem + (size_t)(i % slots) * kSlotBytes;
-            w.give(i, piece(i, (const int64_t *)from), from);
+            const Piece p = piece(i, (const int64_t *)from);
+            if (fits(p, total, kSlotBytes)) w.give(i, p, from, dst);
+            else s = misfit(p, total);
         }
     } catch (...) {
         e = hipErrorOutOfMemory;
     }
-    if (e != hipSuccess) hipStreamSynchronize(st);  // nothing writes the ring once it is free again
+    if (e != hipSuccess || s != AMR_OK) (void)hipStreamSynchronize(st);  // nothing writes the ring once it is free again
     for (int k = 0; k < slots; k++)
         if (ev[k]) hipEventDestroy(ev[k]);
-    return e == hipSuccess ? AMR_OK : fail(AMR_ERR_DEVICE, "field transfer: %s", hipGetErrorString(e));
+    return e == hipSuccess ? s : fail(AMR_ERR_DEVICE, "field transfer: %s", hipGetErrorString(e));
 }
 
 }  // namespace
@@ -167,11 +181,18 @@ size_t transfer_chunk(const amr_handle *h, uint64_t total) {
     return c < h->c.staging_bytes ? c : h->c.staging_bytes;
 }
 
-amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::function<void(int, char *)> &fill,
+amr_status transfer_out(amr_handle *h, void *dst_, int n, uint64_t total,
+                        const std::function<hipError_t(int, char *)> &fill,
                         const std::function<Piece(int, const int64_t *)> &piece,
                         const std::function<hipError_t()> &plain) {
     hipStream_t st = h->c.stream;
-    if (n <= 0) return AMR_OK;
+    char *dst = (char *)dst_;
+    // a kernel that was to make the data and was refused: no later call says so
+    HIP_TRY(hipGetLastError());
+    if (n <= 0) {
+        HIP_TRY(hipStreamSynchronize(st));
+        return AMR_OK;
+    }
     h->read_total += total;
     if (!h->pin && ++h->reads == kPinFrom) {
         void *p = nullptr;
@@ -179,10 +200,11 @@ amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::functio
         else (void)hipGetLastError();
     }
     if (n == 1 && total + kHeadBytes <= kPinBytes && h->pin) {
-        fill(0, h->pin);
+        HIP_TRY(fill(0, h->pin));
         HIP_TRY(hipStreamSynchronize(st));
         const Piece p = piece(0, (const int64_t *)h->pin);
-        memcpy(p.dst, h->pin + p.offset, p.bytes);
+        if (!fits(p, total, kPinBytes)) return misfit(p, total);
+        memcpy(dst + p.at, h->pin + p.offset, p.bytes);
         return AMR_OK;
     }
     std::unique_lock<std::mutex> use(g_ring.use, std::try_to_lock);
@@ -192,7 +214,7 @@ amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::functio
             if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess) g_ring.mem = (char *)p;
             else (void)hipGetLastError();
         }
-        if (g_ring.mem) return through_ring(h, n, total, fill, piece);
+        if (g_ring.mem) return through_ring(h, dst, n, total, fill, piece);
         use.unlock();
     }
     if (plain) {
@@ -202,28 +224,27 @@ amr_status transfer_out(amr_handle *h, int n, uint64_t total, const std::functio
     }
     for (int i = 0; i < n; i++) {  // through the staging area and the runtime's own pinned memory
         int64_t head[kHeadBytes / 8];
-        fill(i, (char *)h->c.staging);
+        HIP_TRY(fill(i, (char *)h->c.staging));
         HIP_TRY(hipMemcpyAsync(head, h->c.staging, sizeof(head), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         const Piece p = piece(i, head);
-        HIP_TRY(hipMemcpyAsync(p.dst, (char *)h->c.staging + p.offset, p.bytes, hipMemcpyDeviceToHost, st));
+        if (!fits(p, total, h->c.staging_bytes)) return misfit(p, total);
+        HIP_TRY(hipMemcpyAsync(dst + p.at, (char *)h->c.staging + p.offset, p.bytes, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
     }
     return AMR_OK;
 }
 
 amr_status copy_out(amr_handle *h, void *dst, const void *dev, size_t bytes) {
-    if (bytes == 0) return AMR_OK;
     hipStream_t st = h->c.stream;
     const size_t chunk = bytes + kHeadBytes <= kPinBytes ? bytes : transfer_chunk(h, bytes);
     const auto size = [&](int i) { return bytes - (size_t)i * chunk < chunk ? bytes - (size_t)i * chunk : chunk; };
-    // (a failed copy is reported by the synchronisation that follows)
     return transfer_out(
-        h, (int)((bytes + chunk - 1) / chunk), bytes,
+        h, dst, bytes ? (int)((bytes + chunk - 1) / chunk) : 0, bytes,
         [&](int i, char *to) {
-            (void)hipMemcpyAsync(to, (const char *)dev + (size_t)i * chunk, size(i), hipMemcpyDefault, st);
+            return hipMemcpyAsync(to, (const char *)dev + (size_t)i * chunk, size(i), hipMemcpyDefault, st);
         },
-        [&](int i, const int64_t *) { return Piece{(char *)dst + (size_t)i * chunk, 0, size(i)}; },
+        [&](int i, const int64_t *) { return Piece{(uint64_t)i * chunk, 0, size(i)}; },
         [&] { return hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, st); });
 }
 
