@@ -532,7 +532,7 @@ amr_status amr_tag(amr_t *h, const amr_tag_params *p, const int8_t *tags_in, int
     launch_crit_reset(c);
     if (tags_in) {
         const void *from = tags_in;
-        if (h->pin && cap <= kPinBytes) from = memcpy(h->pin, tags_in, cap);  // read before this call returns
+        if (h->pin && cap <= kPinBytes && host_memory(tags_in)) from = memcpy(h->pin, tags_in, cap);  // read before this call returns
         HIP_TRY(hipMemcpyAsync(c.m.tag, from, cap, hipMemcpyHostToDevice, c.stream));
     } else if (p->kind == AMR_TAG_VORTICITY_REL || p->kind == AMR_TAG_LADDER) {
         const LevelParams lp = level_params(h);
@@ -758,36 +758,46 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         if ((s = need((uint64_t)n_out * row)) != AMR_OK) return s;
         // a chunk: its head (first row, rows), then the rows of whole blocks
         const uint64_t total = (uint64_t)n_out * row;
-        size_t chunk = transfer_chunk(h, total);
-        if (total + kHeadBytes <= kPinBytes) chunk = (size_t)h->n_outb * row * mb + kHeadBytes;  // in one
-        const int per = std::max(1, (int)((chunk - kHeadBytes) / (row * mb)));
-        s = transfer_out(
-            h, buf, (h->n_outb + per - 1) / per, total,
+        int per = h->n_outb;
+        const Source src = {
+            [&](size_t chunk) {
+                if (total + kHeadBytes > chunk) per = std::max(1, (int)((chunk - kHeadBytes) / (row * mb)));
+                else per = h->n_outb;
+                return (h->n_outb + per - 1) / per;
+            },
             [&](int i, char *to) {
                 launch_out_gather(c, kind, i * per, std::min(h->n_outb, (i + 1) * per), h->n_outb, h->n_out,
                                   (int64_t *)to, to + kHeadBytes, lp);
                 return hipGetLastError();
             },
             [&](int, const int64_t *head) {
-                return Piece{(uint64_t)head[0] * row, kHeadBytes, (size_t)head[1] * row};
-            });
+                return head ? Piece{(uint64_t)head[0] * row, kHeadBytes, (size_t)head[1] * row}
+                            : Piece{0, kHeadBytes, (size_t)total};
+            },
+            nullptr};
+        s = transfer_out(h, buf, total, src);
         return s == AMR_OK ? sync_checked(h) : s;
     }
     case AMR_FIELD_BLOCK_F: {
         const size_t row = (size_t)mb * q * 8;
         if ((s = need(cap * row)) != AMR_OK) return s;
         if (op == AMR_GET) {
-            const int per = std::max(1, (int)(transfer_chunk(h, cap * row) / row));
+            int per = 1;
             const auto end = [&](int i) { return std::min((int)cap, (i + 1) * per); };
-            s = transfer_out(
-                h, buf, ((int)cap + per - 1) / per, cap * row,
+            const Source src = {
+                [&](size_t chunk) {
+                    per = std::max(1, (int)(chunk / row));
+                    return ((int)cap + per - 1) / per;
+                },
                 [&](int i, char *to) {
                     launch_block_f(c, 0, i * per, end(i), (double *)to, lp);
                     return hipGetLastError();
                 },
                 [&](int i, const int64_t *) {
                     return Piece{(uint64_t)i * per * row, 0, (size_t)(end(i) - i * per) * row};
-                });
+                },
+                nullptr};
+            s = transfer_out(h, buf, cap * row, src);
             return s == AMR_OK ? sync_checked(h) : s;
         }
         const int per_blocks = (int)(c.staging_bytes / row);

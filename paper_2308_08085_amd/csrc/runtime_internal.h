@@ -85,19 +85,24 @@ struct Piece {
 
 void transfer_add_user(amr_handle *h);   // with the handle's creation
 void transfer_drop_user(amr_handle *h);  // with its end
-size_t transfer_chunk(const amr_handle *h, uint64_t total);  // chunk size for a transfer of `total` bytes
-// n chunks of at most transfer_chunk() bytes to the `total` bytes at dst:
-// fill(i, to) enqueues what writes chunk i to `to` (pinned host or device
-// memory) on the handle's stream and returns whether that was accepted, and
-// piece(i, head) says where it goes, given the chunk's first kHeadBytes.
-// Without pinned memory: `plain`, if given, enqueues the whole transfer, else
-// the chunks go through the staging area.  Synchronises the stream.  Fails, with
+// What a transfer moves, in chunks whose size depends on the way it takes.
+struct Source {
+    // chunks of at most `chunk` bytes from now on; how many
+    std::function<int(size_t chunk)> split;
+    // enqueues what writes chunk i to `to` (pinned host or device memory) on the
+    // handle's stream; whether that was accepted
+    std::function<hipError_t(int i, char *to)> fill;
+    // where chunk i goes, given its first kHeadBytes (null if it is the only one)
+    std::function<Piece(int i, const int64_t *head)> piece;
+    // for a plain copy: enqueues all of it, without chunks
+    std::function<hipError_t()> plain;
+};
+// The `total` bytes of src to dst.  Synchronises the stream.  Fails, with
 // nothing moved, if an earlier launch was refused, and never writes outside dst.
-amr_status transfer_out(amr_handle *h, void *dst, int n, uint64_t total,
-                        const std::function<hipError_t(int, char *)> &fill,
-                        const std::function<Piece(int, const int64_t *)> &piece,
-                        const std::function<hipError_t()> &plain = nullptr);
-// a range of device memory to pageable host memory, as transfer_out
+amr_status transfer_out(amr_handle *h, void *dst, uint64_t total, const Source &src);
+// whether memory of the caller is the host's (else the GPU's)
+bool host_memory(const void *p);
+// a range of device memory to the caller's memory, as transfer_out
 amr_status copy_out(amr_handle *h, void *dst, const void *dev, size_t bytes);
 
 

@@ -1,7 +1,7 @@
-// transfer.hip -- device data to the caller's host memory.  That memory is
-// pageable, so data goes through pinned memory that the kernels (or a copy)
-// write directly; while the GPU fills the next chunks, host threads move the
-// finished ones on.
+// transfer.hip -- device data to the caller's memory.  Pageable host memory is
+// reached through pinned memory that the kernels (or a copy) write directly;
+// while the GPU fills the next chunks, host threads move the finished ones on.
+// Memory that the GPU can write by itself needs no such help.
 //
 // What bounds it: PCIe carries 55 GB/s into pinned memory, one host thread
 // copies into freshly mapped memory at 5-14 GB/s, eight at 24-92 GB/s (4 KiB /
@@ -15,6 +15,14 @@
 // in all (0.4 ms) and given back when the last handle is destroyed.  One
 // transfer uses the ring at a time; others meanwhile, and all if pinned memory
 // cannot be had, take the runtime's path.
+//
+// us to pageable memory, runtime's path and ring:
+//   copy of 1.3 MB   80 and 110      rho, u of 0.13 MB   75 and  20
+//           4.5 MB  260 and 250                  2.1 MB  205 and 130
+//          10.6 MB  620 and 415                 28.3 MB 1840 and 820
+// and to pinned memory, staging area and ring:
+//   rho, u of 0.13 MB  70 and 20, 1.0 MB 43 and 87, 28.3 MB 545 and 822.
+#include <algorithm>
 #include <condition_variable>
 #include <cstring>
 #include <mutex>
@@ -29,6 +37,13 @@ namespace {
 
 constexpr uint64_t kRingFrom = uint64_t(4) << 20;
 constexpr int kPinFrom = 32;
+// Which way is faster (figures above): plain copies to pageable memory take the
+// ring up to kRingCopySmall (one or two chunks, which this thread copies: 0.22 MB
+// 25 us, the runtime 19 to 98) and from kRingCopyLarge on (several threads);
+// gathers always, but into pinned memory of the caller only below
+// kPinnedDirectFrom.
+constexpr uint64_t kRingCopySmall = uint64_t(512) << 10, kRingCopyLarge = uint64_t(4) << 20;
+constexpr uint64_t kPinnedDirectFrom = uint64_t(1) << 20;
 constexpr int kSlots = 8, kMaxWorkers = 6;
 constexpr size_t kWorkerBytes = size_t(2) << 20;  // one host thread per this much of a transfer: starting one takes 20 us
 
@@ -116,11 +131,15 @@ amr_status misfit(const Piece &p, uint64_t total) {
                 (unsigned long long)p.at, (unsigned long long)total);
 }
 
+size_t ring_chunk(uint64_t total) {
+    const size_t c = (size_t)(total / kSlots);
+    return std::min(kSlotBytes, std::max(size_t(256) << 10, c));
+}
+
 // through the ring (held by the caller)
-amr_status through_ring(amr_handle *h, char *dst, int n, uint64_t total,
-                        const std::function<hipError_t(int, char *)> &fill,
-                        const std::function<Piece(int, const int64_t *)> &piece) {
+amr_status through_ring(amr_handle *h, char *dst, uint64_t total, const Source &src) {
     hipStream_t st = h->c.stream;
+    const int n = src.split(ring_chunk(total));
     const int slots = n < kSlots ? n : kSlots;
     hipEvent_t ev[kSlots] = {nullptr};
     hipError_t e = hipSuccess;
@@ -137,14 +156,14 @@ amr_status through_ring(amr_handle *h, char *dst, int n, uint64_t total,
                     if (launched > i) break;
                     w.wait(before);
                 }
-                e = fill(launched, g_ring.mem + (size_t)(launched % slots) * kSlotBytes);
+                e = src.fill(launched, g_ring.mem + (size_t)(launched % slots) * kSlotBytes);
                 if (e == hipSuccess) e = hipEventRecord(ev[launched % slots], st);
                 launched++;
             }
             if (e == hipSuccess) e = hipEventSynchronize(ev[i % slots]);
             if (e != hipSuccess) break;
             const char *from = g_ring.mem + (size_t)(i % slots) * kSlotBytes;
-            const Piece p = piece(i, (const int64_t *)from);
+            const Piece p = src.piece(i, n > 1 ? (const int64_t *)from : nullptr);
             if (fits(p, total, kSlotBytes)) w.give(i, p, from, dst);
             else s = misfit(p, total);
         }
@@ -155,6 +174,39 @@ amr_status through_ring(amr_handle *h, char *dst, int n, uint64_t total,
     for (int k = 0; k < slots; k++)
         if (ev[k]) hipEventDestroy(ev[k]);
     return e == hipSuccess ? s : fail(AMR_ERR_DEVICE, "field transfer: %s", hipGetErrorString(e));
+}
+
+// through the staging area and the runtime's own pinned memory, or directly to
+// memory of the caller that the GPU can write
+amr_status through_staging(amr_handle *h, char *dst, uint64_t total, const Source &src) {
+    hipStream_t st = h->c.stream;
+    const int n = src.split(h->c.staging_bytes);
+    for (int i = 0; i < n; i++) {
+        int64_t head[kHeadBytes / 8];
+        HIP_TRY(src.fill(i, (char *)h->c.staging));
+        if (n > 1) {
+            HIP_TRY(hipMemcpyAsync(head, h->c.staging, sizeof(head), hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+        }
+        const Piece p = src.piece(i, n > 1 ? head : nullptr);
+        if (!fits(p, total, h->c.staging_bytes)) return misfit(p, total);
+        HIP_TRY(hipMemcpyAsync(dst + p.at, (char *)h->c.staging + p.offset, p.bytes, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+    }
+    return AMR_OK;
+}
+
+// Memory that the GPU writes by itself: the caller's pinned memory, or a GPU's.
+enum class Memory { Pageable, Pinned, Device };
+Memory memory_of(const void *p) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return Memory::Pageable;
+    }
+    return a.type == hipMemoryTypeUnregistered ? Memory::Pageable
+           : a.type == hipMemoryTypeHost       ? Memory::Pinned
+                                               : Memory::Device;
 }
 
 }  // namespace
@@ -174,22 +226,14 @@ void transfer_drop_user(amr_handle *h) {
     g_ring.mem = nullptr;
 }
 
-size_t transfer_chunk(const amr_handle *h, uint64_t total) {
-    size_t c = (size_t)(total / kSlots);
-    if (c < (size_t(256) << 10)) c = size_t(256) << 10;
-    if (c > kSlotBytes) c = kSlotBytes;
-    return c < h->c.staging_bytes ? c : h->c.staging_bytes;
-}
+bool host_memory(const void *p) { return memory_of(p) != Memory::Device; }
 
-amr_status transfer_out(amr_handle *h, void *dst_, int n, uint64_t total,
-                        const std::function<hipError_t(int, char *)> &fill,
-                        const std::function<Piece(int, const int64_t *)> &piece,
-                        const std::function<hipError_t()> &plain) {
+amr_status transfer_out(amr_handle *h, void *dst_, uint64_t total, const Source &src) {
     hipStream_t st = h->c.stream;
     char *dst = (char *)dst_;
     // a kernel that was to make the data and was refused: no later call says so
     HIP_TRY(hipGetLastError());
-    if (n <= 0) {
+    if (total == 0) {
         HIP_TRY(hipStreamSynchronize(st));
         return AMR_OK;
     }
@@ -199,53 +243,51 @@ amr_status transfer_out(amr_handle *h, void *dst_, int n, uint64_t total,
         if (hipHostMalloc(&p, kPinBytes, hipHostMallocPortable) == hipSuccess) h->pin = (char *)p;
         else (void)hipGetLastError();
     }
-    if (n == 1 && total + kHeadBytes <= kPinBytes && h->pin) {
-        HIP_TRY(fill(0, h->pin));
+    const Memory to = memory_of(dst);
+    if (total + kHeadBytes <= kPinBytes && h->pin && to != Memory::Device) {
+        if (src.split(kPinBytes) != 1) return fail(AMR_ERR_DEVICE, "field transfer: more than one chunk");
+        HIP_TRY(src.fill(0, h->pin));
         HIP_TRY(hipStreamSynchronize(st));
-        const Piece p = piece(0, (const int64_t *)h->pin);
+        const Piece p = src.piece(0, nullptr);
         if (!fits(p, total, kPinBytes)) return misfit(p, total);
         memcpy(dst + p.at, h->pin + p.offset, p.bytes);
         return AMR_OK;
     }
-    std::unique_lock<std::mutex> use(g_ring.use, std::try_to_lock);
-    if (use.owns_lock()) {
-        if (!g_ring.mem && h->read_total >= kRingFrom) {
-            void *p = nullptr;
-            if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess) g_ring.mem = (char *)p;
-            else (void)hipGetLastError();
+    const bool ring = to == Memory::Pageable
+                          ? !src.plain || total <= kRingCopySmall || total >= kRingCopyLarge
+                          : to == Memory::Pinned && !src.plain && total < kPinnedDirectFrom;
+    if (ring) {
+        std::unique_lock<std::mutex> use(g_ring.use, std::try_to_lock);
+        if (use.owns_lock()) {
+            if (!g_ring.mem && h->read_total >= kRingFrom) {
+                void *p = nullptr;
+                if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess) g_ring.mem = (char *)p;
+                else (void)hipGetLastError();
+            }
+            if (g_ring.mem) return through_ring(h, dst, total, src);
         }
-        if (g_ring.mem) return through_ring(h, dst, n, total, fill, piece);
-        use.unlock();
     }
-    if (plain) {
-        HIP_TRY(plain());
-        HIP_TRY(hipStreamSynchronize(st));
-        return AMR_OK;
-    }
-    for (int i = 0; i < n; i++) {  // through the staging area and the runtime's own pinned memory
-        int64_t head[kHeadBytes / 8];
-        HIP_TRY(fill(i, (char *)h->c.staging));
-        HIP_TRY(hipMemcpyAsync(head, h->c.staging, sizeof(head), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        const Piece p = piece(i, head);
-        if (!fits(p, total, h->c.staging_bytes)) return misfit(p, total);
-        HIP_TRY(hipMemcpyAsync(dst + p.at, (char *)h->c.staging + p.offset, p.bytes, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-    }
+    if (!src.plain) return through_staging(h, dst, total, src);
+    HIP_TRY(src.plain());
+    HIP_TRY(hipStreamSynchronize(st));
     return AMR_OK;
 }
 
 amr_status copy_out(amr_handle *h, void *dst, const void *dev, size_t bytes) {
     hipStream_t st = h->c.stream;
-    const size_t chunk = bytes + kHeadBytes <= kPinBytes ? bytes : transfer_chunk(h, bytes);
-    const auto size = [&](int i) { return bytes - (size_t)i * chunk < chunk ? bytes - (size_t)i * chunk : chunk; };
-    return transfer_out(
-        h, dst, bytes ? (int)((bytes + chunk - 1) / chunk) : 0, bytes,
+    size_t chunk = bytes;
+    const auto size = [&](int i) { return std::min(chunk, bytes - (size_t)i * chunk); };
+    const Source src = {
+        [&](size_t c) {
+            chunk = c;
+            return (int)((bytes + c - 1) / c);
+        },
         [&](int i, char *to) {
             return hipMemcpyAsync(to, (const char *)dev + (size_t)i * chunk, size(i), hipMemcpyDefault, st);
         },
         [&](int i, const int64_t *) { return Piece{(uint64_t)i * chunk, 0, size(i)}; },
-        [&] { return hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, st); });
+        [&] { return hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, st); }};
+    return transfer_out(h, dst, bytes, src);
 }
 
 }  // namespace amr

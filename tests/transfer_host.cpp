@@ -15,6 +15,7 @@ namespace {
 std::atomic<int> g_calls{0};    // fallible calls so far
 int g_fail_at = -1;             // the one that fails
 bool g_no_pinned = false;       // pinned memory cannot be had
+hipMemoryType g_type = hipMemoryTypeUnregistered;  // of the caller's memory
 hipError_t g_last = hipSuccess;  // of refused launches
 hipError_t call() { return g_calls++ == g_fail_at ? hipErrorInvalidValue : hipSuccess; }
 }  // namespace
@@ -45,6 +46,11 @@ hipError_t hipHostFree(void *p) {
     free(p);
     return hipSuccess;
 }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
+    a->type = g_type;
+    if (g_type != hipMemoryTypeUnregistered) return hipSuccess;
+    return g_last = hipErrorInvalidValue;  // as for memory that the runtime does not know
+}
 hipError_t hipGetLastError(void) {
     const hipError_t e = g_last;
     g_last = hipSuccess;
@@ -71,6 +77,7 @@ enum Fault { kNone_, kEarlier, kRefused, kHeadHigh, kHeadNegative };
 struct Run {
     amr_status s;
     bool right, guards;
+    int chunks;
 };
 
 // one transfer of `bytes`; rows: as a gather with heads, else a copy
@@ -87,17 +94,20 @@ Run transfer(size_t bytes, bool rows, bool pin, bool ring, Fault fault) {
     else g_no_pinned = true;
     char *dst = out.data() + 1024;
     if (fault == kEarlier) g_last = hipErrorInvalidConfiguration;
-    Run r;
+    Run r{};
     if (rows) {
         const size_t row = 32;
-        const size_t per = std::max<size_t>(1, (transfer_chunk(&h, bytes) - kHeadBytes) / row);
         const int64_t all = (int64_t)(bytes / row);
-        const int n = (int)((all + per - 1) / per);
-        r.s = transfer_out(
-            &h, dst, n, bytes,
+        int64_t per = 1;
+        int n = 0;
+        const Source src = {
+            [&](size_t chunk) {
+                per = (int64_t)((chunk - kHeadBytes) / row);
+                return n = (int)((all + per - 1) / per);
+            },
             [&](int i, char *to) {
                 if (fault == kRefused && i == n - 1) return hipErrorInvalidConfiguration;  // and nothing written
-                const int64_t first = (int64_t)i * per, end = std::min(all, (int64_t)(i + 1) * (int64_t)per);
+                const int64_t first = i * per, end = std::min(all, (i + 1) * per);
                 int64_t head[2] = {first, end - first};
                 if (i == n - 1 && fault == kHeadHigh) head[0] += 1;
                 if (i == n - 1 && fault == kHeadNegative) head[0] = -1;
@@ -106,8 +116,13 @@ Run transfer(size_t bytes, bool rows, bool pin, bool ring, Fault fault) {
                 return hipSuccess;
             },
             [&](int, const int64_t *head) {
-                return Piece{(uint64_t)head[0] * row, kHeadBytes, (size_t)head[1] * row};
-            });
+                expect((n == 1) == (head == nullptr), "head", bytes, n);
+                return head ? Piece{(uint64_t)head[0] * row, kHeadBytes, (size_t)head[1] * row}
+                            : Piece{0, kHeadBytes, bytes};
+            },
+            nullptr};
+        r.s = transfer_out(&h, dst, bytes, src);
+        r.chunks = n;
     } else {
         r.s = copy_out(&h, dst, data.data(), bytes);
     }
@@ -126,14 +141,16 @@ Run transfer(size_t bytes, bool rows, bool pin, bool ring, Fault fault) {
 int main() {
     int n = 0;
     const size_t sizes[] = {0, 32, 4096, 65472, 65504, 700000 / 32 * 32, (size_t(5) << 20) + 96};
-    for (int mode = 0; mode < 8; mode++) {
+    const hipMemoryType types[] = {hipMemoryTypeUnregistered, hipMemoryTypeHost, hipMemoryTypeDevice};
+    for (int mode = 0; mode < 24; mode++) {
         const bool rows = mode & 1, pin = mode & 2, ring = mode & 4;
+        g_type = types[mode >> 3];
         for (size_t bytes : sizes) {
             g_fail_at = -1;
             g_calls = 0;
             Run r = transfer(bytes, rows, pin, ring, kNone_);
             expect(r.s == AMR_OK && r.right && r.guards, "plain transfer", bytes, -1);
-            const int calls = g_calls;
+            const int calls = g_calls, chunks = r.chunks;
             expect(calls > 0, "synchronises", bytes, -1);
             for (int k = 0; k < calls; k++) {
                 g_fail_at = k;
@@ -146,7 +163,8 @@ int main() {
             r = transfer(bytes, rows, pin, ring, kEarlier);
             expect(r.s == AMR_ERR_DEVICE && r.guards, "earlier launch refused", bytes, -1);
             for (Fault f : {kRefused, kHeadHigh, kHeadNegative}) {
-                if (!rows || bytes == 0) continue;
+                // the head is not used where there is one chunk
+                if (!rows || bytes == 0 || (chunks == 1 && f != kRefused)) continue;
                 r = transfer(bytes, rows, pin, ring, f);
                 expect(r.s == AMR_ERR_DEVICE && r.guards, "refused launch or wrong head", bytes, -1);
                 n++;
