@@ -141,10 +141,14 @@ amr_status through_ring(amr_handle *h, char *dst, uint64_t total, const Source &
     hipStream_t st = h->c.stream;
     const int n = src.split(ring_chunk(total));
     const int slots = n < kSlots ? n : kSlots;
+    // The host reads what the kernels wrote once the chunk's event has passed; pinned
+    // memory is not promised to be coherent (HIP_HOST_COHERENT), so the event releases
+    // to the host.
+    constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventReleaseToSystem;
     hipEvent_t ev[kSlots] = {nullptr};
     hipError_t e = hipSuccess;
     amr_status s = AMR_OK;
-    for (int k = 0; k < slots && e == hipSuccess; k++) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+    for (int k = 0; k < slots && e == hipSuccess; k++) e = hipEventCreateWithFlags(&ev[k], kEventFlags);
     try {
         const uint64_t want = total / kWorkerBytes;
         Workers w(n, n > 1 && want > 1 ? (int)(want < kMaxWorkers ? want : kMaxWorkers) : 0);
