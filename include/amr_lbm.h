@@ -193,8 +193,9 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats);
  * AMR_ERR_UNSTABLE if it is not finite.
  * Errors: AMR_ERR_ARG (n < 0), AMR_ERR_UNSTABLE, AMR_ERR_DEVICE. */
 #define AMR_CHECK_FINITE 1u
-#define AMR_USE_GRAPH 2u   /* accepted and without effect: plain launches run ahead of the GPU and were
-                              measured faster than replaying a captured coarse step (HIP graph) */
+#define AMR_USE_GRAPH 2u   /* coarse steps may be replayed from a captured one (HIP graph).  They are where
+                              that is faster: when one thread steps several simulations in turn and its
+                              launches cannot keep the GPU busy.  Results do not depend on it */
 #define AMR_PROFILE 4u     /* time every solver launch with HIP events on the stream (eager; see
                               AMR_FIELD_KERNEL_STATS); synchronises the stream */
 amr_status lbm_step(amr_t *h, int32_t n_coarse_steps, uint32_t flags);

@@ -75,6 +75,7 @@ struct amr_batch {
     int par0 = 0;                   // level-0 buffer parity shared by every member
     int n_cu = 256;
     amr_batch_tuning tune;
+    StepReplay replay;              // coarse steps under AMR_USE_GRAPH
 };
 
 namespace {
@@ -202,10 +203,30 @@ amr_status refresh_descs(amr_batch *b) {
     return AMR_OK;
 }
 
-// Plain launches, with or without AMR_USE_GRAPH: the host stays ahead of the GPU
-// (2.5 us per launch), and a captured coarse step replayed no faster (32 mixed
-// cavities: 593 us against 588 with schedule 0, 495 against 441 with schedule 1).
-amr_status run_steps(amr_batch *b, int32_t n) {
+// kernels that a coarse step launches
+int step_launches(const amr_batch *b) {
+    int n = 0;
+    for (const auto &g : b->groups)
+        for (int L = 0; L < g.lmax; L++)  // per visit of a level: sweep, exchange, interpolation and averaging
+            n += (1 << L) * (1 + (g.solid ? 1 : 0) + (L + 1 < g.lmax ? 2 : 0));
+    return n;
+}
+
+// graph: replay the coarse steps where StepReplay finds that faster.  One batch
+// alone is bound by the GPU (32 mixed cavities, us per step launched and
+// replayed: 588 and 593 with schedule 0, 441 and 495 with schedule 1); four
+// batches of four 64 x 64 D2Q9 cavities stepped in turn 34 and 24 us per step.
+// A captured step holds no counts, so it outlives mesh changes.
+amr_status run_steps(amr_batch *b, int32_t n, bool graph) {
+    const bool replay = graph && b->replay.begin(b->stream, step_launches(b));
+    if (replay && !b->replay.captured())
+        for (int p = 0; p < 2; p++) {
+            const hipError_t e = b->replay.capture(b->stream, p, [&] { return batch_coarse_step(b, p) == AMR_OK; });
+            if (e != hipSuccess) {
+                b->replay.drop(b->stream);
+                return fail(AMR_ERR_DEVICE, "step capture: %s", hipGetErrorString(e));
+            }
+        }
     // members adapt between calls only, so their work lists serve every step
     // of this one (rebuilt in each step they cost 20 us per group of 16
     // simulations)
@@ -213,13 +234,18 @@ amr_status run_steps(amr_batch *b, int32_t n) {
         for (auto &g : b->groups)
             launch_batch_items(b->stream, g.desc, (int)g.members.size(), g.lmax, g.cap_max, g.items, g.stride, g.counts);
     for (int32_t k = 0; k < n; k++) {
-        amr_status s = batch_coarse_step(b, b->par0);
-        if (s != AMR_OK) return s;
+        if (replay) {
+            HIP_TRY(b->replay.launch(b->stream, b->par0));
+        } else {
+            amr_status s = batch_coarse_step(b, b->par0);
+            if (s != AMR_OK) return s;
+        }
         b->par0 ^= 1;
     }
     set_member_parity(b);
     count_member_sweeps(b, n);
     HIP_TRY(hipGetLastError());
+    if (n > 0) b->replay.enqueued();
     return AMR_OK;
 }
 
@@ -310,7 +336,7 @@ amr_status amr_batch_step(amr_batch_t *b, int32_t n, uint32_t flags) {
         if (h->par[0] != b->par0) return fail(AMR_ERR_STATE, "a member was stepped outside the batch");
     amr_status s = refresh_descs(b);
     if (s != AMR_OK) return s;
-    s = run_steps(b, n);
+    s = run_steps(b, n, (flags & AMR_USE_GRAPH) != 0);
     if (s != AMR_OK) return s;
     if (flags & AMR_CHECK_FINITE) {
         int bad = -1;
@@ -332,6 +358,8 @@ amr_status amr_batch_set_tuning(amr_batch_t *b, const amr_batch_tuning *t) {
     amr_status s = check_tuning(t);
     if (s != AMR_OK) return s;
     HIP_TRY(hipStreamSynchronize(b->stream));
+    StepReplay::waited();
+    b->replay.drop(b->stream);
     b->tune = *t;
     return AMR_OK;
 }
@@ -366,10 +394,10 @@ amr_status amr_batch_autotune(amr_batch_t *b, int32_t trial_steps, amr_batch_tun
                 s = amr_batch_set_tuning(b, &c);
                 if (s != AMR_OK) break;
                 // two untimed steps first
-                s = run_steps(b, 2);
+                s = run_steps(b, 2, false);
                 if (s != AMR_OK) break;
                 if (hipEventRecord(t0, b->stream) != hipSuccess) { s = fail(AMR_ERR_DEVICE, "event record"); break; }
-                s = run_steps(b, trial_steps);
+                s = run_steps(b, trial_steps, false);
                 if (s != AMR_OK) break;
                 float ms = 0.f;
                 if (hipEventRecord(t1, b->stream) != hipSuccess || hipEventSynchronize(t1) != hipSuccess ||
@@ -396,6 +424,7 @@ amr_status amr_batch_autotune(amr_batch_t *b, int32_t trial_steps, amr_batch_tun
 amr_status amr_batch_destroy(amr_batch_t *b) {
     if (!b) return AMR_OK;
     if (b->stream || !b->sims.empty()) hipStreamSynchronize(b->stream);
+    b->replay.drop(b->stream);
     for (auto st : b->side) {
         hipStreamSynchronize(st);
         hipStreamDestroy(st);

@@ -2,6 +2,7 @@
 // carve-up, the recursive sub-cycled schedule, tagging and adaptation
 // sequencing, field access.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -28,6 +29,56 @@ amr_status fail(amr_status code, const char *fmt, ...) {
     va_end(ap);
     g_err = buf;
     return code;
+}
+
+// id of the simulation or batch whose steps this thread enqueued last without
+// waiting for any since; 0: none
+static thread_local uint64_t t_enqueued = 0;
+
+uint64_t StepReplay::next_id() {
+    static std::atomic<uint64_t> n{0};
+    return ++n;
+}
+
+void StepReplay::enqueued() const { t_enqueued = id_; }
+void StepReplay::waited() { t_enqueued = 0; }
+
+bool StepReplay::begin(hipStream_t st, int launches) {
+    // the default streams cannot be captured
+    if (launches < kReplayFrom || t_enqueued == 0 || t_enqueued == id_ || (uintptr_t)st <= 2) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipPeekAtLastError() != hipSuccess || hipStreamIsCapturing(st, &cap) != hipSuccess ||
+        cap != hipStreamCaptureStatusNone)
+        return false;  // into the caller's capture; an error is left for the call to report
+    if (captured()) return true;
+    if (hipStreamQuery(st) != hipSuccess) {
+        (void)hipGetLastError();  // not ready
+        dry_ = 0;
+        return false;
+    }
+    return ++dry_ >= kDry;
+}
+
+hipError_t StepReplay::capture(hipStream_t st, int par, const std::function<bool()> &step) {
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return e;
+    const bool ok = step();
+    e = hipStreamEndCapture(st, &g);
+    if (e == hipSuccess && !ok) e = hipErrorLaunchFailure;
+    if (e == hipSuccess) e = hipGraphInstantiate(&exec_[par], g, nullptr, nullptr, 0);
+    if (g) (void)hipGraphDestroy(g);
+    return e;
+}
+
+void StepReplay::drop(hipStream_t st) {
+    dry_ = 0;
+    if (!exec_[0] && !exec_[1]) return;
+    (void)hipStreamSynchronize(st);
+    for (auto &x : exec_) {
+        if (x) (void)hipGraphExecDestroy(x);
+        x = nullptr;
+    }
 }
 
 LevelParams level_params(const amr_handle *h) {
@@ -200,17 +251,21 @@ void collide_stream(amr_handle *h, int L, bool fused = false, bool exchanged = f
     const bool exchange = h->force_on && h->nsolid[L] > 0;
     int n = 0;
     const int32_t *list = sweep_list(h, L, &n);
-    if (!fused)
+    if (!fused) {
+        h->launches += n > 0;
         timed_launch(h, 0, n, L, [&] {
             exchanged = launch_collide_stream(h->c, list, n, L, lp, h->bc, exchange && join_launches(h));
         });
+    }
     h->par[L] ^= 1;
     // momentum exchange with solid blocks, from the buffer just written
-    if (exchange && !exchanged)
+    if (exchange && !exchanged) {
+        h->launches++;
         launch_exchange(h->c, h->c.solidl + (size_t)L * h->c.m.cap, h->nsolid[L], L, level_params(h));
+    }
 }
 
-// recursive sub-cycled advancement (Sec. "Grid Advancement")
+// recursive sub-cycled advancement (Sec. "Grid Advancement"); counts its launches
 void step_level(amr_handle *h, int L) {
     if (L == h->lmax - 1) {
         collide_stream(h, L);
@@ -218,6 +273,7 @@ void step_level(amr_handle *h, int L) {
     }
     const size_t cap = (size_t)h->c.m.cap;
     const bool fuse = h->niface[L] > 0 && join_launches(h) && small_level(h, L);
+    if (h->niface[L] > 0) h->launches += 2;  // interpolation (and sweep), averaging
     bool exchanged = false;
     if (fuse) {
         const LevelParams lp = level_params(h);
@@ -240,6 +296,7 @@ void step_level(amr_handle *h, int L) {
 
 amr_status collect_timings(amr_handle *h) {
     HIP_TRY(hipStreamSynchronize(h->c.stream));
+    StepReplay::waited();
     for (auto &t : h->timed) {
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, t.a, t.b));
@@ -280,6 +337,7 @@ amr_status refresh_counts(amr_handle *h) {
 amr_status sync_checked(amr_handle *h) {
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(h->c.stream));
+    StepReplay::waited();
     return AMR_OK;
 }
 
@@ -451,6 +509,7 @@ amr_status amr_create(const amr_config *cfg, void *dev_arena, uint64_t arena_byt
 amr_status amr_destroy(amr_t *h) {
     if (!h) return AMR_OK;
     hipStreamSynchronize(h->c.stream);
+    h->replay.drop(h->c.stream);
     for (auto &t : h->timed) {
         hipEventDestroy(t.a);
         hipEventDestroy(t.b);
@@ -467,14 +526,33 @@ amr_status lbm_step(amr_t *h, int32_t n, uint32_t flags) {
     if (!h) return fail(AMR_ERR_ARG, "handle is NULL");
     if (n < 0) return fail(AMR_ERR_ARG, "n_coarse_steps must be >= 0");
     h->profiling = (flags & AMR_PROFILE) != 0;
-    // With or without AMR_USE_GRAPH: plain launches.  They cost the host 2.5 us
-    // each, less than any of the step's kernels lasts, so the GPU never waits for
-    // them; replaying a captured coarse step cost 11 to 19 us of host time that
-    // the GPU did wait for (single level of 256 D2Q9 blocks 16.0 against 5.7 us a
-    // step, D2Q9 cylinder on three levels 66.1 against 61.9 us, D3Q19 cavity 207.1
-    // against 202.4 us), and every adaptation another capture (0.25 ms).
-    for (int32_t sidx = 0; sidx < n; sidx++) step_level(h, 0);
+    const bool replay = (flags & AMR_USE_GRAPH) && !h->profiling && h->replay.begin(h->c.stream, h->launches);
+    if (replay && !h->replay.captured()) {
+        // one coarse step of each parity of level 0; every level returns to its parity
+        hipError_t e = hipSuccess;
+        const int p0 = h->par[0];
+        for (int k = 0; k < 2 && e == hipSuccess; k++)
+            e = h->replay.capture(h->c.stream, (p0 + k) & 1, [&] {
+                step_level(h, 0);
+                return true;
+            });
+        h->par[0] = p0;
+        if (e != hipSuccess) {
+            h->replay.drop(h->c.stream);
+            return fail(AMR_ERR_DEVICE, "step capture: %s", hipGetErrorString(e));
+        }
+    }
+    for (int32_t sidx = 0; sidx < n; sidx++) {
+        if (replay) {
+            HIP_TRY(h->replay.launch(h->c.stream, h->par[0]));
+            h->par[0] ^= 1;
+        } else {
+            h->launches = 0;
+            step_level(h, 0);
+        }
+    }
     HIP_TRY(hipGetLastError());
+    if (n > 0) h->replay.enqueued();
     if (h->force_on)
         for (int L = 0; L < h->lmax; L++) h->force_sweeps[L] += (double)n * (double)(1 << L);
     if (h->profiling) {
@@ -590,6 +668,7 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats) {
     if ((long long)c.nc * n_ref > dc.gtop)
         return fail(AMR_ERR_CAPACITY, "%d refinements need %d free block IDs, %d left", n_ref, c.nc * n_ref, dc.gtop);
     const LevelParams lp = level_params(h);
+    h->replay.drop(c.stream);  // a captured step holds the mesh's block counts
     // blocks are created and removed: the momentum-exchange sums restart
     launch_force_reset(c);
     for (int L = 0; L < kMaxLevels; L++) h->force_sweeps[L] = 0.0;
@@ -628,6 +707,7 @@ amr_status amr_adapt(amr_t *h, amr_adapt_stats *stats) {
 amr_status amr_set_collision(amr_t *h, int32_t kind, double s_high) {
     if (!h) return fail(AMR_ERR_ARG, "handle is NULL");
     if (kind == AMR_COLLIDE_BGK) {
+        if (h->c.coll != kind) h->replay.drop(h->c.stream);
         h->c.coll = AMR_COLLIDE_BGK;
         return AMR_OK;
     }
@@ -638,6 +718,7 @@ amr_status amr_set_collision(amr_t *h, int32_t kind, double s_high) {
         return fail(AMR_ERR_ARG, "AMR_COLLIDE_MRT_MFMA needs a storage with FP32 arithmetic");
     if (!(s_high > 0.0 && s_high < 2.0)) return fail(AMR_ERR_ARG, "s_high must lie in (0, 2), not %g", s_high);
     if (h->batches > 0) return fail(AMR_ERR_ARG, "the handle is in a batch, which advances BGK members only");
+    if (kind != h->c.coll || s_high != h->c.s_high) h->replay.drop(h->c.stream);
     h->c.coll = kind;
     h->c.s_high = s_high;
     return AMR_OK;
@@ -672,6 +753,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             return AMR_OK;
         }
         if (*v != 0 && *v != 1) return fail(AMR_ERR_ARG, "AMR_FIELD_FORCE_ON takes 0 or 1, not %d", *v);
+        if ((*v == 1) != h->force_on) h->replay.drop(h->c.stream);
         h->force_on = *v == 1;
         return AMR_OK;
     }
@@ -697,6 +779,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
         if (*v == 1 && h->c.m.interp != AMR_INTERP_LINEAR)
             return fail(AMR_ERR_ARG, "AMR_FIELD_SKIP_PARENTS needs linear interpolation (cubic stencils reach "
                                      "into neighbouring parents)");
+        if ((*v == 1) != h->skip_parents) h->replay.drop(h->c.stream);
         h->skip_parents = *v == 1;
         return AMR_OK;
     }
@@ -708,6 +791,7 @@ amr_status amr_fields(amr_t *h, int32_t op, int32_t kind, int32_t sim, void *buf
             return AMR_OK;
         }
         if (*v < 0) return fail(AMR_ERR_ARG, "AMR_FIELD_STREAM_BYTES must be >= 0, not %lld", (long long)*v);
+        if (*v != h->c.stream_bytes) h->replay.drop(h->c.stream);
         h->c.stream_bytes = *v;
         return AMR_OK;
     }

@@ -21,6 +21,42 @@ amr_status fail(amr_status code, const char *fmt, ...);
         if (e_ != hipSuccess) return fail(AMR_ERR_DEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// Coarse steps under AMR_USE_GRAPH: launched, or replayed from a captured step.
+//
+// A replay costs the host 13 to 16 us per coarse step whatever it holds, a
+// launch 2.5 us, but the GPU takes launches faster and a mesh change costs
+// another capture (0.25 ms).  For one simulation the GPU is what bounds the
+// steps, and they are launched (D2Q9 cavity 64 x 64, three levels, us per step:
+// 51 against 59).  A thread that steps several simulations in turn, each on its
+// own stream, is bound by its own launches: eight such cavities 28 us per step
+// launched, 20 replayed.  So a step of at least kReplayFrom launches is replayed
+// if this thread has enqueued another simulation's steps since it last waited
+// for one, and has twice in a row found this one's stream out of work.
+// Results do not depend on it.
+class StepReplay {
+  public:
+    // At the start of a call; true: replay its steps.  launches: of the last
+    // coarse step launched.
+    bool begin(hipStream_t st, int launches);
+    bool captured() const { return exec_[0] && exec_[1]; }
+    // Captures what `step` enqueues on st as the coarse step of level-0 parity `par`.
+    hipError_t capture(hipStream_t st, int par, const std::function<bool()> &step);
+    hipError_t launch(hipStream_t st, int par) const { return hipGraphLaunch(exec_[par], st); }
+    // At the end of a call that enqueued steps.
+    void enqueued() const;
+    // The captured steps are out of date (or the simulation ends).
+    void drop(hipStream_t st);
+    // This thread has waited for the GPU.
+    static void waited();
+
+  private:
+    static constexpr int kReplayFrom = 8, kDry = 2;
+    static uint64_t next_id();
+    const uint64_t id_ = next_id();
+    hipGraphExec_t exec_[2] = {nullptr, nullptr};
+    int dry_ = 0;  // calls in a row that found the stream out of work
+};
+
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
@@ -47,6 +83,8 @@ struct amr_handle {
     double force_sweeps[kMaxLevels] = {0};  // collide-stream sweeps per level since the force reset
     bool force_on = true;                   // accumulate the momentum exchange every sweep
     bool sync_velocity = true;              // criterion velocities from the synchronisation's averaging
+    amr::StepReplay replay;                 // coarse steps under AMR_USE_GRAPH
+    int launches = 0;                       // kernels launched by the coarse step under way, or the last
     bool skip_parents = false;              // sweeps leave out refined blocks without N_SKIP children
     int batches = 0;                        // batches this handle is a member of
     char *pin = nullptr;                    // pinned memory for small transfers (kPinBytes), may be null

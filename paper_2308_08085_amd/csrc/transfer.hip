@@ -233,6 +233,7 @@ void transfer_drop_user(amr_handle *h) {
 bool host_memory(const void *p) { return memory_of(p) != Memory::Device; }
 
 amr_status transfer_out(amr_handle *h, void *dst_, uint64_t total, const Source &src) {
+    StepReplay::waited();  // every way below waits for the stream
     hipStream_t st = h->c.stream;
     char *dst = (char *)dst_;
     // a kernel that was to make the data and was refused: no later call says so
