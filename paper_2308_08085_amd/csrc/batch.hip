@@ -245,7 +245,7 @@ amr_status run_steps(amr_batch *b, int32_t n, bool graph) {
     set_member_parity(b);
     count_member_sweeps(b, n);
     HIP_TRY(hipGetLastError());
-    if (n > 0) b->replay.enqueued();
+    if (n > 0) b->replay.enqueued(b->stream);
     return AMR_OK;
 }
 

@@ -31,21 +31,26 @@ amr_status fail(amr_status code, const char *fmt, ...) {
     return code;
 }
 
-// id of the simulation or batch whose steps this thread enqueued last without
-// waiting for any since; 0: none
-static thread_local uint64_t t_enqueued = 0;
+// the simulation or batch whose steps this thread enqueued last without waiting
+// for any since, and their stream; id 0: none
+static thread_local struct {
+    uint64_t id;
+    hipStream_t st;
+} t_enqueued = {0, nullptr};
 
 uint64_t StepReplay::next_id() {
     static std::atomic<uint64_t> n{0};
     return ++n;
 }
 
-void StepReplay::enqueued() const { t_enqueued = id_; }
-void StepReplay::waited() { t_enqueued = 0; }
+void StepReplay::enqueued(hipStream_t st) const { t_enqueued = {id_, st}; }
+void StepReplay::waited() { t_enqueued = {0, nullptr}; }
 
 bool StepReplay::begin(hipStream_t st, int launches) {
     // the default streams cannot be captured
-    if (launches < kReplayFrom || t_enqueued == 0 || t_enqueued == id_ || (uintptr_t)st <= 2) return false;
+    if (launches < kReplayFrom || t_enqueued.id == 0 || t_enqueued.id == id_ || t_enqueued.st == st ||
+        (uintptr_t)st <= 2)
+        return false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipPeekAtLastError() != hipSuccess || hipStreamIsCapturing(st, &cap) != hipSuccess ||
         cap != hipStreamCaptureStatusNone)
@@ -219,7 +224,7 @@ void timed_launch(amr_handle *h, int kind, int blocks, int L, F &&fn) {
 
 // Outside profiled runs (which time each kernel on its own) BGK sweeps save
 // launch gaps: a sweep adds the momentum exchange itself (the variant needs at
-// most 7 more VGPRs), and on small levels the ghost interpolation into level
+// most 7 more VGPRs; a joined one with streaming stores does not have it), and on small levels the ghost interpolation into level
 // L+1 joins the sweep.  Large levels gain nothing from it (D3Q27 cylinder, every
 // level joined: 9.72 ms per coarse step with FP32 and 5.78 with FP16 storage,
 // apart 9.73 and 5.78).
@@ -552,7 +557,7 @@ amr_status lbm_step(amr_t *h, int32_t n, uint32_t flags) {
         }
     }
     HIP_TRY(hipGetLastError());
-    if (n > 0) h->replay.enqueued();
+    if (n > 0) h->replay.enqueued(h->c.stream);
     if (h->force_on)
         for (int L = 0; L < h->lmax; L++) h->force_sweeps[L] += (double)n * (double)(1 << L);
     if (h->profiling) {

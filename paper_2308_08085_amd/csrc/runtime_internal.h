@@ -30,8 +30,8 @@ amr_status fail(amr_status code, const char *fmt, ...);
 // 51 against 59).  A thread that steps several simulations in turn, each on its
 // own stream, is bound by its own launches: eight such cavities 28 us per step
 // launched, 20 replayed.  So a step of at least kReplayFrom launches is replayed
-// if this thread has enqueued another simulation's steps since it last waited
-// for one, and has twice in a row found this one's stream out of work.
+// if this thread has enqueued another simulation's steps on another stream since
+// it last waited for one, and has twice in a row found this one's stream out of work.
 // Results do not depend on it.
 class StepReplay {
   public:
@@ -42,8 +42,8 @@ class StepReplay {
     // Captures what `step` enqueues on st as the coarse step of level-0 parity `par`.
     hipError_t capture(hipStream_t st, int par, const std::function<bool()> &step);
     hipError_t launch(hipStream_t st, int par) const { return hipGraphLaunch(exec_[par], st); }
-    // At the end of a call that enqueued steps.
-    void enqueued() const;
+    // At the end of a call that enqueued steps on st.
+    void enqueued(hipStream_t st) const;
     // The captured steps are out of date (or the simulation ends).
     void drop(hipStream_t st);
     // This thread has waited for the GPU.
