@@ -227,7 +227,7 @@ def run_batch(steps, warmup, theta, trial_steps=2):
         tot_a += ams
     # the same members one after another, each stepping on its own
     u = updates()
-    for g in sims:  # capture outside the timed region
+    for g in sims:  # untimed steps first
         g.step(2, graph=True)
     b.step(0)
     ev0.record(stream)

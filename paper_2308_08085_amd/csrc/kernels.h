@@ -71,8 +71,8 @@ struct Ctx {
 constexpr int64_t kStreamingBytes = int64_t(128) << 20;
 
 // ---- LBM kernels (lbm_kernels.hip) ----
-// exchange: also add the momentum exchange with solid blocks (BGK sweeps with
-// ordinary stores); returns whether it did, else launch_exchange follows
+// exchange: also add the momentum exchange with solid blocks (BGK sweeps);
+// returns whether it did, else launch_exchange follows
 bool launch_collide_stream(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp,
                            const BCParams &bc, bool exchange = false);
 // mode 0: ghost cells of children with an N_SKIP link; 1: every cell of every child
@@ -91,7 +91,8 @@ void launch_average(const Ctx &c, const int32_t *list, int n, int L, const Level
                     double *U = nullptr);
 // ghost interpolation into level L+1 (interface parents ilist) and the
 // collide-stream sweep of level L (launch order clist) in one launch; BGK;
-// exchange and the result as for launch_collide_stream
+// exchange and the result as for launch_collide_stream, but with streaming stores
+// it leaves the exchange to launch_exchange
 bool launch_interp_collide(const Ctx &c, const int32_t *ilist, int ni, const int32_t *clist, int nblk, int L,
                            const LevelParams &lp, const BCParams &bc, bool exchange = false);
 void launch_fill_rest(const Ctx &c);

@@ -206,8 +206,8 @@ __device__ __forceinline__ void gather_interior(const InteriorLane &u, typename 
 // workgroup (three barriers, one cache line per link and block) and a branch
 // per population for blocks with walls or coarser neighbours, a D3Q27 sweep of
 // the cylinder (4.2e5 blocks) took 1,360 us with FP32 and 871 us with FP16
-// storage, now 1,297 and 744 us (1,258 and 741 with the wave limit of
-// collide_waves: 4.67 and 4.01 TB/s); a D3Q19 FP32 sweep of 16,384 blocks 33.0,
+// storage, now 1,297 and 744 us (1,250 and 739 with the wave limit of
+// collide_waves); a D3Q19 FP32 sweep of 16,384 blocks 33.0,
 // now 30.2 us; a D2Q9 FP64 sweep of 64 blocks 7.2, now 5.3 us; a coarse step of
 // 32 mixed cavities in a batch 870, now 700 us.  An entry whose link is not a
 // block holds the link code, sign extended, so it is negative as an int64.
@@ -567,7 +567,6 @@ struct BlockStage {
     int32_t id[NBLK];
     int32_t hid[NBLK];
     int32_t sim[NBLK];
-    uint8_t flag[NBLK];
 };
 
 // st.id[] (-1 = none) must be written and synchronised before the call;
@@ -578,20 +577,13 @@ __device__ void stage_blocks_by(MeshOf mesh_of, BlockStage<Lt, NBLK> &st) {
         const int s = e / Lt::NB, p = e - s * Lt::NB;
         const int B = st.id[s];
         int32_t v = 0, h = -1;
-        uint8_t fl = 0;
         if (B >= 0) {
             const DevMesh &m = mesh_of(s);
             v = m.nbr[(int64_t)p * m.cap + B];
-            if (p == 0) {
-                h = m.hid[B];
-                fl = m.bflag[B];
-            }
+            if (p == 0) h = m.hid[B];
         }
         st.link[s][dir_region<Lt>(p)] = v;
-        if (p == 0) {
-            st.hid[s] = h;
-            st.flag[s] = fl;
-        }
+        if (p == 0) st.hid[s] = h;
     }
     __syncthreads();
 }
@@ -881,7 +873,8 @@ constexpr int collide_threads() { return 256; }
 // 1140, 876, 760, 742, 739, 779.  Uniform D3Q19 FP32 level of 256^3 cells with
 // 3, 4, 5, 6, 7: 531, 510, 517, 520, 526.  FP64 is left to the compiler (2256 to
 // 2386 over runs; 2 to 4 waves 2298 to 2462, 4 with spills).  Smaller levels do
-// not depend on it; BGK only, the other collisions were not swept.
+// not depend on it; k_collide_stream and BGK only, the joined kernel and the
+// other collisions were not swept.
 template <int Q, int S, bool NTS, int COLL>
 constexpr int collide_waves(bool most) {
     if (!(NTS && COLL == 0 && Lat<Q>::D == 3) || S == AMR_F64) return most ? 8 : 1;  // the compiler's choice
@@ -1206,8 +1199,8 @@ __global__ __launch_bounds__(256) void k_interp_collide(const int32_t *__restric
 
 // Batched ghost fill of level L+1 from level L (interface parents of every
 // simulation), persistent teams; par0/par1 = buffers of levels L, L+1.
-// CUB: 0 every member linear, 2 the member's choice (131 instead of 70 VGPRs for
-// D3Q19, so groups without a cubic member do not carry it).
+// CUB: 0 every member linear, 2 the member's choice (131 instead of 77 VGPRs for
+// D3Q19 at 16 bits, so groups without a cubic member do not carry it).
 template <int Q, int S, int CUB>
 __global__ __launch_bounds__(256) void k_interp_batch(const SimDesc *__restrict__ sims,
                                                       const uint32_t *__restrict__ items,
