@@ -47,7 +47,8 @@ struct Ctx {
     int32_t *order;      // [lmax][cap] solver launch order per level (Morton)
     int32_t *solidl;     // [lmax][cap] leaf blocks next to a solid block, per level
     int32_t *gap;        // [cap]
-    int32_t *first;      // [cap] first new child; once these are in place, the halo records' numbers before the change
+    int32_t *first;      // [cap] first new child; once these are in place, the halo records' numbers before the
+                         // change, then whether a record moves
     int32_t *rlist;      // [cap]
     int32_t *scan_part;  // counts of the ordered lists
     int32_t *off;        // [cap] first output cell of each block
@@ -80,10 +81,11 @@ void launch_interp(const Ctx &c, const int32_t *list, int n, const LevelParams &
 // after new children (parents in `list`) were interpolated: the populations of
 // existing same-level neighbour cells that now stream from the new blocks
 void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
-// halo records to their new numbers (m.hid), with what streamed in from blocks
-// that this mesh change removed; old: their numbers before.  After the new
-// numbers, before the new descriptors.
-void launch_move_records(const Ctx &c, const int32_t *old);
+// the blocks' descriptors, and what the mesh change moves of their halo records;
+// old: the records' numbers before, null for a new mesh, overwritten for the next
+void launch_block_desc(const Ctx &c, int32_t *old);
+// the cells that the grid communication of each level moves, and the records back
+void launch_target_cells(const Ctx &c, const int32_t *moved);
 // list: refined blocks of level L; mode 0: interface parent cells; 1: every parent cell
 // U (all_cells = 1): the averaging also writes the criterion velocities of
 // the children it reads that have no N_SKIP link

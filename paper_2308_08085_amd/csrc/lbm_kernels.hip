@@ -1310,22 +1310,40 @@ __global__ __launch_bounds__(256) void k_refresh_neighbours(const int32_t *__res
 // its neighbour C was removed, the populations that streamed from C's cells are
 // in C's rows and belong to the record from now on.  The next step's ghost
 // fill rewrites all of it, but a synchronisation may come first, and its
-// averaging reads it.  BACK = false: what the block needs, to its new number in
-// the buffer that is free between steps; true: back from there.  (Not moved,
-// records held another block's values or zeros after a change that no step
-// followed.  Records at the block's own ID would not have to move, but so
-// spread out they cost the steps of the 64^3 D3Q19 cavity 2 to 4 %.)
+// averaging reads it.  So what a block needs goes to its new number in the
+// buffer that is free between steps (records_out), and back from there once
+// all have (records_back).  (Not moved, records held another block's values or
+// zeros after a change that no step followed.  Records at the block's own ID
+// would not have to move, but so spread out they cost the steps of the 64^3
+// D3Q19 cavity 2 to 4 %.)
 //
-// 64 block IDs per workgroup: their numbers in one coalesced read, then each
-// block that has something to move by one wave.  Bound by their launches, two
-// beside the 31 others of a mesh change with three levels.
-template <int Q, int S, bool BACK>
-__global__ __launch_bounds__(256) void k_move_records(DevMesh m, const DevCounters *ctr, const int32_t *__restrict__ old,
-                                                      const typename Store<S>::T *__restrict__ src,
-                                                      typename Store<S>::T *__restrict__ dst) {
+// 64 block IDs per 256-thread workgroup: their numbers in one coalesced read,
+// then each block that has something to move by one wave.  Both halves ride on
+// launches that a mesh change makes anyway: 6 us more of a change of a small 2-D
+// mesh (210 us), chains of dependent loads; as launches of their own 10 to 15 us.
+
+// populations of every cell of a block that come from a region whose entry in
+// `links` is not kNone, by its MB lanes: at(p, record entry, region's entry,
+// source cell)
+template <typename Lt, typename F>
+__device__ __forceinline__ void for_record_entries(const int32_t *links, int l, F &&at) {
+    static_for<Lt::Q>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        const int sx = (l & 3) - Lt::cx(p), sy = ((l >> 2) & 3) - Lt::cy(p), sz = (l >> 4) - Lt::cz(p);
+        const int rg = region_of<Lt>(sx, sy, sz);
+        const int32_t code = rg == kCenterSlot<Lt> ? kNone : links[rg];
+        if (code != kNone)
+            at(pc, halo_entry<Lt, p>((uint64_t(1) << l) - 1), code, (sx & 3) + 4 * (sy & 3) + 16 * (sz & 3));
+    });
+}
+
+// `old`: the records' numbers before the change; on return whether they move.
+// Descriptors, and the rows of removed blocks, are those before the change.
+template <int Q, typename T>
+__device__ __forceinline__ void records_out(const DevMesh &m, const DevCounters *ctr, int32_t *old,
+                                            const T *__restrict__ src, T *__restrict__ dst, int32_t *links) {
     using Lt = Lat<Q>;
     using De = Desc<Lt::D>;
-    __shared__ int32_t links[4][De::kLinks];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int B0 = blockIdx.x * 64;
     // a number that stays may still gain entries from a removed block
@@ -1335,9 +1353,11 @@ __global__ __launch_bounds__(256) void k_move_records(DevMesh m, const DevCounte
         now = m.hid[B0 + lane];
         was = old[B0 + lane];
     }
-    const bool move = now >= 0 && (removed || now != was) && !m.fresh[B0 + lane];
+    const uint64_t look = __ballot(now >= 0 && (removed || now != was) && !m.fresh[min(B0 + lane, m.cap - 1)]);
+    __syncthreads();  // every wave has read `old`
+    if (wave == 0 && B0 + lane < m.cap && !((look >> lane) & 1ull)) old[B0 + lane] = 0;
     int k = 0;
-    for (uint64_t todo = __ballot(move); todo; todo &= todo - 1) {
+    for (uint64_t todo = look; todo; todo &= todo - 1) {
         if ((k++ & 3) != wave) continue;
         const int i = __builtin_ctzll(todo), B = B0 + i;
         const int nw = __shfl(now, i, 64), wa = __shfl(was, i, 64);
@@ -1345,29 +1365,126 @@ __global__ __launch_bounds__(256) void k_move_records(DevMesh m, const DevCounte
         int32_t w = kNone;
         if (lane < De::kLinks) {
             w = m.desc[(int64_t)B * De::kWords + lane];
-            if (w >= 0) w = m.status[w] == ST_INACTIVE ? w : kNone;
-            else if (w != kNSkip || wa < 0 || wa == nw) w = kNone;
-            links[wave][lane] = w;
+            if (w >= 0 ? m.status[w] != ST_INACTIVE : w != kNSkip) w = kNone;
+            links[lane] = w;
         }
-        if (!__any(w != kNone)) continue;
+        const bool moves = wa != nw || __any(w >= 0);
+        if (lane == 0) old[B] = moves;
+        if (!moves) continue;
         wave_lds_sync();
-        typedef typename Store<S>::T T;
         T *rec = dst + (m.halo_base + (int64_t)nw * m.nh);
-        const T *at = src + (m.halo_base + (int64_t)(BACK ? nw : wa) * m.nh);
+        const T *from = src + (m.halo_base + (int64_t)wa * m.nh);
         if (lane < Lt::MB)
-            static_for<Q>([&](auto pc) {
-                constexpr int p = decltype(pc)::value;
-                const int sx = (lane & 3) - Lt::cx(p), sy = ((lane >> 2) & 3) - Lt::cy(p), sz = (lane >> 4) - Lt::cz(p);
-                const int rg = region_of<Lt>(sx, sy, sz);
-                const int32_t code = rg == kCenterSlot<Lt> ? kNone : links[wave][rg];
-                if (code != kNone) {
-                    const uint32_t e = halo_entry<Lt, p>((uint64_t(1) << lane) - 1);
-                    rec[e] = BACK || code < 0 ? at[e]
-                                              : src[mslot<Lt>(code, p, (sx & 3) + 4 * (sy & 3) + 16 * (sz & 3))];
-                }
+            for_record_entries<Lt>(links, lane, [&](auto pc, uint32_t e, int32_t code, int s) {
+                rec[e] = code < 0 ? from[e] : src[mslot<Lt>(code, decltype(pc)::value, s)];
             });
         wave_lds_sync();
     }
+}
+
+// moved: as records_out left it; the descriptors are the new ones
+template <int Q, typename T>
+__device__ __forceinline__ void records_back(const DevMesh &m, const int32_t *__restrict__ moved, int wg,
+                                             const T *__restrict__ src, T *__restrict__ dst, int32_t *links) {
+    using Lt = Lat<Q>;
+    using De = Desc<Lt::D>;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int B0 = wg * 64;
+    int k = 0;
+    for (uint64_t todo = __ballot(B0 + lane < m.cap && moved[B0 + lane] != 0); todo; todo &= todo - 1) {
+        if ((k++ & 3) != wave) continue;
+        const int B = B0 + __builtin_ctzll(todo);
+        const int32_t w = lane < De::kWords ? m.desc[(int64_t)B * De::kWords + lane] : 0;
+        if (lane < De::kLinks) links[lane] = w == kNSkip ? w : kNone;
+        const int64_t rec = m.halo_base + (int64_t)__shfl(w, De::kHid, 64) * m.nh;
+        wave_lds_sync();
+        if (lane < Lt::MB)
+            for_record_entries<Lt>(links, lane, [&](auto, uint32_t e, int32_t, int) { dst[rec + e] = src[rec + e]; });
+        wave_lds_sync();
+    }
+}
+
+// Packed block descriptors (Desc): one workgroup turns the links of 64
+// consecutive blocks, read along each link array, into 64 rows through LDS.
+// Before it overwrites the descriptors of the mesh before, it moves what their
+// halo records need (old: null for a new mesh).
+template <int Q, int S>
+__global__ __launch_bounds__(256) void k_block_desc(DevMesh m, const DevCounters *ctr, int32_t *old,
+                                                    const typename Store<S>::T *__restrict__ f0,
+                                                    typename Store<S>::T *__restrict__ f1) {
+    using Dd = Lat<Q>;
+    using De = Desc<Dd::D>;
+    constexpr int NW = De::kWords;
+    __shared__ int32_t row[64][NW + 1];
+    if (old) {
+        records_out<Q>(m, ctr, old, f0, f1, row[threadIdx.x >> 6]);
+        __syncthreads();
+    }
+    const int B0 = blockIdx.x * 64;
+    const int b = threadIdx.x & 63, B = B0 + b;
+    const bool act = B < m.cap && m.status[B] != ST_INACTIVE;
+    for (int p = threadIdx.x >> 6; p < NW; p += 4) {
+        int32_t v = 0;
+        if (act) {
+            if (p < Dd::NB) v = m.nbr[(int64_t)p * m.cap + B];
+            else if (p == De::kHid) v = m.hid[B];
+            else if (p == De::kFlags)
+                v = (int32_t)(m.bflag[B] | (m.status[B] == ST_UNREF ? DF_LEAF : 0u) | ((uint32_t)m.level[B] << 16));
+            else if (p == De::kFirst) v = m.nbrc[B];
+            else if (p == De::kGhost)
+                v = Dd::D == 3 ? (int32_t)m.gmask[B] : (int32_t)(m.gmask[B] | m.imask[B] << 16);
+            else if (Dd::D == 3) v = (int32_t)(m.gmask[B] >> 32);
+        }
+        const int at = p < Dd::NB ? dir_region<Dd>(p) : p;
+        row[b][at] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 64 * NW; e += 256)
+        if (B0 + e / NW < m.cap) m.desc[(int64_t)B0 * NW + e] = row[e / NW][e % NW];
+}
+
+// Cells the interpolation and the averaging of each level move (for the
+// byte counts of the solver's kernel statistics): over the interface parents
+// of level L, the ghost cells of their children and the parent cells whose
+// first fine cell (even i, j, k) is an interface cell.
+// One thread per interface parent of one level; the sums are reduced over the
+// wave before one atomic per wave.
+template <typename Lt>
+__device__ __forceinline__ void target_cells(const DevMesh &m, const int32_t *__restrict__ iface, DevCounters *ctr,
+                                             int L, int i) {
+    unsigned long long g = 0, a = 0;
+    if (i < ctr->niface[L]) {
+        const int P = iface[(int64_t)L * m.cap + i];
+        const int first = m.nbrc[P];
+        // fine cells with even coordinates: the first of each parent cell's 2^d
+        const uint64_t lead = Lt::D == 3 ? 0x0000050500000505ull : 0x0505ull;
+        if (first >= 0 && first <= m.cap - Lt::NC)
+            for (int c = 0; c < Lt::NC; c++) {
+                g += __popcll(m.gmask[first + c]);
+                a += __popcll(m.imask[first + c] & lead);
+            }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        g += __shfl_xor(g, off, 64);
+        a += __shfl_xor(a, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (g) atomicAdd(&ctr->ghost_w[L], g);
+        if (a) atomicAdd(&ctr->avg_w[L], a);
+    }
+}
+
+// The first workgroups take the records that moved, 64 block IDs each (none for
+// a new mesh), the others the levels, `per` each.
+template <int Q, int S>
+__global__ __launch_bounds__(256) void k_target_cells(DevMesh m, const int32_t *__restrict__ iface, DevCounters *ctr,
+                                                      const int32_t *__restrict__ moved, int nrec, int per,
+                                                      typename Store<S>::T *__restrict__ f0,
+                                                      const typename Store<S>::T *__restrict__ f1) {
+    __shared__ int32_t links[4][Desc<Lat<Q>::D>::kLinks];
+    const int wg = (int)blockIdx.x - nrec;
+    if (wg < 0) records_back<Q>(m, moved, blockIdx.x, f1, f0, links[threadIdx.x >> 6]);
+    else target_cells<Lat<Q>>(m, iface, ctr, wg / per, wg % per * 256 + (int)threadIdx.x);
 }
 
 static __global__ void k_clear_fresh(const int32_t *__restrict__ list, int n, DevMesh m, int nc) {
@@ -2199,7 +2316,8 @@ struct Launch {
     static void average_batch(hipStream_t stream, const SimDesc *sims, const uint32_t *items, const int32_t *count,
                               int L, int par0, int par1, const BatchShape &s);
     static void refresh_neighbours(const Ctx &c, const int32_t *list, int n, const LevelParams &lp);
-    static void move_records(const Ctx &c, const int32_t *old);
+    static void block_desc(const Ctx &c, int32_t *old);
+    static void target_cells(const Ctx &c, const int32_t *moved);
     static void average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells,
                         double *U);
     static void fill_rest(const Ctx &c);
@@ -2363,10 +2481,15 @@ void Launch<Q, S>::refresh_neighbours(const Ctx &c, const int32_t *list, int n, 
 // Buffers: mesh changes come between coarse steps, when every level above 0 is
 // back in buffer 0; level 0 has no records.
 template <int Q, int S>
-void Launch<Q, S>::move_records(const Ctx &c, const int32_t *old) {
-    const int grid = (c.m.cap + 63) / 64;
-    k_move_records<Q, S, false><<<grid, 256, 0, c.stream>>>(c.m, c.ctr, old, buf<S>(c, 0), buf<S>(c, 1));
-    k_move_records<Q, S, true><<<grid, 256, 0, c.stream>>>(c.m, c.ctr, old, buf<S>(c, 1), buf<S>(c, 0));
+void Launch<Q, S>::block_desc(const Ctx &c, int32_t *old) {
+    k_block_desc<Q, S><<<(c.m.cap + 63) / 64, 256, 0, c.stream>>>(c.m, c.ctr, old, buf<S>(c, 0), buf<S>(c, 1));
+}
+
+template <int Q, int S>
+void Launch<Q, S>::target_cells(const Ctx &c, const int32_t *moved) {
+    const int nrec = moved ? (c.m.cap + 63) / 64 : 0, per = (c.m.cap + 255) / 256;
+    k_target_cells<Q, S><<<nrec + per * c.m.lmax, 256, 0, c.stream>>>(c.m, c.iface, c.ctr, moved, nrec, per,
+                                                                    buf<S>(c, 0), buf<S>(c, 1));
 }
 
 template <int Q, int S>
@@ -2499,8 +2622,12 @@ void launch_refresh_neighbours(const Ctx &c, const int32_t *list, int n, const L
     k_clear_fresh<<<(n * c.nc + 255) / 256, 256, 0, c.stream>>>(list, n, c.m, c.nc);
 }
 
-void launch_move_records(const Ctx &c, const int32_t *old) {
-    dispatch(c.q, c.storage, [&](auto l) { l.move_records(c, old); });
+void launch_block_desc(const Ctx &c, int32_t *old) {
+    dispatch(c.q, c.storage, [&](auto l) { l.block_desc(c, old); });
+}
+
+void launch_target_cells(const Ctx &c, const int32_t *moved) {
+    dispatch(c.q, c.storage, [&](auto l) { l.target_cells(c, moved); });
 }
 
 void launch_average(const Ctx &c, const int32_t *list, int n, int L, const LevelParams &lp, int all_cells, double *U) {

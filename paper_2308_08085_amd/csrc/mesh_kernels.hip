@@ -323,7 +323,7 @@ struct InitJob : BlockJob {
 template <typename Dd>
 __global__ void k_block_masks(DevMesh m, DevCounters *ctr) {
     const int B = blockIdx.x * blockDim.x + threadIdx.x;
-    if (B < kMaxLevels) ctr->ghost_w[B] = ctr->avg_w[B] = 0;  // for k_target_cells
+    if (B < kMaxLevels) ctr->ghost_w[B] = ctr->avg_w[B] = 0;  // for k_target_cells (lbm_kernels.hip)
     if (B >= m.cap) return;
     if (m.status[B] == ST_INACTIVE) {
         m.bflag[B] = 0;
@@ -370,36 +370,6 @@ __global__ void k_parent_mask(DevMesh m) {
     bool any = false;
     for (int c = 0; c < Dd::NC; c++) any = any || (m.bflag[c0 + c] & BF_NSKIP);
     if (any) m.bflag[B] = m.bflag[B] | BF_PARENT_MASK;
-}
-
-// Packed block descriptors (Desc): one workgroup turns the links of 64
-// consecutive blocks, read along each link array, into 64 rows through LDS.
-template <typename Dd>
-__global__ __launch_bounds__(256) void k_block_desc(DevMesh m) {
-    using De = Desc<Dd::D>;
-    constexpr int NW = De::kWords;
-    __shared__ int32_t row[64][NW + 1];
-    const int B0 = blockIdx.x * 64;
-    const int b = threadIdx.x & 63, B = B0 + b;
-    const bool act = B < m.cap && m.status[B] != ST_INACTIVE;
-    for (int p = threadIdx.x >> 6; p < NW; p += 4) {
-        int32_t v = 0;
-        if (act) {
-            if (p < Dd::NB) v = m.nbr[(int64_t)p * m.cap + B];
-            else if (p == De::kHid) v = m.hid[B];
-            else if (p == De::kFlags)
-                v = (int32_t)(m.bflag[B] | (m.status[B] == ST_UNREF ? DF_LEAF : 0u) | ((uint32_t)m.level[B] << 16));
-            else if (p == De::kFirst) v = m.nbrc[B];
-            else if (p == De::kGhost)
-                v = Dd::D == 3 ? (int32_t)m.gmask[B] : (int32_t)(m.gmask[B] | m.imask[B] << 16);
-            else if (Dd::D == 3) v = (int32_t)(m.gmask[B] >> 32);
-        }
-        const int at = p < Dd::NB ? offset_slot(Dd::cx(p), Dd::cy(p), Dd::cz(p)) - (Dd::D == 2 ? 9 : 0) : p;
-        row[b][at] = v;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 64 * NW; e += 256)
-        if (B0 + e / NW < m.cap) m.desc[(int64_t)B0 * NW + e] = row[e / NW][e % NW];
 }
 
 // ---------------------------------------------------------------------------
@@ -873,39 +843,6 @@ struct SweepJob : BlockJob {
     __device__ void done(const DevMesh &, DevCounters *ctr, const int32_t *tot) const { ctr->nsweep[L] = tot[0]; }
 };
 
-// Cells the interpolation and the averaging of each level move (for the
-// byte counts of the solver's kernel statistics): over the interface parents
-// of level L, the ghost cells of their children and the parent cells whose
-// first fine cell (even i, j, k) is an interface cell.
-// One thread per interface parent of one level (grid y = level); the sums
-// are reduced over the wave before one atomic per wave.
-template <typename Dd>
-__global__ __launch_bounds__(256) void k_target_cells(DevMesh m, const int32_t *__restrict__ iface,
-                                                      DevCounters *ctr) {
-    const int L = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long g = 0, a = 0;
-    if (i < ctr->niface[L]) {
-        const int P = iface[(int64_t)L * m.cap + i];
-        const int first = m.nbrc[P];
-        // fine cells with even coordinates: the first of each parent cell's 2^d
-        const uint64_t lead = Dd::D == 3 ? 0x0000050500000505ull : 0x0505ull;
-        if (first >= 0 && first <= m.cap - Dd::NC)
-            for (int c = 0; c < Dd::NC; c++) {
-                g += __popcll(m.gmask[first + c]);
-                a += __popcll(m.imask[first + c] & lead);
-            }
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        g += __shfl_xor(g, off, 64);
-        a += __shfl_xor(a, off, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        if (g) atomicAdd(&ctr->ghost_w[L], g);
-        if (a) atomicAdd(&ctr->avg_w[L], a);
-    }
-}
-
 // changed: the mesh was another one before, whose descriptors are still there
 template <typename Dd>
 void masks_and_lists(const Ctx &c, bool changed) {
@@ -914,15 +851,14 @@ void masks_and_lists(const Ctx &c, bool changed) {
     k_parent_mask<Dd><<<grid_for(cap), 256, 0, c.stream>>>(c.m);
     run_lists(c, HaloJob{{1}, c.first}, SolidJob{{lmax}, c.solidl}, OutListJob{{1}, c.outl, c.mb}, OutOffsetJob{{1}, c.off, c.mb},
               RefinedJob<true>{{lmax}, c.ids, c.iface}, RefinedJob<false>{{lmax}, c.ids, c.refl});
-    if (changed) launch_move_records(c, c.first);
-    k_block_desc<Dd><<<grid_for(cap, 64), 256, 0, c.stream>>>(c.m);
+    launch_block_desc(c, changed ? c.first : nullptr);
     for (int L = 0; L < lmax; L++) {
         const int32_t *cur = c.order + (size_t)L * cap;
         const SweepJob sweep{{1}, cur, c.sweep + (size_t)L * cap, L};
         if (L + 1 < lmax) run_lists(c, OrderJob{{1}, cur, c.order + (size_t)(L + 1) * cap, L, Dd::NC}, sweep);
         else run_lists(c, sweep);
     }
-    k_target_cells<Dd><<<dim3(grid_for(cap), lmax), 256, 0, c.stream>>>(c.m, c.iface, c.ctr);
+    launch_target_cells(c, changed ? c.first : nullptr);
 }
 
 template <typename Dd>
