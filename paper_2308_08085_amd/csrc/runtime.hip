@@ -224,10 +224,10 @@ void timed_launch(amr_handle *h, int kind, int blocks, int L, F &&fn) {
 
 // Outside profiled runs (which time each kernel on its own) BGK sweeps save
 // launch gaps: a sweep adds the momentum exchange itself (the variant needs at
-// most 7 more VGPRs; a joined one with streaming stores does not have it), and on small levels the ghost interpolation into level
-// L+1 joins the sweep.  Large levels gain nothing from it (D3Q27 cylinder, every
-// level joined: 9.72 ms per coarse step with FP32 and 5.78 with FP16 storage,
-// apart 9.73 and 5.78).
+// most 7 more VGPRs; joined sweeps with streaming stores have none), and on
+// small levels the ghost interpolation into level L+1 joins the sweep.  Large
+// levels gain nothing from it (D3Q27 cylinder, every level joined: 9.72 ms per
+// coarse step with FP32 and 5.78 with FP16 storage, apart 9.73 and 5.78).
 static bool join_launches(const amr_handle *h) { return h->c.coll == AMR_COLLIDE_BGK && !h->profiling; }
 
 static bool small_level(const amr_handle *h, int L) {
