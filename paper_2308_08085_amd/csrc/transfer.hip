@@ -18,8 +18,9 @@
 //
 // us to pageable memory, runtime's path and ring:
 //   copy of 1.3 MB   80 and 110      rho, u of 0.13 MB   75 and  20
-//           4.5 MB  260 and 250                  2.1 MB  205 and 130
+//           3.2 MB  200 and 190                  2.1 MB  205 and 130
 //          10.6 MB  620 and 415                 28.3 MB 1840 and 820
+// (3.2 MB to memory that was never touched 240 and 210),
 // and to pinned memory, staging area and ring:
 //   rho, u of 0.13 MB  70 and 20, 1.0 MB 43 and 87, 28.3 MB 545 and 822.
 #include <algorithm>
@@ -42,7 +43,7 @@ constexpr int kPinFrom = 32;
 // 25 us, the runtime 19 to 98) and from kRingCopyLarge on (several threads);
 // gathers always, but into pinned memory of the caller only below
 // kPinnedDirectFrom.
-constexpr uint64_t kRingCopySmall = uint64_t(512) << 10, kRingCopyLarge = uint64_t(4) << 20;
+constexpr uint64_t kRingCopySmall = uint64_t(512) << 10, kRingCopyLarge = uint64_t(3) << 20;
 constexpr uint64_t kPinnedDirectFrom = uint64_t(1) << 20;
 constexpr int kSlots = 8, kMaxWorkers = 6;
 constexpr size_t kWorkerBytes = size_t(2) << 20;  // one host thread per this much of a transfer: starting one takes 20 us
